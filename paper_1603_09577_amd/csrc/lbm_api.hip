@@ -41,7 +41,8 @@ struct lbm_ctx {
     Dims dm;
     Geom g;
     size_t coef_bytes;
-    unsigned char host_coefs[sizeof(Coefs<double>)];
+    alignas(16) unsigned char host_coefs[sizeof(Coefs<double>)];
+    double wall_cb[6][kMaxC];   // C-bar of the description in FP64, for the wall terms
     void *d_coefs = nullptr;
     // device scratch: [flag int (256 B)] [reduce partials] [reduce out 8] [adj partials] [k0 acc 8]
     // [offset shift 8]
@@ -148,23 +149,32 @@ double polyval(const double *c, int n, double x) {
     return acc;
 }
 
-// e+_k(pw): the even part of Eq. 3 at a wall value, from the C-bar
-// polynomials already in m (so Remark III's C = 0 carries over).
-double wall_even(const HostModel &m, const Dims &dm, double pw, int k) {
+// ewp[side * 19 + k] = 2 e+_k(phi_w) of both walls, e+ the even part of Eq. 3
+// at the wall value, from the C-bar polynomials (so Remark III's C = 0 carries
+// over).
+void wall_terms(const double cb[6][kMaxC], const Dims &dm, const lbm_desc &d, double *ewp) {
     const int dim = dm.q == 9 ? 2 : 3;
-    double E[6];
-    for (int i = 0; i < 6; ++i) E[i] = polyval(m.cb[i], kMaxC, pw) - (i < dim ? pw / 3.0 : 0.0);
-    if (dim == 2) E[2] = 0.0;
-    const double tr3 = (E[0] + E[1] + E[2]) / 3.0;
-    int c[3];
-    double w;
-    if (dm.q == 9) { c[0] = Lattice<9>::cx(k); c[1] = Lattice<9>::cy(k); c[2] = 0; w = Lattice<9>::w(k); }
-    else { c[0] = Lattice<19>::cx(k); c[1] = Lattice<19>::cy(k); c[2] = Lattice<19>::cz(k); w = Lattice<19>::w(k); }
-    double cc = -tr3;
-    for (int a = 0; a < 3; ++a) cc += c[a] * c[a] * E[a];
-    cc += 2.0 * (c[0] * c[1] * E[3] + c[1] * c[2] * E[4] + c[0] * c[2] * E[5]);
-    return w * (pw + 4.5 * cc);
+    for (int side = 0; side < 2; ++side) {
+        const double pw = d.phi_wall[dim - 1][side];
+        double E[6];
+        for (int i = 0; i < 6; ++i) E[i] = polyval(cb[i], kMaxC, pw) - (i < dim ? pw / 3.0 : 0.0);
+        if (dim == 2) E[2] = 0.0;
+        const double tr3 = (E[0] + E[1] + E[2]) / 3.0;
+        for (int k = 0; k < 19; ++k) {
+            if (k >= dm.q) { ewp[side * 19 + k] = 0.0; continue; }
+            int c[3];
+            double w;
+            if (dm.q == 9) { c[0] = Lattice<9>::cx(k); c[1] = Lattice<9>::cy(k); c[2] = 0; w = Lattice<9>::w(k); }
+            else { c[0] = Lattice<19>::cx(k); c[1] = Lattice<19>::cy(k); c[2] = Lattice<19>::cz(k); w = Lattice<19>::w(k); }
+            double cc = -tr3;
+            for (int a = 0; a < 3; ++a) cc += c[a] * c[a] * E[a];
+            cc += 2.0 * (c[0] * c[1] * E[3] + c[1] * c[2] * E[4] + c[0] * c[2] * E[5]);
+            ewp[side * 19 + k] = 2.0 * (w * (pw + 4.5 * cc));
+        }
+    }
 }
+
+double weight(const Dims &dm, int k) { return dm.q == 9 ? Lattice<9>::w(k) : Lattice<19>::w(k); }
 
 // All derived constants of a description (FP64).
 void derive(const lbm_desc &d, const Dims &dm, HostModel &m) {
@@ -216,14 +226,9 @@ void derive(const lbm_desc &d, const Dims &dm, HostModel &m) {
     m.nr = std::max(1, top_count(d.rpoly, kMaxP));
     // anti-bounce-back constants: 2 (e+_k(phi_w) - w_k phi_ref), e+ the even
     // part of Eq. 3 at the wall value
-    const int la = dim - 1;
+    wall_terms(m.cb, dm, d, &m.ewp[0][0]);
     for (int side = 0; side < 2; ++side)
-        for (int k = 0; k < dm.q; ++k) {
-            const double w = dm.q == 9 ? Lattice<9>::w(k) : Lattice<19>::w(k);
-            const double ep = wall_even(m, dm, d.phi_wall[la][side], k);
-            m.ewp[side][k] = 2.0 * ep;
-            m.ew[side][k] = 2.0 * (ep - w * d.phi_ref);
-        }
+        for (int k = 0; k < dm.q; ++k) m.ew[side][k] = m.ewp[side][k] - 2.0 * (weight(dm, k) * d.phi_ref);
     for (int i = 0; i < 19; ++i) m.s[i] = (i < dm.q) ? d.s[i] : 0.0;
     m.srate = d.s[1];
     m.phi_ref = d.phi_ref;
@@ -333,25 +338,22 @@ int validate(const lbm_desc *d, Dims &dm) {
     return LBM_OK;
 }
 
-// Derive and pack the constants of c->desc into c->host_coefs (no upload).
-void pack_host(lbm_ctx *c, HostModel &m) {
-    derive(c->desc, c->dm, m);
-    if (c->dm.prec == 0) {
-        Coefs<double> cf;
-        pack(m, cf);
-        std::memcpy(c->host_coefs, &cf, sizeof(cf));
-        c->coef_bytes = sizeof(cf);
-    } else {
-        Coefs<float> cf;
-        pack(m, cf);
-        std::memcpy(c->host_coefs, &cf, sizeof(cf));
-        c->coef_bytes = sizeof(cf);
-    }
+// New wall terms 2 e+_k(phi_w) in the host copy of the constants.
+template <typename TC>
+void store_walls(lbm_ctx *c, const double *ewp) {
+    Coefs<TC> *cf = reinterpret_cast<Coefs<TC> *>(c->host_coefs);
+    for (int side = 0; side < 2; ++side)
+        for (int k = 0; k < c->dm.q; ++k) {
+            const double e = ewp[side * 19 + k];
+            cf->ewp[side][k] = (TC)e;
+            cf->ew[side][k] = (TC)(e - 2.0 * (weight(c->dm, k) * c->desc.phi_ref));
+        }
 }
 
 int upload_coefs(lbm_ctx *c) {
     HostModel m;
     derive(c->desc, c->dm, m);
+    std::memcpy(c->wall_cb, m.cb, sizeof(m.cb));
     if (c->dm.prec == 0) {
         Coefs<double> cf;
         pack(m, cf);
@@ -892,11 +894,14 @@ int lbm_set_phi_wall(lbm_ctx *c, double phi_lo, double phi_hi, void *stream) {
     const int la = (c->dm.q == 9 ? 2 : 3) - 1;
     c->desc.phi_wall[la][0] = phi_lo;
     c->desc.phi_wall[la][1] = phi_hi;
-    HostModel m;
-    pack_host(c, m);   // the host copy (restored by lbm_init) carries the new values too
+    // Only the wall terms depend on the wall values; the host copy (restored by
+    // lbm_init) carries the new ones too.  A program that moves its walls every
+    // step pays for this call as often as for a sweep, and deriving and packing
+    // the whole model here took longer than the kernel it launches.
     double ewp[2 * 19];
-    for (int s = 0; s < 2; ++s)
-        for (int k = 0; k < 19; ++k) ewp[s * 19 + k] = m.ewp[s][k];
+    wall_terms(c->wall_cb, c->dm, c->desc, ewp);
+    if (c->dm.prec == 0) store_walls<double>(c, ewp);
+    else store_walls<float>(c, ewp);
     hipError_t e = c->dm.q == 9 ? launch_set_wall_q9(c->dm, c->d_coefs, ewp, (hipStream_t)stream)
                                 : launch_set_wall_q19(c->dm, c->d_coefs, ewp, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "wall kernel");

@@ -207,14 +207,16 @@ def desc_from_spec(spec, flags=0):
 
 
 def _stream(stream):
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        # the handle of torch.cuda.current_stream(), without building its Stream
+        # object: a few microseconds on every call, as much as a small sweep takes
+        import torch
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _ptr(t):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 class Lbm:
