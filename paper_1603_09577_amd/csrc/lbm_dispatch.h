@@ -336,7 +336,8 @@ hipError_t sweep2_3d_typed(const Dims &dm, const Geom &g, const void *coefs, con
     }
 }
 
-// Scheme B and/or per-node fields: the general kernel (any polynomial length).
+// Scheme B and/or per-node fields: the general kernel, in its 3-term form where
+// every polynomial has degree <= 2 and every array spans less than 4 GiB.
 template <int Q, typename TS, typename TC>
 hipError_t sweep_gen_typed(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
                            void *p, int *flag, const double *kfield, const double *rfield, bool remark3,
@@ -347,15 +348,17 @@ hipError_t sweep_gen_typed(const Dims &dm, const Geom &g, const void *coefs, con
     auto *fo = (TS *)fout;
     auto *pp = (TP *)p;
     const dim3 grid(g.nblocks), block(kBlock);
-    const int code = (dm.eqr ? 4 : 0) | (dm.wall ? 2 : 0) | (dm.sb ? 1 : 0);
-#define LBM_GEN(E, W, B)                                                                            \
-    case (E * 4 + W * 2 + B):                                                                       \
-        hipLaunchKernelGGL((k_sweep_gen<Q, TS, TC, E, W, B>), grid, block, 0, st, g, cf, fi, fo, pp, flag, \
+    const int code = (dm.eqr ? 4 : 0) | (dm.wall ? 2 : 0) | (dm.sb ? 1 : 0) | (dm.deg3 && dm.o32 ? 8 : 0);
+#define LBM_GEN(E, W, B, NP)                                                                        \
+    case ((NP == 3) * 8 + E * 4 + W * 2 + B):                                                       \
+        hipLaunchKernelGGL((k_sweep_gen<Q, TS, TC, E, W, B, NP>), grid, block, 0, st, g, cf, fi, fo, pp, flag, \
                            kfield, rfield, remark3 ? 1 : 0);                                        \
         break;
     switch (code) {
-        LBM_GEN(0, 0, 0) LBM_GEN(0, 0, 1) LBM_GEN(0, 1, 0) LBM_GEN(0, 1, 1)
-        LBM_GEN(1, 0, 0) LBM_GEN(1, 0, 1) LBM_GEN(1, 1, 0) LBM_GEN(1, 1, 1)
+        LBM_GEN(0, 0, 0, 9) LBM_GEN(0, 0, 1, 9) LBM_GEN(0, 1, 0, 9) LBM_GEN(0, 1, 1, 9)
+        LBM_GEN(1, 0, 0, 9) LBM_GEN(1, 0, 1, 9) LBM_GEN(1, 1, 0, 9) LBM_GEN(1, 1, 1, 9)
+        LBM_GEN(0, 0, 0, 3) LBM_GEN(0, 0, 1, 3) LBM_GEN(0, 1, 0, 3) LBM_GEN(0, 1, 1, 3)
+        LBM_GEN(1, 0, 0, 3) LBM_GEN(1, 0, 1, 3) LBM_GEN(1, 1, 0, 3) LBM_GEN(1, 1, 1, 3)
         default: return hipErrorInvalidValue;
     }
 #undef LBM_GEN

@@ -998,8 +998,6 @@ k_sweep2(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ 
     sweep2_tile<TS, TC, SRC, KVAR, NP, TH, NW, SB, WALL, EQ>(g, cf, fin, fout, pin, pout, tx, ty, flag);
 }
 
-// The general sweep: Scheme B and/or per-node fields.  Polynomials of any
-// length, K(phi) evaluated per node, Scheme-A history kept when SB is off.
 // ---------------------------------------------------------------------------
 // Two time steps per pass for D3Q19 (3-term polynomials; walls on z or
 // periodic).  A workgroup owns a column of 62 x TY nodes in x and y and a
@@ -1227,15 +1225,21 @@ k_sweep2_3d(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict
     if (bad) *flag = 1;
 }
 
-template <int Q, typename TS, typename TC, bool EQR, bool WALL, bool SB>
+// The general sweep: Scheme B and/or per-node fields.  Scheme-A history kept
+// when SB is off.  NP = 3 with 32-bit offsets (every polynomial of degree <= 2,
+// arrays below 4 GiB; the host checks) or NP = 9.  Latency-bound on the grids
+// the fields are used on (400^2: 2500 waves on 1024 SIMDs, one round), so what
+// counts is the chain of one node: evaluating nine terms of polynomials that
+// have two took 8.2 us per FP64 sweep.
+template <int Q, typename TS, typename TC, bool EQR, bool WALL, bool SB, int NP>
 __global__ void __launch_bounds__(kBlock)
 k_sweep_gen(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin,
             TS *__restrict__ fout, typename HistType<TS>::T *p, int *flag, const double *kfield,
             const double *rfield, int remark3) {
     const uint32_t n = block_index(blockIdx.x, gridDim.x, g.remap) * kBlock + threadIdx.x;
     if (n >= g.N) return;
-    sweep_node<Q, TS, TC, EQR, !SB, true, WALL, 9, false, SB, true>(g, cf, fin, fout, p, flag, n, kfield, rfield,
-                                                                   remark3 != 0);
+    sweep_node<Q, TS, TC, EQR, !SB, true, WALL, NP, false, SB, true, NP == 3>(g, cf, fin, fout, p, flag, n, kfield,
+                                                                             rfield, remark3 != 0);
 }
 
 // ---------------------------------------------------------------------------
