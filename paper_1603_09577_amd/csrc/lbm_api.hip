@@ -131,7 +131,7 @@ void sym_inv_host(const double *G, double *A, int dim) {
 struct HostModel {
     double b[3][kMaxP], bp[3][kMaxP], bpp[3][kMaxP], cb[6][kMaxC], cbd[6][kMaxC], g0[6], kp[kMaxP],
         kdp[kMaxP], a[6], r[kMaxP], rp[kMaxP], ew[2][19], ewp[2][19], s[19], phi_ref, srate, k0scale,
-        bq[kMaxP], bqp[kMaxP];
+        bq[kMaxP], bqp[kMaxP], ce[9][kMaxC], cm[3][kMaxC], sn[9];
     int nb, ncb, nk, nr, nq;
 };
 
@@ -232,6 +232,26 @@ void derive(const lbm_desc &d, const Dims &dm, HostModel &m) {
     for (int i = 0; i < 19; ++i) m.s[i] = (i < dm.q) ? d.s[i] : 0.0;
     m.srate = d.s[1];
     m.phi_ref = d.phi_ref;
+    // the collision's even polynomials, E = C-bar - phi/3 I folded with their
+    // constant factors in FP64
+    for (int p = 0; p < kMaxC; ++p) {
+        double E[6];
+        for (int i = 0; i < 6; ++i) E[i] = m.cb[i][p] - (i < dim && p == 1 ? 1.0 / 3.0 : 0.0);
+        if (dim == 2) E[2] = E[4] = E[5] = 0.0;
+        const double tr3 = (E[0] + E[1] + E[2]) / 3.0;
+        const double w1 = dim == 2 ? Lattice<9>::w(1) : Lattice<19>::w(1);
+        const double w2 = dim == 2 ? Lattice<9>::w(8) : Lattice<19>::w(18);
+        for (int a = 0; a < dim; ++a) m.ce[a][p] = 4.5 * m.srate * w1 * (E[a] - tr3);
+        for (int i = 0; i < dim * (dim - 1) / 2; ++i) {
+            m.ce[3 + i][p] = 4.5 * m.srate * w2 * (E[pa[3 + i]] + E[pb[3 + i]] - tr3);
+            m.ce[6 + i][p] = 9.0 * m.srate * w2 * E[3 + i];
+        }
+        m.cm[0][p] = 3.0 * (E[0] + E[1]);
+        m.cm[1][p] = E[0] - E[1];
+        m.cm[2][p] = E[3];
+    }
+    if (dm.q == 9)
+        for (int i = 0; i < 9; ++i) m.sn[i] = d.s[i] / Lattice<9>::N(i);
     // rational flux (Remark III): the denominator and its derivative
     m.nq = 0;
     if (rational_flux(d)) {
@@ -250,15 +270,23 @@ void pack(const HostModel &m, Coefs<TC> &c) {
         }
     for (int i = 0; i < 6; ++i)
         for (int p = 0; p < kMaxC; ++p) { c.cb[i][p] = (TC)m.cb[i][p]; c.cbd[i][p] = (TC)m.cbd[i][p]; }
-    for (int i = 0; i < 6; ++i) { c.g0[i] = (TC)m.g0[i]; c.a[i] = (TC)m.a[i]; }
+    for (int i = 0; i < 6; ++i) { c.g0[i] = (TC)m.g0[i]; c.a[i] = (TC)m.a[i]; c.ah[i] = (TC)(0.5 * m.a[i]); }
+    for (int i = 0; i < 9; ++i)
+        for (int p = 0; p < kMaxC; ++p) c.ce[i][p] = (TC)m.ce[i][p];
+    for (int i = 0; i < 3; ++i)
+        for (int p = 0; p < kMaxC; ++p) c.cm[i][p] = (TC)m.cm[i][p];
+    for (int i = 0; i < 9; ++i) c.sn[i] = (TC)m.sn[i];
     for (int p = 0; p < kMaxP; ++p) {
         c.kp[p] = (TC)m.kp[p]; c.kdp[p] = (TC)m.kdp[p]; c.r[p] = (TC)m.r[p]; c.rp[p] = (TC)m.rp[p];
+        c.rh[p] = (TC)(0.5 * m.r[p]);
     }
     for (int s = 0; s < 2; ++s)
         for (int k = 0; k < 19; ++k) { c.ew[s][k] = (TC)m.ew[s][k]; c.ewp[s][k] = (TC)m.ewp[s][k]; }
     for (int i = 0; i < 19; ++i) c.s[i] = (TC)m.s[i];
     c.phi_ref = (TC)m.phi_ref;
     c.srate = (TC)m.srate;
+    c.shalf = (TC)(0.5 * m.srate);
+    c.oms = (TC)(1.0 - m.srate);
     c.k0scale = (TC)m.k0scale;
     c.nb = m.nb; c.ncb = m.ncb; c.nk = m.nk; c.nr = m.nr;
     for (int p = 0; p < kMaxP; ++p) { c.bq[p] = (TC)m.bq[p]; c.bqp[p] = (TC)m.bqp[p]; }

@@ -52,13 +52,23 @@ struct Coefs {
     TC kp[kMaxP];         // k(phi)
     TC kdp[kMaxP];        // k'(phi)
     TC a[6];              // A when k is constant
+    TC ah[6];             // A / 2
     TC r[kMaxP];          // R(phi)
+    TC rh[kMaxP];         // R(phi) / 2
+    // Even parts of the equal-rate collision with their factors, E = C-bar -
+    // phi/3 I: per axis w1 9/2 s (E_aa - tr E / 3); per plane (xy, yz, xz) of
+    // axes a, b w2 9/2 s (E_aa + E_bb - tr E / 3) and w2 9 s E_ab
+    TC ce[9][kMaxC];
+    // D2Q9 moment-space collision: 3 (Exx + Eyy), Exx - Eyy, Exy
+    TC cm[3][kMaxC];
     TC rp[kMaxP];         // R'(phi)
     TC ew[2][19];         // anti-bounce-back wall terms 2 (e+_k(phi_w) - w_k phi_ref)
     TC ewp[2][19];        // 2 e+_k(phi_w): the wall terms without the offset
     TC s[19];             // diagonal rates in moment order
+    TC sn[9];             // D2Q9: rates over the row norms
     TC phi_ref;
-    TC srate;             // common non-flux rate (equal-rate path)
+    TC srate;             // common non-flux rate s (equal-rate path)
+    TC shalf, oms;        // s / 2 and 1 - s
     TC k0scale;           // 3 / d = dG / d(K0 k)
     int nb, ncb, nk, nr;  // used coefficient counts
     // rational flux B_a = (sum b[a] phi^p) / Q(phi) (Remark III only): Q and Q',

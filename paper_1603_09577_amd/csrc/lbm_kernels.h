@@ -45,10 +45,21 @@ __device__ __forceinline__ TC load_s(const TS *p) {
     return (TC)(*p);
 }
 
+// A value rounded to the storage type.  For FP16 the FP32 value passes through
+// an empty asm first: otherwise the compiler may join its last multiply-add
+// and the conversion into one mixed-precision instruction with one rounding,
+// in some kernels and not in others, and the kernels would no longer agree
+// bit for bit.
+template <typename TS, typename TC>
+__device__ __forceinline__ TS to_store(TC v) {
+    if constexpr (std::is_same<TS, _Float16>::value) asm("" : "+v"(v));
+    return (TS)v;
+}
+
 template <bool NT = false, typename TS, typename TC>
 __device__ __forceinline__ void store_s(TS *p, TC v) {
-    if (NT) __builtin_nontemporal_store((TS)v, p);
-    else *p = (TS)v;
+    if (NT) __builtin_nontemporal_store(to_store<TS>(v), p);
+    else *p = to_store<TS>(v);
 }
 
 // Element idx of an array starting at `base`.  With O32 the host has checked
@@ -144,12 +155,13 @@ __device__ __forceinline__ uint32_t block_index(uint32_t b, uint32_t nb, int rem
 __device__ __forceinline__ double recip(double x) { return 1.0 / x; }
 __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// Symmetric inverse of G (2x2 or 3x3), symmetric storage (xx, yy, zz, xy, yz, xz).
+// Symmetric inverse of G (2x2 or 3x3) times `scale` (a power of two), symmetric
+// storage (xx, yy, zz, xy, yz, xz).
 template <int DIM, typename T>
-__device__ __forceinline__ void sym_inverse(const T *G, T *A) {
+__device__ __forceinline__ void sym_inverse(const T *G, T *A, T scale = T(1)) {
     if (DIM == 2) {
         const T det = G[0] * G[1] - G[3] * G[3];
-        const T id = recip(det);
+        const T id = recip(det) * scale;
         A[0] = G[1] * id;
         A[1] = G[0] * id;
         A[3] = -G[3] * id;
@@ -162,7 +174,7 @@ __device__ __forceinline__ void sym_inverse(const T *G, T *A) {
         const T c12 = G[3] * G[5] - G[0] * G[4];
         const T c02 = G[3] * G[4] - G[5] * G[1];
         const T det = G[0] * c00 + G[3] * c01 + G[5] * c02;
-        const T id = recip(det);
+        const T id = recip(det) * scale;
         A[0] = c00 * id; A[1] = c11 * id; A[2] = c22 * id;
         A[3] = c01 * id; A[4] = c12 * id; A[5] = c02 * id;
     }
@@ -181,16 +193,6 @@ __device__ __forceinline__ void ablock(const Coefs<TC> *__restrict__ cf, TC phi,
 #pragma unroll
         for (int i = 0; i < 6; ++i) A[i] = cf->a[i];
     }
-}
-
-// A = (g0n k(phi) + I/2)^-1 (Eq. 26) with a per-node g0n = 3 K0(x) / d.
-template <int DIM, int NP, typename TC>
-__device__ __forceinline__ void ablock_field(const Coefs<TC> *__restrict__ cf, const TC *g0n, TC phi, TC *A) {
-    const TC kv = poly<NP>(cf->kp, phi);
-    TC G[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) G[i] = g0n[i] * kv + (i < 3 ? TC(0.5) : TC(0));
-    sym_inverse<DIM>(G, A);
 }
 
 // Per-node 3 K0(x) / d from a field of K0 (2-D: xx, yy, xy; 3-D: xx, yy, zz,
@@ -244,6 +246,31 @@ __device__ __forceinline__ void equilibrium(const Coefs<TC> *__restrict__ cf, TC
         if (x && z) ccE += TC(2 * x * z) * E[5];
         feq[k] = TC(L::w(k)) * (phio + TC(3) * cB + TC(4.5) * ccE);
     }
+}
+
+// A / 2, the form the sweep uses (Eq. 26 as above; halving is exact), from the
+// description's K0 or from a per-node g0n = 3 K0(x) / d.
+template <int DIM, bool KVAR, int NP, typename TC>
+__device__ __forceinline__ void ablock_half(const Coefs<TC> *__restrict__ cf, TC phi, TC *Ah) {
+    if (KVAR) {
+        const TC kv = poly<NP>(cf->kp, phi);
+        TC G[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) G[i] = cf->g0[i] * kv + (i < 3 ? TC(0.5) : TC(0));
+        sym_inverse<DIM>(G, Ah, TC(0.5));
+    } else {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) Ah[i] = cf->ah[i];
+    }
+}
+
+template <int DIM, int NP, typename TC>
+__device__ __forceinline__ void ablock_half_field(const Coefs<TC> *__restrict__ cf, const TC *g0n, TC phi, TC *Ah) {
+    const TC kv = poly<NP>(cf->kp, phi);
+    TC G[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) G[i] = g0n[i] * kv + (i < 3 ? TC(0.5) : TC(0));
+    sym_inverse<DIM>(G, Ah, TC(0.5));
 }
 
 // Scheme-A source pieces at one time level: R(phi) and Btilde = (I - A/2) B'
@@ -409,36 +436,52 @@ __device__ __forceinline__ T phi_scheme_b(const Coefs<TC> *__restrict__ cf, T x0
     return x0 + T(0.5) * *R;
 }
 
-// The Scheme-A source terms of one time level at a node: R and Btilde of
-// Eq. 28 (gamma = 0), from which Eq. 9 builds R_k.
+// The Scheme-A source terms of one time level at a node, from which Eq. 9
+// builds R_k: Rh = R / 2 and S = Rh Btilde, Btilde = (I - A/2) B' (Eq. 28,
+// gamma = 0).
 template <typename TC>
 struct SrcLevel {
-    TC R;
-    TC Bt[3];
+    TC Rh;
+    TC S[3];
 };
 
-// Hands this level's terms (R, Bt) to cur and takes the previous level's
-// (Rp, Btp) from prev, or rebuilds them at phi(t - 1) = phi_ref + pp_off.
+template <int D, int NP, typename TC>
+__device__ __forceinline__ SrcLevel<TC> src_level(const Coefs<TC> *__restrict__ cf, TC phi, const TC *Ah) {
+    SrcLevel<TC> lv;
+    TC Bp[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) Bp[a] = (a < D) ? flux_bp<NP>(cf, a, phi) : TC(0);
+    lv.Rh = poly<NP>(cf->rh, phi);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        TC acc = Bp[a];
+#pragma unroll
+        for (int b = 0; b < D; ++b) acc -= Ah[sym(a, b)] * Bp[b];
+        lv.S[a] = (a < D) ? lv.Rh * acc : TC(0);
+    }
+    return lv;
+}
+
+// The previous level's terms: prev if given, else rebuilt at
+// phi(t - 1) = phi_ref + pp_off.
 template <int D, bool KVAR, int NP, typename TC>
-__device__ __forceinline__ void src_levels(const Coefs<TC> *__restrict__ cf, bool kfon, const TC *g0n, TC pp_off,
-                                           TC R, const TC *Bt, SrcLevel<TC> *cur, const SrcLevel<TC> *prev,
-                                           TC &Rp, TC *Btp) {
-    if (cur) {
-        cur->R = R;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) cur->Bt[a] = Bt[a];
-    }
-    if (prev) {
-        Rp = prev->R;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) Btp[a] = prev->Bt[a];
-        return;
-    }
+__device__ __forceinline__ SrcLevel<TC> src_prev(const Coefs<TC> *__restrict__ cf, bool kfon, const TC *g0n, TC pp_off,
+                                                 const SrcLevel<TC> *prev) {
+    if (prev) return *prev;
     TC Ap[6];
     const TC pp = cf->phi_ref + pp_off;
-    if (kfon) ablock_field<D, NP>(cf, g0n, pp, Ap);
-    else ablock<D, KVAR, NP>(cf, pp, Ap);
-    source_terms<D, NP>(cf, pp, Ap, Btp, Rp);
+    if (kfon) ablock_half_field<D, NP>(cf, g0n, pp, Ap);
+    else ablock_half<D, KVAR, NP>(cf, pp, Ap);
+    return src_level<D, NP>(cf, pp, Ap);
+}
+
+// Sum of n values by halves: log2(n) dependent additions instead of n - 1 (a
+// wave on a small grid has no other wave to hide that chain behind).
+template <int N, typename T>
+__device__ __forceinline__ T tree_sum(const T *v) {
+    if constexpr (N == 1) return v[0];
+    else if constexpr (N == 2) return v[0] + v[1];
+    else return tree_sum<(N + 1) / 2>(v) + tree_sum<N / 2>(v + (N + 1) / 2);
 }
 
 // One node of the sweep (shared by the single-instance and batched kernels).
@@ -467,137 +510,232 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
                                            const double *kfield, const double *rfield, bool rem3, TC *out,
                                            SrcLevel<TC> *cur = nullptr, const SrcLevel<TC> *prev = nullptr) {
     using L = Lattice<Q>;
-    constexpr int D = L::dim;
+    constexpr int D = L::dim, P = (Q - 1) / 2;
     TC g0n[6];
     const bool kfon = KF && kfield != nullptr;   // uniform across the launch
     if (kfon) g0_of_field<D>(cf, kfield, n, g0n);
-    TC phio = TC(0);
+    // sums and differences of the P opposite pairs (even and odd parts of h)
+    TC hs[P + 1], hd[P];
+    hs[0] = h[0];
 #pragma unroll
-    for (int k = 0; k < Q; ++k) phio += h[k];
+    for (int i = 0; i < P; ++i) {
+        const int k = L::pair(i), kb = L::opp(k);
+        hs[i + 1] = h[k] + h[kb];
+        hd[i] = h[k] - h[kb];
+    }
+    TC phio = tree_sum<P + 1>(hs);
     // Scheme B: phi from Eq. 35 and R at this node and time
     TC Rx = TC(0);
     if (SB) phio = phi_scheme_b<TC>(cf, phio, rfield ? (TC)rfield[n] : TC(0), &Rx);
     const TC phi = cf->phi_ref + phio;
 
-    TC A[6];
-    if (kfon) ablock_field<D, NP>(cf, g0n, phi, A);
-    else ablock<D, KVAR, NP>(cf, phi, A);
+    TC Ah[6];   // A / 2
+    if (kfon) ablock_half_field<D, NP>(cf, g0n, phi, Ah);
+    else ablock_half<D, KVAR, NP>(cf, phi, Ah);
 
-    // mass the source adds this step: Scheme A 3/2 R(t) - 1/2 R(t-1); Scheme B
-    // R / 2 on top of phi - phi_ref (the stored sum is phi - R/2 before, phi + R/2 after)
-    TC Se = TC(0);
+    TC B[3], j[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        B[a] = (a < D) ? flux_b<NP>(cf, a, phi) : TC(0);
+        j[a] = TC(0);
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const int c = L::c(L::pair(i), a);
+            if (c == 1) j[a] += hd[i];
+            else if (c == -1) j[a] -= hd[i];
+        }
+    }
+
+    // Mass the source adds this step: Scheme A Se = 3/2 R(t) - 1/2 R(t-1);
+    // Scheme B R / 2 on top of phi - phi_ref (the stored sum is phi - R/2
+    // before, phi + R/2 after).  The source enters direction k as
+    // w_k (Se + 3 c_k . V), V = 3/2 R(t) Btilde(t) - 1/2 R(t-1) Btilde(t-1);
+    // Remark III adds (I - A/2) (B(phi) - B(phi(t - 1))) to V (Eq. 37).
+    TC Se = TC(0), V[3] = {TC(0), TC(0), TC(0)};
+    if (SRC) {
+        const SrcLevel<TC> lv = src_level<D, NP>(cf, phi, Ah);
+        const SrcLevel<TC> lp = src_prev<D, KVAR, NP>(cf, kfon, g0n, pp_off, prev);
+        if (cur) *cur = lv;
+        Se = TC(3) * lv.Rh - lp.Rh;
+#pragma unroll
+        for (int a = 0; a < D; ++a) V[a] = TC(3) * lv.S[a] - lp.S[a];
+    }
+    if (rem3) {
+        const TC pp = cf->phi_ref + pp_off;
+        TC dB[3] = {TC(0), TC(0), TC(0)};
+#pragma unroll
+        for (int a = 0; a < D; ++a) dB[a] = B[a] - flux_b<NP>(cf, a, pp);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            TC acc = dB[a];
+#pragma unroll
+            for (int b = 0; b < D; ++b) acc -= Ah[sym(a, b)] * dB[b];
+            V[a] += acc;
+        }
+    }
+
     if (EQR) {
         // All non-flux rates equal s.  With orthogonal rows and the flux rows
         // equal to c_a, (M^-1 S M)(g - feq) = s (g - feq) + c_k . v with
         // v = (A - s I)(j - B) / |c_a|^2 (the density row drops out in Scheme A
-        // since sum g = sum feq = phi).  Adding s feq_k and the Scheme-A source
-        // and splitting every term into its part even and odd under
-        // c_k -> -c_k gives
+        // since sum g = sum feq = phi).  Adding s feq_k and the source and
+        // splitting every term into its part even and odd under c_k -> -c_k
+        // gives
         //   out_k = (1 - s) g_k + w_k (s phio + Se + 9/2 s (E : c_k c_k - tr E / 3))
-        //           + c_k . (w_k (3 s B + Vo) - v),
-        // E = Cbar - phi/3 I, Se = 3/2 R(t) - 1/2 R(t-1) and
-        // Vo = 3 (3/2 R(t) Btilde(t) - 1/2 R(t-1) Btilde(t-1)).  Opposite
-        // directions share the even part and negate the odd one.
-        const TC s = cf->srate;
-        TC B[3], E[6];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) B[a] = (a < D) ? flux_b<NP>(cf, a, phi) : TC(0);
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            const bool used = (D == 3) || (i == 0 || i == 1 || i == 3);
-            E[i] = used ? poly<PolyLen<NP>::NC>(cf->cb[i], phi) : TC(0);
-        }
-        const TC third = phi * TC(1.0 / 3.0);
-        E[0] -= third; E[1] -= third;
-        if (D == 3) E[2] -= third;
-        const TC trE3 = (E[0] + E[1] + E[2]) * TC(1.0 / 3.0);
-        TC Vo[3] = {TC(0), TC(0), TC(0)};
-        TC jsh[3] = {TC(0), TC(0), TC(0)};   // Scheme B: R B' / 2, the part of j the shift removed
-        if (SRC) {
-            TC Bt[3], R, Btp[3], Rp;
-            source_terms<D, NP>(cf, phi, A, Bt, R);
-            src_levels<D, KVAR, NP>(cf, kfon, g0n, pp_off, R, Bt, cur, prev, Rp, Btp);
-            Se = TC(1.5) * R - TC(0.5) * Rp;
-#pragma unroll
-            for (int a = 0; a < D; ++a) Vo[a] = TC(4.5) * R * Bt[a] - TC(1.5) * Rp * Btp[a];
-        }
+        //           + c_k . (3 w_k T - v),
+        // E = Cbar - phi/3 I, T = s B + V.  The even polynomials carry their
+        // factor w_k 9/2 s from the host (cf->ce: one per axis, and per axis
+        // pair the sum and the xy term), so each even part is one Horner chain
+        // plus w_k base.  With w1 and w2 the axis and diagonal weights the odd
+        // part is 3 w1 c_k . d on the axes and 3 w1 c_k . q on the diagonals,
+        // d = T - v / (3 w1), q = d - (1 - w2 / w1) T: the factor 3 w1 goes
+        // into the last multiply-add of each population.
+        // Bound by vector issue on large grids: 105 instead of 131 operations
+        // of a D2Q9 node with K(phi) and the Scheme-A source before the factors
+        // moved to the host.
+        constexpr double w1 = L::w(1), w2 = L::w(Q - 1), kj = 1.0 / (L::jnorm * 1.5 * w1);
+        const TC s = cf->srate, sh = cf->shalf, oms = cf->oms;
+        TC T[3], d[3], q[3], ju[3];
+        TC Rs = Se;                      // even source part: Scheme A Se, Scheme B (1 - s/2) R
         if (SB) {
-            // (1 - s/2) R_k = w_k (1 - s/2) R + c_k . 3 w_k (1 - s/2) R B'
-            const TC hs = (TC(1) - TC(0.5) * s) * Rx;
+            // (1 - s/2) R_k = w_k (1 - s/2) R + c_k . 3 w_k (1 - s/2) R B'; j is
+            // the first moment of f = fbar + R_k / 2, i.e. plus R B' / 2
+            Rs = (TC(1) - sh) * Rx;
 #pragma unroll
             for (int a = 0; a < D; ++a) {
                 const TC bp = flux_bp<NP>(cf, a, phi);
-                Vo[a] = TC(3) * hs * bp;
-                jsh[a] = TC(0.5) * Rx * bp;
+                V[a] += Rs * bp;
+                j[a] += TC(0.5) * Rx * bp;
+            }
+            Se = TC(0.5) * Rx;
+        }
+#pragma unroll
+        for (int a = 0; a < D; ++a) ju[a] = (j[a] - B[a]) * TC(kj);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            T[a] = s * B[a] + V[a];
+            TC acc = T[a];
+#pragma unroll
+            for (int b = 0; b < D; ++b) acc -= (a == b ? Ah[a] - sh : Ah[sym(a, b)]) * ju[b];
+            d[a] = acc;
+            q[a] = acc - TC(1.0 - w2 / w1) * T[a];
+        }
+        const TC wb1 = TC(w1) * (s * phio + Rs);
+        const TC wb2 = TC(w2 / w1) * wb1;
+        constexpr int NC = PolyLen<NP>::NC, NPL = D * (D - 1) / 2;
+        TC ea[D], es[NPL], eo[NPL];
+        if constexpr (NC <= 6) {
+#pragma unroll
+            for (int a = 0; a < D; ++a) ea[a] = poly<NC>(cf->ce[a], phi);
+#pragma unroll
+            for (int i = 0; i < NPL; ++i) {
+                es[i] = poly<NC>(cf->ce[3 + i], phi);
+                eo[i] = poly<NC>(cf->ce[6 + i], phi);
+            }
+        } else {
+            // long polynomials: one Horner chain per tensor entry costs less
+            // than one per even part
+            TC E[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                const bool used = (D == 3) || (i == 0 || i == 1 || i == 3);
+                E[i] = used ? poly<NC>(cf->cb[i], phi) : TC(0);
+            }
+            const TC third = phi * TC(1.0 / 3.0);
+            E[0] -= third; E[1] -= third;
+            if (D == 3) E[2] -= third;
+            const TC tr3 = (E[0] + E[1] + E[2]) * TC(1.0 / 3.0);
+            const TC f1 = TC(9.0 * w1) * sh, f2 = TC(9.0 * w2) * sh;
+#pragma unroll
+            for (int a = 0; a < D; ++a) ea[a] = f1 * (E[a] - tr3);
+#pragma unroll
+            for (int i = 0; i < NPL; ++i) {
+                const int a = i == 1 ? 1 : 0, b = i == 0 ? 1 : 2;
+                es[i] = f2 * ((E[a] - tr3) + E[b]);
+                eo[i] = TC(2) * f2 * E[3 + i];
             }
         }
-        if (rem3) {
-            // Remark III: c_k . 3 w_k (I - A/2) (B(phi) - B(phi(t - 1)))
-            const TC pp = cf->phi_ref + pp_off;
-            TC dB[3] = {TC(0), TC(0), TC(0)};
 #pragma unroll
-            for (int a = 0; a < D; ++a) dB[a] = flux_b<NP>(cf, a, phi) - flux_b<NP>(cf, a, pp);
+        for (int a = 0; a < D; ++a) {
+            // the axis pair (c = e_a, -e_a)
+            const int k = L::axis(a), kb = L::opp(k);
+            const TC even = ea[a] + wb1;
+            out[k] = TC(3.0 * w1) * d[a] + (oms * h[k] + even);
+            out[kb] = TC(-3.0 * w1) * d[a] + (oms * h[kb] + even);
+        }
 #pragma unroll
-            for (int a = 0; a < D; ++a) {
-                TC acc = dB[a];
+        for (int i = 0; i < D * (D - 1) / 2; ++i) {
+            // the two diagonal pairs in the plane of axes a < b
+            const int a = i == 1 ? 1 : 0, b = i == 0 ? 1 : 2;
+            const TC e0 = es[i] + wb2;
+            const int kp = L::diag(i, 1), km = L::diag(i, -1);   // c = e_a + e_b, e_a - e_b
+            const TC op = q[a] + q[b], om = q[a] - q[b];
+            const TC ep = e0 + eo[i], em = e0 - eo[i];
+            out[kp] = TC(3.0 * w1) * op + (oms * h[kp] + ep);
+            out[L::opp(kp)] = TC(-3.0 * w1) * op + (oms * h[L::opp(kp)] + ep);
+            out[km] = TC(3.0 * w1) * om + (oms * h[km] + em);
+            out[L::opp(km)] = TC(-3.0 * w1) * om + (oms * h[L::opp(km)] + em);
+        }
+    } else if constexpr (Q == 9) {
+        // Unequal rates: S acts on the moments of Eq. 15.  The even moments
+        // (e, eps, pxx, pxy) come from the pair sums and the odd ones (j, q)
+        // from the differences; their equilibria are those of Eq. 3 in offset
+        // form, e: -2 phio + Et, eps: phio - Et, pxx: Exx - Eyy, pxy: Exy,
+        // j: B, q: -B, with Et = 3 (Exx + Eyy) (cf->cm).  r holds the relaxed
+        // moments over the row norms (cf->sn = s_i / N_i), and the way back
+        // uses the same pairs.  No 9 x 9 transform of g, feq and r: about 110
+        // operations instead of 230 for a node without a source.
+        const TC ax = hs[1] + hs[2], di = hs[3] + hs[4];   // axis and diagonal pairs
+        const TC Et = poly<PolyLen<NP>::NC>(cf->cm[0], phi), Ed = poly<PolyLen<NP>::NC>(cf->cm[1], phi),
+                 Ex = poly<PolyLen<NP>::NC>(cf->cm[2], phi);
+        const TC me = (TC(2) * di - TC(4) * h[0] - ax) - (Et - TC(2) * phio);
+        const TC mp = (TC(4) * h[0] - TC(2) * ax + di) - (phio - Et);
+        TC re = cf->sn[1] * me, rp = cf->sn[2] * mp;
+        const TC rxx = cf->sn[7] * (hs[1] - hs[2] - Ed);
+        const TC rxy = cf->sn[8] * (hs[3] - hs[4] - Ex);
+        // q_x = -2 (h1 - h3) + (diagonals of j_x), diagonals = j_x - (h1 - h3)
+        TC rj[2], rq[2];
+        TC jn[2];
 #pragma unroll
-                for (int b = 0; b < D; ++b) acc -= TC(0.5) * A[sym(a, b)] * dB[b];
-                Vo[a] += TC(3) * acc;
+        for (int a = 0; a < 2; ++a) {
+            jn[a] = j[a] - B[a];
+            rq[a] = cf->sn[4 + 2 * a] * (j[a] - TC(3) * hd[a] + B[a]);
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+            rj[a] = TC(1.0 / 3.0) * (Ah[a] * jn[a] + Ah[3] * jn[1 - a]);
+        TC r0 = TC(0);
+        if (SB) {
+            // r -= (I - S/2) M R_k, R_k = w_k R (1 + 3 c_k . B') (Eq. 9, Btilde =
+            // B'): its moments are rho: R, e: -2 R, eps: R, j: R B', q: -R B',
+            // and rho's own term leaves -R
+            re += Rx * (TC(2.0 / 36.0) - cf->sn[1]);
+            rp -= Rx * (TC(1.0 / 36.0) - TC(0.5) * cf->sn[2]);
+            r0 = TC(-1.0 / 9.0) * Rx;
+#pragma unroll
+            for (int a = 0; a < 2; ++a) jn[a] = Rx * flux_bp<NP>(cf, a, phi);
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                rj[a] -= TC(1.0 / 6.0) * (jn[a] - (Ah[a] * jn[a] + Ah[3] * jn[1 - a]));
+                rq[a] += (TC(1.0 / 12.0) - TC(0.5) * cf->sn[4 + 2 * a]) * jn[a];
             }
+            Se = TC(0.5) * Rx;
         }
-        // j - B, with j the first moment of the gathered populations (Scheme B:
-        // of f = fbar + R_k / 2, i.e. plus R B' / 2)
-        TC jd[3], v[3];
+        // even parts on the axes and the diagonals, with the source w_k Se
+        const TC srcA = SB ? -r0 : TC(1.0 / 9.0) * Se, srcD = SB ? -r0 : TC(1.0 / 36.0) * Se;
+        const TC ea = srcA + (re + TC(2) * rp), ed = srcD - (TC(2) * re + rp);
+        TC oa[2], od[2];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            TC acc = TC(0);
-#pragma unroll
-            for (int k = 0; k < Q; ++k) {
-                const int c = L::c(k, a);
-                if (c == 1) acc += h[k];
-                else if (c == -1) acc -= h[k];
-            }
-            jd[a] = (a < D) ? acc + jsh[a] - B[a] : TC(0);
+        for (int a = 0; a < 2; ++a) {
+            oa[a] = TC(1.0 / 3.0) * V[a] - (rj[a] - TC(2) * rq[a]);
+            od[a] = TC(1.0 / 12.0) * V[a] - (rj[a] + rq[a]);
         }
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            TC acc = TC(0);
-#pragma unroll
-            for (int b = 0; b < D; ++b) acc += (A[sym(a, b)] - (a == b ? s : TC(0))) * jd[b];
-            v[a] = acc * TC(1.0 / L::jnorm);
-        }
-        // even source part: Scheme A Se; Scheme B (1 - s/2) R.  Mass target
-        // below: Scheme A phio + Se; Scheme B phio + R/2 (sum of the gathered
-        // fbar is phio - R/2, the collision returns phio + R/2).
-        const TC base = s * phio + (SB ? (TC(1) - TC(0.5) * s) * Rx : Se);
-        if (SB) Se = TC(0.5) * Rx;
-        const TC s45 = TC(4.5) * s;
-        const TC oms = TC(1) - s;
-#pragma unroll
-        for (int k = 0; k < Q; ++k) {
-            const int kb = L::opp(k);
-            if (kb < k) continue;
-            const int x = L::cx(k), y = L::cy(k), z = L::cz(k);
-            TC ccE = -trE3;
-            if (x) ccE += E[0];
-            if (y) ccE += E[1];
-            if (z) ccE += E[2];
-            if (x && y) ccE += TC(2 * x * y) * E[3];
-            if (y && z) ccE += TC(2 * y * z) * E[4];
-            if (x && z) ccE += TC(2 * x * z) * E[5];
-            const TC w = TC(L::w(k));
-            const TC even = w * (base + s45 * ccE);
-            if (kb == k) {
-                out[k] = oms * h[k] + even;
-                continue;
-            }
-            TC odd = TC(0);
-            if (x) odd += TC(x) * (w * (TC(3) * s * B[0] + Vo[0]) - v[0]);
-            if (y) odd += TC(y) * (w * (TC(3) * s * B[1] + Vo[1]) - v[1]);
-            if (z) odd += TC(z) * (w * (TC(3) * s * B[2] + Vo[2]) - v[2]);
-            out[k] = oms * h[k] + even + odd;
-            out[kb] = oms * h[kb] + even - odd;
-        }
+        const TC e1 = ea - rxx, e2 = ea + rxx, e5 = ed - rxy, e6 = ed + rxy;
+        const TC o5 = od[0] + od[1], o6 = od[1] - od[0];
+        out[1] = h[1] + (e1 + oa[0]); out[3] = h[3] + (e1 - oa[0]);
+        out[2] = h[2] + (e2 + oa[1]); out[4] = h[4] + (e2 - oa[1]);
+        out[5] = h[5] + (e5 + o5);    out[7] = h[7] + (e5 - o5);
+        out[6] = h[6] + (e6 + o6);    out[8] = h[8] + (e6 - o6);
     } else {
         // m = M (g - feq); relax with S (diagonal rates, block A on the flux
         // rows, Eq. 17); back with M^-1 = M^T N^-1 (orthogonal rows).
@@ -624,7 +762,7 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
         for (int a = 0; a < D; ++a) {
             TC acc = TC(0);
 #pragma unroll
-            for (int b = 0; b < D; ++b) acc += A[sym(a, b)] * m[L::jrow[b]];
+            for (int b = 0; b < D; ++b) acc += TC(2) * Ah[sym(a, b)] * m[L::jrow[b]];
             r[L::jrow[a]] = acc;
         }
         if (SB) {
@@ -661,7 +799,7 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
             for (int a = 0; a < D; ++a) {
                 TC acc = TC(0);
 #pragma unroll
-                for (int b = 0; b < D; ++b) acc += A[sym(a, b)] * mR[L::jrow[b]];
+                for (int b = 0; b < D; ++b) acc += TC(2) * Ah[sym(a, b)] * mR[L::jrow[b]];
                 sR[L::jrow[a]] = acc;
             }
 #pragma unroll
@@ -682,49 +820,17 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
             }
             out[k] = h[k] - acc;
         }
-    }
-
-    if (SRC && !EQR) {
-        // Scheme A: + 3/2 R_k(t) - 1/2 R_k(t - 1), R_k = w_k (1 + 3 c.Btilde) R (Eq. 9)
-        TC Bt[3], R, Btp[3], Rp;
-        source_terms<D, NP>(cf, phi, A, Bt, R);
-        src_levels<D, KVAR, NP>(cf, kfon, g0n, pp_off, R, Bt, cur, prev, Rp, Btp);
-        const TC r1 = TC(1.5) * R, r0 = TC(0.5) * Rp;
-        Se = r1 - r0;
+        if (SRC || rem3) {
 #pragma unroll
-        for (int k = 0; k < Q; ++k) {
-            TC cb1 = TC(0), cb0 = TC(0);
+            for (int k = 0; k < Q; ++k) {
+                TC cv = TC(0);
 #pragma unroll
-            for (int a = 0; a < D; ++a) {
-                const int c = L::c(k, a);
-                if (c) { cb1 += TC(c) * Bt[a]; cb0 += TC(c) * Btp[a]; }
+                for (int a = 0; a < D; ++a) {
+                    const int c = L::c(k, a);
+                    if (c) cv += TC(c) * V[a];
+                }
+                out[k] += TC(L::w(k)) * ((SRC ? Se : TC(0)) + TC(3) * cv);
             }
-            out[k] += TC(L::w(k)) * (r1 * (TC(1) + TC(3) * cb1) - r0 * (TC(1) + TC(3) * cb0));
-        }
-    }
-
-    if (rem3 && !EQR) {
-        // Remark III: + G_k = 3 w_k c_k . (I - A/2) (B(phi) - B(phi(t - 1)))
-        const TC pp = cf->phi_ref + pp_off;
-        TC dB[3] = {TC(0), TC(0), TC(0)}, gq[3] = {TC(0), TC(0), TC(0)};
-#pragma unroll
-        for (int a = 0; a < D; ++a) dB[a] = flux_b<NP>(cf, a, phi) - flux_b<NP>(cf, a, pp);
-#pragma unroll
-        for (int a = 0; a < D; ++a) {
-            TC acc = dB[a];
-#pragma unroll
-            for (int b = 0; b < D; ++b) acc -= TC(0.5) * A[sym(a, b)] * dB[b];
-            gq[a] = TC(3) * acc;
-        }
-#pragma unroll
-        for (int k = 0; k < Q; ++k) {
-            TC cg = TC(0);
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                const int c = L::c(k, a);
-                if (c) cg += TC(c) * gq[a];
-            }
-            out[k] += TC(L::w(k)) * cg;
         }
     }
 
@@ -733,12 +839,7 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
     // the remainder.  The map is unchanged in exact arithmetic; in FP32 it
     // stops the drift that rounded weights (sum_k w_k = 1 + O(1e-8)) would
     // otherwise add to the mass at every step.
-    {
-        TC moving = TC(0);
-#pragma unroll
-        for (int k = 1; k < Q; ++k) moving += out[k];
-        out[0] = (phio + Se) - moving;
-    }
+    out[0] = (phio + Se) - tree_sum<Q - 1>(out + 1);
 
     return phio;
 }
@@ -908,7 +1009,7 @@ __device__ __forceinline__ void sweep2_tile(const Geom &g, const Coefs<TC> *__re
             const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB>(cf, h, ps[i], 0u, nullptr, nullptr, false, out,
                                                                         HAND ? &lev[HAND ? i : 0] : nullptr);
 #pragma unroll
-            for (int k = 0; k < 9; ++k) lf[k][r][lane] = (TS)out[k];
+            for (int k = 0; k < 9; ++k) lf[k][r][lane] = to_store<TS>(out[k]);
             if (!HAND) lp[HAND ? 0 : r][lane] = (TP)phio;
             bad |= !__builtin_isfinite(phio);
         }
@@ -939,7 +1040,7 @@ __device__ __forceinline__ void sweep2_tile(const Geom &g, const Coefs<TC> *__re
             const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB>(cf, h, pp_off, n, nullptr, nullptr, false, out,
                                                                         HAND ? &lev[HAND ? i : 0] : nullptr);
 #pragma unroll
-            for (int k = 0; k < 9; ++k) lf[k][r][lane] = (TS)out[k];
+            for (int k = 0; k < 9; ++k) lf[k][r][lane] = to_store<TS>(out[k]);
             if (!HAND) lp[HAND ? 0 : r][lane] = (TP)phio;
             bad |= !__builtin_isfinite(phio);
         }
@@ -987,9 +1088,14 @@ __device__ __forceinline__ void sweep2_tile(const Geom &g, const Coefs<TC> *__re
     if (bad) *flag = 1;
 }
 
+// FP32 and FP16 tiles of at most two rows per wave need fewer than 64 vector
+// registers and fit 8 waves per SIMD in LDS; the attribute keeps the compiler
+// from taking more scalar registers than that allows (104 would give 7, i.e.
+// 3 instead of 4 workgroups of 8 waves per CU).
 template <typename TS, typename TC, bool SRC, bool KVAR, int NP, int TH, int NW = kBlock / 64, bool SB = false,
           bool WALL = false, bool EQ = true>
 __global__ void __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(sizeof(TC) == 4 && NP == 3 && (TH + 2) / NW <= 2 ? 8 : 1, 8)))
 k_sweep2(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin, TS *__restrict__ fout,
          const typename HistType<TS>::T *__restrict__ pin, typename HistType<TS>::T *__restrict__ pout,
          uint32_t tiles_x, int *flag) {
@@ -1148,11 +1254,11 @@ k_sweep2_3d(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict
                     if (SRC && !HAND) lp[s1 & 1][(SRC && !HAND) ? r : 0][lane] = (TP)phio;
                     if (HAND) ph0[HAND ? j : 0] = (TP)phio;
 #pragma unroll
-                    for (int c = 0; c < 9; ++c) r0[s1][c][r][lane] = (TS)out[Zc3::z[c]];
+                    for (int c = 0; c < 9; ++c) r0[s1][c][r][lane] = to_store<TS>(out[Zc3::z[c]]);
 #pragma unroll
                     for (int c = 0; c < 5; ++c) {
-                        rm[s1][c][r][lane] = (TS)out[Zc3::m[c]];
-                        keep[j][c] = (TS)out[Zc3::p[c]];
+                        rm[s1][c][r][lane] = to_store<TS>(out[Zc3::m[c]]);
+                        keep[j][c] = to_store<TS>(out[Zc3::p[c]]);
                     }
                 }
             }

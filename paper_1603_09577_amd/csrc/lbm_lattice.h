@@ -34,6 +34,14 @@ struct Lattice<9> {
         constexpr int v[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
         return v[k];
     }
+    // one direction of each opposite pair: the axes, then the diagonals
+    __host__ __device__ static constexpr int pair(int i) {
+        constexpr int v[4] = {1, 2, 5, 6};
+        return v[i];
+    }
+    // c = e_a, and c = e_x + s e_y (one plane in 2-D)
+    __host__ __device__ static constexpr int axis(int a) { return 1 + a; }
+    __host__ __device__ static constexpr int diag(int, int s) { return s > 0 ? 5 : 8; }
     __host__ __device__ static constexpr int M(int i, int k) {
         constexpr int m[9][9] = {
             {1, 1, 1, 1, 1, 1, 1, 1, 1},
@@ -76,6 +84,14 @@ struct Lattice<19> {
         return k == 0 ? 1.0 / 3.0 : (k < 7 ? 1.0 / 18.0 : 1.0 / 36.0);
     }
     __host__ __device__ static constexpr int opp(int k) { return k == 0 ? 0 : ((k & 1) ? k + 1 : k - 1); }
+    // one direction of each opposite pair
+    __host__ __device__ static constexpr int pair(int i) { return 1 + 2 * i; }
+    // c = e_a, and c = e_a + s e_b in the planes xy, yz, xz (a < b)
+    __host__ __device__ static constexpr int axis(int a) { return 1 + 2 * a; }
+    __host__ __device__ static constexpr int diag(int i, int s) {
+        constexpr int v[3][2] = {{7, 9}, {15, 17}, {11, 14}};
+        return v[i][s > 0 ? 0 : 1];
+    }
     // basis row i at velocity k (polynomials of c)
     __host__ __device__ static constexpr int M(int i, int k) {
         const int x = cx(k), y = cy(k), z = cz(k);
