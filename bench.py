@@ -6,13 +6,13 @@ Headline workload: D2Q9 MRT, nonlinear anisotropic CDE with the Scheme-A
 source on a periodic 1024 x 1024 grid (B = 0.5 phi^2 (1, 1),
 K = K0 (1 + phi^2), R = 0.1 phi (1 - phi), phi0 = 0.5 + 0.1 U[-1, 1) seed 2),
 distributions stored as FP32 offsets.  One step = one time step of every
-node: one fused sweep, or half of a pass that runs two time steps (the
+node: one fused sweep, or one of the two to eight steps of a pass (the
 autotuner's choice where it is faster; the results are bit-identical).  The
 value is the median of 5 timed regions of --steps steps each.  The roofline
 object describes the kernel launched: algorithmic bytes per node update (one
 read and one write of every population and of the phi history) times the
-updates one launch performs, over the launch time; a two-step pass performs
-two updates per node while moving the state once, so its fraction can exceed
+updates one launch performs, over the launch time; a pass of several steps
+performs as many updates per node while moving the state once, so its fraction can exceed
 1 (its fraction on its own bytes is reported beside it), and single sweeps
 are reported beside it too.  The same run in FP64 storage, the
 reversed (adjoint) sweep on the
@@ -133,7 +133,7 @@ TWO_STEP_3D = None
 
 def run_forward(torch, lbm, spec, phi0, steps, warmup, label, tune=True, two_step=None):
     """Time `steps` sweeps.  With tune, the launch shape is the autotuner's
-    (which may pick two time steps per pass); two_step forces that choice,
+    (which may pick several time steps per pass); two_step forces that choice,
     TWO_STEP_SHAPE the tile shape of a two-step run."""
     sim = lbm.Lbm(spec).init(phi0)
     rep = sim.tune(reps=20).splitlines()[-1] if tune else "untuned"
@@ -159,6 +159,10 @@ def run_forward(torch, lbm, spec, phi0, steps, warmup, label, tune=True, two_ste
     two = (" two 1" in rep) if two_step is None else bool(two_step)
     m = re.search(r" rows (\d+) waves (\d+)", rep)
     rows = f"{m.group(1)} rows x {m.group(2)} waves" if (two and m) else None
+    # time steps of one launch: the tuner's pass, or a forced two-step pass
+    m = re.search(r" steps (\d+) ", rep)
+    forced = two_step is not None or "forced" in rep
+    spl = (2 if forced or not m else int(m.group(1))) if two else 1
     per, tinfo = time_steps(torch, sim, steps, warmup)
     N = sim.N
     prec = spec.get("precision", "f64")
@@ -166,13 +170,13 @@ def run_forward(torch, lbm, spec, phi0, steps, warmup, label, tune=True, two_ste
     bpn = bytes_per_node(sim.q, prec, src)
     out = {
         "label": label, "nodes": N, "steps": steps, "ms_per_step": per * 1e3,
-        "mlups": N / per / 1e6, "bytes_per_node": bpn, "two_step": two, "tile_rows": rows,
-        "timing": tinfo, "tuner": rep,
+        "mlups": N / per / 1e6, "bytes_per_node": bpn, "two_step": two, "steps_per_launch": spl,
+        "tile_rows": rows, "timing": tinfo, "tuner": rep,
     }
     # algorithmic bytes of the launched kernel: a single sweep reads and writes
-    # the state once per step; a two-step pass once per two steps
+    # the state once per step; a pass once per its steps
     launch_bytes = bpn * N
-    launch_s = 2 * per if two else per
+    launch_s = spl * per
     out["achieved_gbs"] = launch_bytes / launch_s / 1e9
     out["hbm_frac"] = out["achieved_gbs"] / PEAK_HBM_GBS
     # per node update at the single-sweep bytes (the HBM roofline of one sweep per step)
@@ -817,7 +821,8 @@ def main():
         one, s1, _ = run_forward(torch, lbm, spec4, p4, 200, 64, "nonlinear2d-4096 f32 single", two_step=False)
         del s1
         extra["hbm_resident_4096_f32"] = {
-            "mlups": big["mlups"], "two_step": big["two_step"], "tile_rows": big["tile_rows"],
+            "mlups": big["mlups"], "two_step": big["two_step"], "steps_per_launch": big["steps_per_launch"],
+            "tile_rows": big["tile_rows"],
             "per_update_hbm_frac": big["per_update_hbm_frac"], "hbm_frac": big["hbm_frac"],
             "single_sweep_mlups": one["mlups"], "single_sweep_hbm_frac": one["hbm_frac"],
             "state_bytes": 2 * 9 * 4 * 4096 * 4096 + 4 * 4096 * 4096}
@@ -841,7 +846,13 @@ def main():
         extra["rel_l2_vs_oracle"] = {"steps": ncpu, **errs}
 
     per = head["ms_per_step"] / 1e3
-    if head["two_step"]:
+    spl = head["steps_per_launch"]
+    if spl > 2:
+        m = re.match(r"(\d+) rows x (\d+) waves", head["tile_rows"] or "")
+        prof = profile_entry(f"nonlinear2d-1024 f32 {spl}-step",
+                             f"k_sweep_multi<float, float, true, true, {spl}, {int(m.group(1)) + 2 * spl - 2}, "
+                             f"{m.group(2)}," if m else "?")
+    elif head["two_step"]:
         m = re.match(r"(\d+) rows x (\d+) waves", head["tile_rows"] or "")
         prof = profile_entry("nonlinear2d-1024 f32 two-step",
                              f"k_sweep2<float, float, true, true, 3, {m.group(1)}, {m.group(2)}," if m else "?")
@@ -870,24 +881,26 @@ def main():
         "roofline": {
             # algorithmic bytes per launch = bytes per node update (one read and
             # one write of every population plus the phi history) x the node
-            # updates one launch performs (2 N for a two-step pass), over the
+            # updates one launch performs (N per step of a pass), over the
             # launch time
             "bound": "hbm", "achieved": head["per_update_hbm_frac"] * PEAK_HBM_GBS, "peak": PEAK_HBM_GBS,
             "unit": "GB/s", "frac": head["per_update_hbm_frac"], "traffic": traffic,
             "frac_own_bytes": head["hbm_frac"],
-            "note": ("frac counts the bytes one sweep per step would move; a two-step pass moves the "
-                     "state through HBM once per two updates (frac_own_bytes: its own bytes over its time), "
+            "note": ("frac counts the bytes one sweep per step would move; a pass of several steps moves the "
+                     "state once per steps_per_launch updates (frac_own_bytes: its own bytes over its time), "
                      "and the 79 MB state also fits the 256 MB Infinity Cache, so frac can exceed 1. "
                      "HBM-resident evidence: hbm_resident_4096_f32 and d3q19_f32/f64"
                      if head["two_step"] else
                      "the 79 MB state fits the 256 MB Infinity Cache; HBM-resident evidence: "
                      "hbm_resident_4096_f32 and d3q19_f32/f64"),
-            "kernel": (f"k_sweep2<float, float, SRC, KVAR, 3-term polynomials, {head['tile_rows']}> "
+            "kernel": (f"k_sweep_multi<float, float, SRC, KVAR, {spl} steps, {head['tile_rows']}> "
+                       f"({spl} steps per pass)" if spl > 2 else
+                       f"k_sweep2<float, float, SRC, KVAR, 3-term polynomials, {head['tile_rows']}> "
                        "(two steps per pass)"
                        if head["two_step"] else "k_sweep<9, float, float, EQR, SRC, KVAR, !WALL, 3-term polynomials>"),
             "bytes_per_node": head["bytes_per_node"], "nodes_per_launch": head["nodes"],
-            "steps_per_launch": 2 if head["two_step"] else 1,
-            "launch_us": head["ms_per_step"] * (2 if head["two_step"] else 1) * 1e3,
+            "steps_per_launch": spl,
+            "launch_us": head["ms_per_step"] * spl * 1e3,
             # measured vector-instruction issue of the same kernel (rocprofv3
             # SQ_INSTS_VALU over its trace time) against 6.14e11 wave-instructions/s
             # (256 CUs x 2.4 GHz, one 64-lane instruction per CU per clock without packed FP32)

@@ -264,6 +264,22 @@ int lbm_set_two_step(lbm_ctx *ctx, int mode);
  * shape. */
 int lbm_two_step_shape(const lbm_ctx *ctx, int shape, int *rows, int *waves);
 
+/* Passes of several time steps for D2Q9 (polynomials of degree <= 2, 32-bit
+ * offsets; periodic or walls on y, equal or unequal rates, any source; with a
+ * Scheme-A source where p2 is bound): the scheme of lbm_set_two_step with 8, 6
+ * or 4 steps, a halo of as many nodes less one, and the same bits.  Passes run
+ * in pairs (their lengths may differ), so state and history end where single
+ * sweeps leave them; the last one to three steps of a call use single sweeps.
+ * On by default where it applies, in a shape picked for the grid, and
+ * launched directly (no graphs); lbm_tune times the shapes; lbm_set_two_step
+ * turns it off.  Not used with per-node fields or Remark III.
+ * mode: -1 on in the library's pick, 0 off, k >= 1 on in shape k - 1.
+ * lbm_multi_step_shape: steps per pass, tile rows and waves per workgroup of a
+ * shape (the tile is 66 - 2 steps nodes wide).
+ * Errors: LBM_E_UNSUPPORTED / LBM_E_INVALID / LBM_E_STATE as lbm_set_two_step. */
+int lbm_multi_step_shape(const lbm_ctx *ctx, int shape, int *steps, int *rows, int *waves);
+int lbm_set_multi_step(lbm_ctx *ctx, int mode);
+
 /* Divergence check every `every` steps inside lbm_step (0 = off): lbm_step
  * then waits on the host at every multiple of `every` (counted from lbm_init)
  * and returns LBM_E_DIVERGED once a sweep has met a non-finite phi.  Steps

@@ -64,6 +64,12 @@ struct lbm_ctx {
     // only when the run keeps a history), and whether the path is on
     void *p2 = nullptr;
     bool two_ok = false, two = false;
+    // passes of several steps (D2Q9): whether they apply and are on, the shape
+    // of the main pass (multi_shape_of), the library's pick and the workgroup
+    // order of the passes
+    bool multi_ok = false, multi = false;
+    int multi_shape = 0, multi_auto = 0;
+    int multi_remap = 1;
     // lbm_step replays captured graphs of kGraphSteps sweeps (lbm_tune may
     // find direct launches faster)
     bool use_graphs = true;
@@ -431,14 +437,21 @@ bool two_ready(const lbm_ctx *c) {
 
 bool two_active(const lbm_ctx *c) { return c->two && two_ready(c) && !general_path(c); }
 
+// Passes of several steps: where two-step passes are on and apply.
+bool multi_active(const lbm_ctx *c) { return c->multi && c->multi_ok && two_active(c); }
+
+// Time steps of a main pass (2: two-step passes).
+int pass_steps(const lbm_ctx *c) {
+    int steps = 2, rows = 0, waves = 0;
+    if (multi_active(c)) multi_shape_of(c->dm.prec, c->multi_shape, &steps, &rows, &waves);
+    return steps;
+}
+
 // Bytes of the second history buffer (0 when two-step passes never read one).
 size_t hist2_bytes(const lbm_ctx *c) {
     return (c->two_ok && keeps_history(c)) ? round256((size_t)c->g.N * hist_size(c->dm.prec)) : 0;
 }
 
-// Four steps as two passes of two steps each: f[start] -> f[start ^ 1] with the
-// history p -> p2, then back; state and history end where four single sweeps
-// would leave them.
 void query_cus(lbm_ctx *c) {
     if (c->ncu) return;
     int dev = 0, n = 0;
@@ -494,6 +507,42 @@ void pick_adj_shape(lbm_ctx *c) {
     c->adj_shape_auto = c->adj_shape;
 }
 
+// Shape of the D2Q9 passes of several steps.  A pass costs one launch (1.6 us
+// between dependent launches, plus the first loads and the last stores), one
+// collision per step on the chain of its waves, and the halo: T - 1 nodes on
+// each side of a 64 x TR region.
+//  - While the grid gives every CU at most one workgroup, nothing else runs on
+//    that CU and the halo is free: the pass of the most steps that still fits
+//    one round wins, with one row per wave (us per step, FP32 with source /
+//    FP64 without: 64^2 T = 8 0.99 / 1.11, 6 1.15 / 1.33, 4 1.47 / 1.86, two
+//    steps per pass 2.46 / 2.38; 256^2 T = 8, three rounds, 2.03 / 2.97, 6
+//    1.24 / 1.49, 4 1.52 / 1.85; 320^2 T = 6, two rounds, 1.72 / 2.49, 4 1.59 /
+//    1.92).
+//  - Then the tall region with six steps (512^2 FP32 2.18 against 2.43 for four
+//    steps in 16 rows, FP64 3.42 against 4.08), or with four where that fits
+//    one round of resident workgroups and six steps do not (1000 x 723 FP32
+//    with walls 5.14 against 5.65).
+//  - Beyond one round the halo work counts: FP32 and FP16 keep six steps in the
+//    tall region (2048^2 FP32 20.4 against 24.1 for four and 22.6 for four in
+//    16 rows), FP64, whose tall region leaves one workgroup per CU, takes four
+//    steps in 16 rows (1024^2 12.5 against 13.0).
+int pick_multi(lbm_ctx *c) {
+    query_cus(c);
+    const uint64_t ncu = c->ncu > 0 ? (uint64_t)c->ncu : 256;
+    auto tiles = [&](int shape) {
+        int t = 2, tr = 0, nw = 0;
+        multi_shape_of(c->dm.prec, shape, &t, &tr, &nw);
+        const uint64_t tw = 64 - 2 * (t - 1), th = (uint64_t)(tr - 2 * (t - 1));
+        return ((c->g.nx + tw - 1) / tw) * ((c->g.ny + th - 1) / th);
+    };
+    for (int shape = 0; shape < 3; ++shape)
+        if (tiles(shape) <= ncu) return shape;
+    const bool f64 = c->dm.prec == 0;
+    if (tiles(3) <= (f64 ? ncu : 2 * ncu)) return 3;
+    if (tiles(4) <= 2 * ncu) return 4;
+    return f64 ? 4 : 3;
+}
+
 // z planes per column of the D3Q19 pass.  Each workgroup lives for its chunk
 // of zc planes plus two, and one workgroup slot per CU (or a few) runs them
 // in rounds, so the pass takes about ceil(workgroups / slots) * (zc + 2)
@@ -526,8 +575,33 @@ uint32_t zchunk(const lbm_ctx *c) {
     return (uint32_t)((nz + tiles_z - 1) / tiles_z);
 }
 
-// Without a source the kernels touch no history, and p stands in for p2.
-hipError_t sweep_pair(lbm_ctx *c, int start, hipStream_t st) {
+// One D2Q9 pass of `steps` time steps (two-step passes have their own shapes).
+hipError_t launch_pass_q9(lbm_ctx *c, int steps, const void *fin, void *fout, const void *pin, void *pout,
+                          hipStream_t st) {
+    const Dims d = eff_dims(c);
+    if (steps == 2)
+        return launch_sweep2_q9(d, c->g, c->d_coefs, fin, fout, pin, pout, c->d_flag, c->two_shape, st);
+    int t = 0, tr = 0, nw = 0, main_tr = 0;
+    multi_shape_of(c->dm.prec, c->multi_shape, &t, &main_tr, &nw);
+    int shape = c->multi_shape;
+    if (t != steps) {
+        // a shorter pass of a remainder: the rows of the main pass where a
+        // shape of that length has them, else the last shape of the length
+        for (int i = 0; multi_shape_of(c->dm.prec, i, &t, &tr, &nw); ++i)
+            if (t == steps) {
+                shape = i;
+                if (tr == main_tr) break;
+            }
+    }
+    Geom g = c->g;
+    g.remap = c->multi_remap;
+    return launch_sweep_multi_q9(d, g, c->d_coefs, fin, fout, pin, pout, c->d_flag, shape, st);
+}
+
+// `a` + `b` steps as two passes: f[start] -> f[start ^ 1] with the history
+// p -> p2, then back.  Without a source the kernels touch no history, and p
+// stands in for p2.
+hipError_t pass_pair(lbm_ctx *c, int start, int a, int b, hipStream_t st) {
     void *p2 = keeps_history(c) ? c->p2 : c->p;
     if (c->dm.q == 19) {
         const uint32_t zc = zchunk(c);
@@ -539,12 +613,30 @@ hipError_t sweep_pair(lbm_ctx *c, int start, hipStream_t st) {
                                   c->two_shape, zc, st);
         return e;
     }
-    const Dims d = eff_dims(c);
-    hipError_t e = launch_sweep2_q9(d, c->g, c->d_coefs, c->f[start], c->f[start ^ 1], c->p, p2, c->d_flag,
-                                    c->two_shape, st);
-    if (e == hipSuccess)
-        e = launch_sweep2_q9(d, c->g, c->d_coefs, c->f[start ^ 1], c->f[start], p2, c->p, c->d_flag,
-                             c->two_shape, st);
+    hipError_t e = launch_pass_q9(c, a, c->f[start], c->f[start ^ 1], c->p, p2, st);
+    if (e == hipSuccess) e = launch_pass_q9(c, b, c->f[start ^ 1], c->f[start], p2, c->p, st);
+    return e;
+}
+
+// The passes of at most n steps from buffer `start`, in pairs, so that state
+// and history end where as many single sweeps would leave them: pairs of main
+// passes, then one pair of shorter ones.  *done: the steps taken (all but at
+// most three).
+hipError_t run_passes(lbm_ctx *c, int start, int n, hipStream_t st, int *done) {
+    *done = 0;
+    if (!two_active(c)) return hipSuccess;
+    const int m = pass_steps(c);
+    hipError_t e = hipSuccess;
+    while (e == hipSuccess && n - *done >= 4) {
+        int a = m, b = m;
+        if (n - *done < 2 * m) {
+            const int even = (n - *done) & ~1;
+            a = (even / 2 + 1) & ~1;
+            b = even - a;
+        }
+        e = pass_pair(c, start, a, b, st);
+        *done += a + b;
+    }
     return e;
 }
 
@@ -574,7 +666,8 @@ hipError_t make_graph(lbm_ctx *c, int start) {
     int cur = start;
     hipError_t le = hipSuccess;
     if (two_active(c)) {
-        for (int i = 0; i < kGraphSteps / 4 && le == hipSuccess; ++i) le = sweep_pair(c, start, c->cap);
+        int done = 0;
+        le = run_passes(c, start, kGraphSteps, c->cap, &done);
     } else {
         for (int i = 0; i < kGraphSteps && le == hipSuccess; ++i) {
             le = sweep(c, c->f[cur], c->f[cur ^ 1], c->p, c->cap);
@@ -621,7 +714,7 @@ int check_flag(lbm_ctx *c, hipStream_t st) {
 }
 
 // n sweeps from the current buffer: whole graphs of kGraphSteps sweeps, then
-// pairs of two-step passes where they apply, then single launches.  With the
+// pairs of passes where they apply, then single launches.  With the
 // divergence check (every k steps) the steps run in chunks that end on the
 // multiples of k, passes and single sweeps within a chunk, and the flag is
 // read at the end of each chunk that reaches a multiple.
@@ -631,12 +724,11 @@ int advance(lbm_ctx *c, int nsteps, hipStream_t st) {
             int chunk = c->check_every - (int)(c->t % c->check_every);
             if (chunk > nsteps) chunk = nsteps;
             nsteps -= chunk;
-            while (two_active(c) && chunk >= 4) {
-                hipError_t e = sweep_pair(c, c->cur, st);
-                if (e != hipSuccess) return hip_fail(e, "two-step sweep kernel");
-                c->t += 4;
-                chunk -= 4;
-            }
+            int done = 0;
+            hipError_t pe = run_passes(c, c->cur, chunk, st, &done);
+            if (pe != hipSuccess) return hip_fail(pe, "multi-step sweep kernel");
+            c->t += done;
+            chunk -= done;
             for (; chunk > 0; --chunk) {
                 hipError_t e = sweep(c, c->f[c->cur], c->f[c->cur ^ 1], c->p, st);
                 if (e != hipSuccess) return hip_fail(e, "sweep kernel");
@@ -650,7 +742,9 @@ int advance(lbm_ctx *c, int nsteps, hipStream_t st) {
         }
         return LBM_OK;
     }
-    const bool graphs = !(c->desc.flags & LBM_FLAG_NO_GRAPH) && c->use_graphs;
+    // a pass of four steps or more takes longer than the host needs to launch
+    // it, so graphs would only add their capture to the first call
+    const bool graphs = !(c->desc.flags & LBM_FLAG_NO_GRAPH) && c->use_graphs && !multi_active(c);
     while (graphs && nsteps >= kGraphSteps) {
         if (!c->gexec[c->cur]) {
             hipError_t e = make_graph(c, c->cur);
@@ -661,12 +755,11 @@ int advance(lbm_ctx *c, int nsteps, hipStream_t st) {
         c->t += kGraphSteps;
         nsteps -= kGraphSteps;
     }
-    while (two_active(c) && nsteps >= 4) {
-        hipError_t e = sweep_pair(c, c->cur, st);
-        if (e != hipSuccess) return hip_fail(e, "two-step sweep kernel");
-        c->t += 4;
-        nsteps -= 4;
-    }
+    int done = 0;
+    hipError_t pe = run_passes(c, c->cur, nsteps, st, &done);
+    if (pe != hipSuccess) return hip_fail(pe, "multi-step sweep kernel");
+    c->t += done;
+    nsteps -= done;
     for (int i = 0; i < nsteps; ++i) {
         hipError_t e = sweep(c, c->f[c->cur], c->f[c->cur ^ 1], c->p, st);
         if (e != hipSuccess) return hip_fail(e, "sweep kernel");
@@ -754,6 +847,9 @@ int lbm_create(const lbm_desc *desc, lbm_ctx **out) {
     c->two_ok = (dm.q == 9 && ((dm.eqr && !dm.wall) || dm.deg3) && c->dm.o32) ||
                 (dm.q == 19 && dm.deg3 && c->dm.o32);
     c->two = c->two_ok;   // on by default where it applies (bit-identical; lbm_tune re-decides)
+    c->multi_ok = c->multi = dm.q == 9 && dm.deg3 && c->dm.o32;
+    c->multi_remap = (desc->flags & LBM_FLAG_NO_XCD_REMAP) ? 0 : 1;
+    if (c->multi_ok) c->multi_shape = c->multi_auto = pick_multi(c);
     {
         // the two-sweep adjoint: periodic D2Q9 only; its partial slots cover
         // the 6-row tiling, the finer of the two
@@ -904,7 +1000,37 @@ int lbm_set_two_step(lbm_ctx *c, int mode) {
     drop_graphs(c);
     c->two = mode != 0;
     c->two_shape = shape;
+    c->multi = false;   // exactly what was asked for
     prepare_zchunk(c);
+    return LBM_OK;
+}
+
+int lbm_multi_step_shape(const lbm_ctx *c, int shape, int *steps, int *rows, int *waves) {
+    if (!c || !steps || !rows || !waves) return fail(LBM_E_INVALID, "null argument");
+    int t = 0, tr = 0, nw = 0;
+    if (!c->multi_ok || !multi_shape_of(c->dm.prec, shape, &t, &tr, &nw))
+        return fail(LBM_E_INVALID, "no such multi-step shape");
+    *steps = t;
+    *rows = tr - 2 * (t - 1);
+    *waves = nw;
+    return LBM_OK;
+}
+
+int lbm_set_multi_step(lbm_ctx *c, int mode) {
+    if (!c) return fail(LBM_E_INVALID, "null context");
+    if (!c->multi_ok)
+        return fail(LBM_E_UNSUPPORTED, "passes of several steps need D2Q9, polynomials of degree <= 2 and 32-bit offsets");
+    int t = 0, tr = 0, nw = 0;
+    if (mode < -1 || (mode > 0 && !multi_shape_of(c->dm.prec, mode - 1, &t, &tr, &nw)))
+        return fail(LBM_E_INVALID, "mode must be -1 (the pick), 0 (off) or 1 + a multi-step shape");
+    if (mode && c->bound && keeps_history(c) && !c->p2)
+        return fail(LBM_E_STATE, "passes with a source need the second history buffer (lbm_init p2)");
+    drop_graphs(c);
+    c->multi = mode != 0;
+    if (c->multi) {
+        c->two = true;   // the remainders of a run take two-step passes
+        c->multi_shape = mode < 0 ? c->multi_auto : mode - 1;
+    }
     return LBM_OK;
 }
 
@@ -1171,6 +1297,7 @@ int lbm_set_nontemporal(lbm_ctx *c, int on) {
 int lbm_set_remap(lbm_ctx *c, int on) {
     if (!c) return fail(LBM_E_INVALID, "null context");
     c->g.remap = on ? 1u : 0u;
+    c->multi_remap = on ? 1 : 0;
     drop_graphs(c);
     return LBM_OK;
 }
@@ -1225,6 +1352,7 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
         if (ms < best) { best = ms; best_chunk = ch; best_nt = c->dm.nt; best_remap = c->g.remap; }
     }
     // two steps per pass: time pairs of passes (four steps), per step
+    c->multi = false;
     bool best_two = false;
     int best_shape = 0;
     c->g.chunk = (uint32_t)best_chunk;
@@ -1253,9 +1381,9 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
                 c->two_shape = shape;
                 prepare_zchunk(c);
                 c->g.remap = (remaps == 2 && ri % remaps == 0) ? 1u : 0u;
-                hipError_t e = sweep_pair(c, c->cur, st);
+                hipError_t e = pass_pair(c, c->cur, 2, 2, st);
                 if (e == hipSuccess) e = hipEventRecord(e0, st);
-                for (int r = 0; r < pair_reps && e == hipSuccess; ++r) e = sweep_pair(c, c->cur, st);
+                for (int r = 0; r < pair_reps && e == hipSuccess; ++r) e = pass_pair(c, c->cur, 2, 2, st);
                 if (e == hipSuccess) e = hipEventRecord(e1, st);
                 if (e == hipSuccess) e = hipEventSynchronize(e1);
                 float ms = 0.f;
@@ -1297,6 +1425,59 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
     c->two_shape = best_shape;
     prepare_zchunk(c);
     drop_graphs(c);
+    // passes of several steps: every shape in both block orders, the library's
+    // pick first; as above, a later candidate must be 2% faster.  Shapes of
+    // small tiles are left out where they would run in many rounds.
+    bool best_multi = false;
+    int best_mshape = c->multi_auto, best_mremap = c->multi_remap;
+    if (c->multi_ok && two_ready(c) && !general_path(c)) {
+        c->two = c->multi = true;
+        int nms = 0, mt = 0, mtr = 0, mnw = 0;
+        while (multi_shape_of(c->dm.prec, nms, &mt, &mtr, &mnw)) ++nms;
+        float best_ms = 1e30f;
+        for (int ri = 0; ri < remaps * nms; ++ri) {
+            const int i = ri / remaps;
+            const int shape = i == 0 ? c->multi_auto : (i <= c->multi_auto ? i - 1 : i);
+            multi_shape_of(c->dm.prec, shape, &mt, &mtr, &mnw);
+            const uint64_t tiles = (uint64_t)((c->g.nx + 65 - 2 * mt) / (66 - 2 * mt)) *
+                                   ((c->g.ny + (uint32_t)(mtr - 2 * mt + 1)) / (uint32_t)(mtr - 2 * mt + 2));
+            if (shape < 3 && tiles > 4ull * (uint64_t)(c->ncu > 0 ? c->ncu : 256)) continue;
+            c->multi_shape = shape;
+            c->multi_remap = (remaps == 2 && ri % remaps == 0) ? 1 : 0;
+            const int pair_reps = std::max(2, reps * 2 / mt);
+            float t = -1.f;
+            for (int trial = 0; trial < 2; ++trial) {
+                hipError_t e = pass_pair(c, c->cur, mt, mt, st);
+                if (e == hipSuccess) e = hipEventRecord(e0, st);
+                for (int r = 0; r < pair_reps && e == hipSuccess; ++r) e = pass_pair(c, c->cur, mt, mt, st);
+                if (e == hipSuccess) e = hipEventRecord(e1, st);
+                if (e == hipSuccess) e = hipEventSynchronize(e1);
+                float ms = 0.f;
+                if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+                if (e != hipSuccess) {
+                    (void)hipEventDestroy(e0); (void)hipEventDestroy(e1);
+                    return hip_fail(e, "tuning multi-step sweep");
+                }
+                ms /= 2 * mt * pair_reps;
+                if (t < 0.f || ms < t) t = ms;
+            }
+            char line[112];
+            std::snprintf(line, sizeof(line), "%d steps per pass rows %d waves %d remap %d: %.4f ms per step\n", mt,
+                          mtr - 2 * mt + 2, mnw, c->multi_remap, t);
+            rep += line;
+            if (t < 0.98f * best_ms) {
+                best_ms = t;
+                best_mshape = shape;
+                best_mremap = c->multi_remap;
+            }
+        }
+        best_multi = best_ms < best;
+        if (best_multi) best = best_ms;
+        c->two = best_two || best_multi;
+    }
+    c->multi = best_multi;
+    c->multi_shape = best_mshape;
+    c->multi_remap = best_mremap;
     // runs of kGraphSteps sweeps: graph replays against direct launches of the
     // same kernels, alternately, three times each (direct launches measured
     // 0.5-3% faster from 128^2 to 1024^2 and level on 256^3, where a launch
@@ -1305,7 +1486,7 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
     // launches are kept unless graphs are at least 1% faster.
     float graph_ms = -1.f, direct_ms = -1.f;
     c->use_graphs = true;
-    if (!(c->desc.flags & LBM_FLAG_NO_GRAPH) && c->check_every == 0) {
+    if (!(c->desc.flags & LBM_FLAG_NO_GRAPH) && c->check_every == 0 && !multi_active(c)) {
         for (int trial = 0; trial < 6; ++trial) {
             c->use_graphs = (trial & 1) == 0;
             int rc = advance(c, kGraphSteps, st);   // warm-up (and the graph capture)
@@ -1331,11 +1512,15 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    int brows = 0, bwaves = 0;
-    if (best_two) shape_of(c, best_shape, &brows, &bwaves);
-    char line[176];
-    std::snprintf(line, sizeof(line), "chosen chunk %d nt %d remap %u two %d rows %d waves %d graphs %d (%.4f ms)",
-                  best_chunk, (int)best_nt, best_remap, (int)best_two, brows, bwaves, (int)c->use_graphs, best);
+    // "two": several steps per pass, `steps` of them
+    int brows = 0, bwaves = 0, bsteps = best_two ? 2 : 1;
+    if (best_multi) lbm_multi_step_shape(c, best_mshape, &bsteps, &brows, &bwaves);
+    else if (best_two) shape_of(c, best_shape, &brows, &bwaves);
+    char line[192];
+    std::snprintf(line, sizeof(line),
+                  "chosen chunk %d nt %d remap %u two %d rows %d waves %d steps %d graphs %d (%.4f ms)", best_chunk,
+                  (int)best_nt, best_multi ? (unsigned)best_mremap : best_remap, (int)(best_two || best_multi), brows,
+                  bwaves, bsteps, best_multi ? 0 : (int)c->use_graphs, best);
     rep += line;
     if (report && report_len) std::snprintf(report, report_len, "%s", rep.c_str());
     // the history buffer was overwritten by the trial sweeps: restart from phi0

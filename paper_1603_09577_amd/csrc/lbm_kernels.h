@@ -909,11 +909,11 @@ k_sweep(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ f
 // `pout` (two history buffers, alternating).  NW waves per workgroup share
 // the TH + 2 rows of phase 1 (more waves: fewer rows and registers per wave).
 // ---------------------------------------------------------------------------
-// Periodic image of a tile coordinate v >= -1 on an axis of n >= 1 nodes
-// (v exceeds n by at most the tile span, so the loop runs a bounded number of
+// Periodic image of a tile coordinate v on an axis of n >= 1 nodes (v lies at
+// most the tile span outside the axis, so the loops run a bounded number of
 // times; once at most when n is at least the tile span).
 __device__ __forceinline__ int wrap_coord(int v, int n) {
-    if (v < 0) v += n;
+    while (v < 0) v += n;
     while (v >= n) v -= n;
     return v;
 }

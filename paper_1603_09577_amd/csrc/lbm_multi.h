@@ -1,0 +1,162 @@
+// T time steps per pass for D2Q9 (T even; 3-term polynomials): the state
+// crosses memory once per T steps and a pass costs one launch.
+//
+// A workgroup owns a tile of (64 - 2H) x (TR - 2H) nodes, H = T - 1, and keeps
+// a region of 64 x TR nodes, the tile and H nodes around it, in LDS.  Step 0
+// gathers the region from the stored state; step s runs on the rows and
+// columns at least s inside the region, so that after T steps the tile is
+// complete, and the last step stores it.  Every node update is the
+// single-sweep arithmetic on the same inputs, with populations rounded to the
+// storage type in LDS as a store would round them, so the result equals T
+// single sweeps bit for bit.
+//
+// One LDS copy serves all steps.  Slot k of a cell holds, before an odd step,
+// the population the cell gathers from direction k; an odd step reads its own
+// cell's nine slots and leaves population k in its own slot opp(k); an even
+// step s > 0 gathers population k from slot opp(k) of the cell at -c_k and
+// leaves its own population k in slot k of the cell at +c_k, which is where it
+// read population opp(k).  Every step thus writes exactly the slots the same
+// node has read, so no second copy is needed and one barrier separates steps.
+// At a wall the node's own slot takes the place of the one beyond it: the
+// reader negates it and adds the wall term (the anti-bounce-back gather).
+// Lanes and rows that are no longer inside hold values nobody uses: a write
+// of a boundary lane that leaves its row of LDS reaches only column 0 or 63 of
+// another slot, which no step reads any more at that point.
+//
+// What it buys: a two-step pass on 1024^2 FP32 (16.0 us) is as long as moving
+// its 84 MB through the Infinity Cache takes with the ramp of a launch, and on
+// a small grid most of a pass is launch, first loads and last stores.  With
+// six steps the bytes per step fall to a third and what is left is vector
+// issue (about 110 operations per node and step, 1.45 times that with the
+// halo) and the barriers.  us per step before -> after, FP32 with K(phi) and a
+// source unless noted: 64^2 FP64 unequal rates 2.41 -> 1.11; 256^2 3.5 -> 1.24;
+// 1024^2 8.0 -> 5.9, FP64 14.3 -> 12.5; 1000 x 723 channel with unequal rates
+// 7.9 -> 5.1; 2048^2 44 -> 20.4, FP64 80 -> 51; 4000 x 2500 FP16 54 -> 44.5.
+//
+// A Scheme-A run reads phi(t - 1) of the region from pin, hands each node's
+// source terms to the next step in the registers of the wave that owns its
+// row, and writes phi(t + T - 1) of the tile to pout (not pin: neighbouring
+// tiles still read it at their halo).
+#pragma once
+
+#include "lbm_kernels.h"
+
+namespace lbm {
+
+template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, bool EQ>
+__device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> *__restrict__ cf,
+                                                 const TS *__restrict__ fin, TS *__restrict__ fout,
+                                                 const typename HistType<TS>::T *__restrict__ pin,
+                                                 typename HistType<TS>::T *__restrict__ pout, uint32_t tx,
+                                                 uint32_t ty, int *flag) {
+    using L = Lattice<9>;
+    using TP = typename HistType<TS>::T;
+    static_assert(T % 2 == 0 && TR % NW == 0 && std::is_same<TP, TC>::value, "even passes, whole rows per wave");
+    constexpr int H = T - 1, TX = 64, TH = TR - 2 * H, NR = TR / NW;
+    __shared__ TS raw[TR * 9 * TX + 2];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    TS *const cell = raw + 1 + lane;                       // slot k of region row r: cell[(r * 9 + k) * TX]
+    const int nx = (int)g.nx, ny = (int)g.ny;
+    const int x0 = (int)(tx * (TX - 2 * H)), y0 = (int)(ty * TH);
+    const int xg = wrap_coord(x0 - H + lane, nx);
+    uint32_t cb[3] = {(uint32_t)(xg == 0 ? nx - 1 : xg - 1) * (uint32_t)sizeof(TS),    // c_x = 1
+                      (uint32_t)xg * (uint32_t)sizeof(TS),                              // c_x = 0
+                      (uint32_t)(xg == nx - 1 ? 0 : xg + 1) * (uint32_t)sizeof(TS)};   // c_x = -1
+    const uint32_t row_bytes = g.nx * (uint32_t)sizeof(TS);
+    const bool own = lane >= H && lane < TX - H && x0 - H + lane < nx;
+    SrcLevel<TC> lev[SRC ? NR : 1];
+    bool bad = false;
+    // step 0: scalar row base plus one of three column offsets per load
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int r = wv + i * NW, yl = y0 - H + r;
+        if (WALL && (yl < 0 || yl >= ny)) continue;        // beyond a wall
+        const int yg = WALL ? yl : wrap_coord(yl, ny);
+        const int ym = yg == 0 ? ny - 1 : yg - 1, yp = yg == ny - 1 ? 0 : yg + 1;
+        TC h[9], out[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            const int cy = L::cy(k);
+            const bool wl = WALL && ((cy == 1 && yg == 0) || (cy == -1 && yg == ny - 1));
+            const uint32_t row = (uint32_t)(wl ? yg : (cy == 1 ? ym : (cy == -1 ? yp : yg)));
+            const TS *pl = fin + (uint64_t)(wl ? L::opp(k) : k) * g.plane;
+            const TC v = (TC)*row_elem(pl, row * row_bytes, cb[wl ? 1 : 1 - L::cx(k)]);
+            h[k] = wl ? -v + cf->ew[cy == 1 ? 0 : 1][k] : v;
+        }
+        const TC pp = SRC ? (TC)*at<true>(pin, (uint32_t)yg * g.nx + (uint32_t)xg) : TC(0);
+        collide_node<9, TC, EQ, SRC, KVAR, 3, SB>(cf, h, pp, 0u, nullptr, nullptr, false, out,
+                                                  SRC ? &lev[SRC ? i : 0] : nullptr);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            const int cy = L::cy(k), cx = L::cx(k);
+            const bool wl = WALL && ((cy == -1 && yg == 0) || (cy == 1 && yg == ny - 1));
+            if (wl) cell[(r * 9 + L::opp(k)) * TX] = to_store<TS>(out[k]);
+            else if (r + cy >= 0 && r + cy < TR) cell[((r + cy) * 9 + k) * TX + cx] = to_store<TS>(out[k]);
+        }
+    }
+    // Steps 1 .. T - 2 in pairs (odd, even), then the last, odd one.  The pair
+    // loop stays rolled: unrolled, the source terms of T = 6 and 8 went to
+    // scratch memory.
+    auto step = [&](int s, auto odd, auto last) {
+        constexpr bool ODD = decltype(odd)::value, LAST = decltype(last)::value;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const int r = wv + i * NW, yl = y0 - H + r;
+            if (r < s || r >= TR - s || (WALL && (yl < 0 || yl >= ny))) continue;
+            TC h[9], out[9];
+#pragma unroll
+            for (int k = 0; k < 9; ++k) {
+                const int cy = L::cy(k), cx = L::cx(k);
+                const bool wl = WALL && ((cy == 1 && yl == 0) || (cy == -1 && yl == ny - 1));
+                const int idx = ODD || wl ? (r * 9 + k) * TX : ((r - cy) * 9 + L::opp(k)) * TX - cx;
+                const TC v = (TC)cell[idx];
+                h[k] = wl ? -v + cf->ew[cy == 1 ? 0 : 1][k] : v;
+            }
+            SrcLevel<TC> *lv = SRC ? &lev[SRC ? i : 0] : nullptr;
+            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, 3, SB>(cf, h, TC(0), 0u, nullptr, nullptr, false, out,
+                                                                      LAST ? nullptr : lv, lv);
+            if constexpr (!LAST) {
+#pragma unroll
+                for (int k = 0; k < 9; ++k) {
+                    const int cy = L::cy(k), cx = L::cx(k);
+                    const bool wl = WALL && ((cy == -1 && yl == 0) || (cy == 1 && yl == ny - 1));
+                    const int idx = ODD || wl ? (r * 9 + L::opp(k)) * TX : ((r + cy) * 9 + k) * TX + cx;
+                    cell[idx] = to_store<TS>(out[k]);
+                }
+            } else if (own && yl < ny) {
+                // a non-finite phi of an earlier step reaches the same node's
+                // later ones through its rest population
+                bad |= !__builtin_isfinite(phio);
+                const uint32_t m = (uint32_t)yl * g.nx + (uint32_t)(x0 - H + lane);
+                store_planes<9, false>(fout, g.plane, m, out);
+                if (SRC) *at<true>(pout, m) = (TP)phio;
+            }
+        }
+    };
+#pragma nounroll
+    for (int s = 1; s < T - 1; s += 2) {
+        __syncthreads();
+        step(s, std::true_type{}, std::false_type{});
+        __syncthreads();
+        step(s + 1, std::false_type{}, std::false_type{});
+    }
+    __syncthreads();
+    step(T - 1, std::true_type{}, std::true_type{});
+    if (bad) *flag = 1;
+}
+
+// FP32 arithmetic with at most two rows per wave fits 64 vector registers, so
+// that LDS decides the waves per CU; the attribute keeps the scalar registers
+// within 8 waves per SIMD too (one more would cost a whole workgroup).
+template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, bool EQ>
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 4 ? 8 : 1, 8)))
+k_sweep_multi(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin, TS *__restrict__ fout,
+              const typename HistType<TS>::T *__restrict__ pin, typename HistType<TS>::T *__restrict__ pout,
+              uint32_t tiles_x, int *flag) {
+    const uint32_t tile = block_index(blockIdx.x, gridDim.x, g.remap);
+    const uint32_t ty = tile / tiles_x, tx = tile - ty * tiles_x;
+    sweep_multi_tile<TS, TC, SRC, KVAR, T, TR, NW, SB, WALL, EQ>(g, cf, fin, fout, pin, pout, tx, ty, flag);
+}
+
+}  // namespace lbm

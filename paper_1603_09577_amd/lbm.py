@@ -33,7 +33,7 @@ EXPORTS = [
     "lbm_batch_step", "lbm_batch_get_phi", "lbm_batch_tune", "lbm_batch_set_shape",
     "lbm_batch_get_shape", "lbm_batch_destroy", "lbm_probe_copy", "lbm_set_chunk", "lbm_tune",
     "lbm_set_nontemporal", "lbm_recenter", "lbm_set_recenter", "lbm_set_fields", "lbm_set_phi_wall",
-    "lbm_set_two_step", "lbm_two_step_shape", "lbm_adjoint_step2", "lbm_adjoint_pair_ok", "lbm_set_remap",
+    "lbm_set_two_step", "lbm_two_step_shape", "lbm_set_multi_step", "lbm_multi_step_shape", "lbm_adjoint_step2", "lbm_adjoint_pair_ok", "lbm_set_remap",
     "lbm_adjoint_tile_shape", "lbm_set_adjoint_tile", "lbm_adjoint_tile",
     "lbm_reduce_async", "lbm_reduce_state", "lbm_reduce_noalloc",
 ]
@@ -131,6 +131,9 @@ def load():
         "lbm_set_phi_wall": ([_VP, ctypes.c_double, ctypes.c_double, _VP], ctypes.c_int),
         "lbm_set_two_step": ([_VP, ctypes.c_int], ctypes.c_int),
         "lbm_set_remap": ([_VP, ctypes.c_int], ctypes.c_int),
+        "lbm_set_multi_step": ([_VP, ctypes.c_int], ctypes.c_int),
+        "lbm_multi_step_shape": ([_VP, ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int),
+                                  ctypes.POINTER(ctypes.c_int)], ctypes.c_int),
         "lbm_two_step_shape": ([_VP, ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)],
                                ctypes.c_int),
         "lbm_adjoint_step2": ([_VP] * 10, ctypes.c_int),
@@ -323,6 +326,19 @@ class Lbm:
         while self.lib.lbm_two_step_shape(self.ctx, i, ctypes.byref(r), ctypes.byref(w)) == 0:
             out.append((r.value, w.value))
             i += 1
+        return out
+
+    def set_multi_step(self, on, shape=None):
+        """Several time steps per pass inside step() (where lbm_set_multi_step
+        applies), in shape `shape` or, with None, the library's pick."""
+        _check(self.lib.lbm_set_multi_step(self.ctx, 0 if not on else (-1 if shape is None else 1 + int(shape))))
+
+    def multi_step_shapes(self):
+        """[(steps per pass, tile rows, waves per workgroup)] of the passes of
+        several steps."""
+        out, v = [], [ctypes.c_int() for _ in range(3)]
+        while self.lib.lbm_multi_step_shape(self.ctx, len(out), *[ctypes.byref(x) for x in v]) == 0:
+            out.append(tuple(x.value for x in v))
         return out
 
     def set_check(self, every):

@@ -1,0 +1,106 @@
+"""D2Q9 passes of 4, 6 and 8 time steps against single sweeps, bit for bit.
+
+Every node update of a pass is the single-sweep arithmetic on the same inputs,
+rounded to the storage type where a sweep would store it, so the state, the
+phi history and phi must be equal, whatever the shape, the grid (ragged, lower
+and narrower than a tile, down to one node) and the number of steps (pairs of
+passes of different lengths, then single sweeps)."""
+import pytest
+
+from paper_1603_09577_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+UNEQUAL = [0.0, 1.3, 1.1, 1.0, 1.4, 1.0, 0.9, 1.2, 1.05]
+STEPS = (4, 5, 6, 10, 13, 14, 16, 31, 40)
+
+
+def _spec(nx, ny, prec, source="A", wall=False, rates="equal", linear=False):
+    spec = W.spec_nonlinear_2d(nx, ny, precision=prec, source=source != "none")
+    if linear:
+        spec = dict(W.spec_linear_gaussian(8, precision=prec), shape=(nx, ny))
+    if source == "B":
+        spec = dict(spec, scheme="B")
+    if wall:
+        spec = dict(spec, bc=["periodic", "abb", "periodic"], phi_wall=[[0.0, 0.0], [0.3, 0.7], [0.0, 0.0]])
+    if rates == "unequal":
+        spec = dict(spec, s=UNEQUAL)
+    return spec
+
+
+def _compare(spec, set_pass, steps=STEPS):
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    nx, ny = spec["shape"]
+    phi0 = W.noise_field((ny, nx), 11)
+    a = lbm.Lbm(spec).init(phi0)
+    a.set_two_step(False)
+    b = lbm.Lbm(spec).init(phi0)
+    set_pass(b)
+    for n in steps:
+        a.step(n)
+        b.step(n)
+        assert a.current() == b.current(), n
+        w, _ = a.current()
+        assert torch.equal(a.storage_view(a.f[w]), b.storage_view(b.f[w])), n
+        if spec["rpoly"] and spec["scheme"] == "A":
+            assert torch.equal(a.p[:4 * nx * ny], b.p[:4 * nx * ny]), n
+        assert torch.equal(a.phi(), b.phi()), n
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("shape", range(5))
+@pytest.mark.parametrize("nx,ny,source,wall,rates", [
+    (100, 37, "A", False, "equal"), (59, 31, "A", True, "unequal"), (131, 70, "none", False, "unequal"),
+    (54, 22, "B", True, "equal"), (3, 2, "A", False, "equal"), (1, 5, "B", False, "unequal"), (66, 1, "A", True, "equal"),
+    (50, 45, "none", True, "equal")])
+def test_every_shape_bit_identical(prec, shape, nx, ny, source, wall, rates):
+    _compare(_spec(nx, ny, prec, source, wall, rates), lambda s: s.set_multi_step(True, shape))
+
+
+@pytest.mark.parametrize("nx,ny,prec", [(64, 64, "f64"), (250, 250, "f32"), (300, 310, "f64"), (500, 500, "f32"),
+                                         (1000, 723, "f32"), (1100, 1200, "f16"), (1100, 1200, "f64")])
+def test_default_pass_bit_identical(nx, ny, prec):
+    """The shape each grid gets by default (one workgroup per CU, one round,
+    several rounds)."""
+    _compare(_spec(nx, ny, prec), lambda s: None, steps=(12, 25, 33))
+
+
+def test_linear_constant_tensor_and_calls():
+    """K, B linear (A from the host), and the refusals of the new calls."""
+    from paper_1603_09577_amd import lbm
+    _compare(_spec(70, 40, "f64", source="none", rates="unequal", linear=True), lambda s: s.set_multi_step(True))
+    s = lbm.Lbm(_spec(64, 64, "f32"))
+    assert [t[0] for t in s.multi_step_shapes()] == [8, 6, 4, 6, 4]
+    with pytest.raises(lbm.LbmError) as e:
+        s.set_multi_step(True, 5)
+    assert e.value.code == lbm.LBM_E_INVALID
+    spec3, _, _ = W.d3q19_walls((8, 8, 8))
+    with pytest.raises(lbm.LbmError) as e:
+        lbm.Lbm(spec3).set_multi_step(True)
+    assert e.value.code == lbm.LBM_E_UNSUPPORTED
+
+
+@pytest.mark.parametrize("every", [5, 8])
+def test_divergence_check_with_passes(every):
+    """Chunks that end on the multiples of the check interval, and a NaN that
+    is met in the middle of a pass."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    spec = _spec(90, 50, "f32")
+    phi0 = W.noise_field((50, 90), 3)
+    a = lbm.Lbm(spec).init(phi0)
+    a.set_two_step(False)
+    b = lbm.Lbm(spec).init(phi0)
+    b.set_check(every)
+    a.step(27)
+    b.step(27)
+    assert torch.equal(a.phi(), b.phi())
+    phi0[20, 30] = float("nan")
+    c = lbm.Lbm(spec).init(phi0)
+    c.set_check(16)
+    with pytest.raises(lbm.LbmError) as e:
+        c.step(16)
+    assert e.value.code == lbm.LBM_E_DIVERGED
