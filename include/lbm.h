@@ -517,13 +517,15 @@ int lbm_batch_tune(lbm_batch *b, int reps, int use_cache, void *stream, char *re
  * thread), (256, 2), (128, 1), (512, 1); grid 0 = one workgroup per tile,
  * otherwise persistent workgroups over contiguous chunks of the list.
  * Batches without a source whose polynomials all have degree <= 2 also offer
- * two time steps per launch (the two-step pass of lbm_set_two_step, one
- * workgroup per 62 x rows tile of an instance, bit-identical to single
- * sweeps): shape 4 = 14 rows x 8 waves and shape 5 = 6 rows x 4 waves for 4-
- * and 2-byte storage, shape 4 = 6 rows x 8 waves for FP64; the grid argument
- * is ignored for them, an odd remaining step runs shape 0, and get_shape
- * reports wg = 64 x waves and npt = -rows.  lbm_batch_tune times them with the
- * others.  LBM_E_INVALID for a shape the batch does not offer. */
+ * several time steps per launch (the passes of lbm_set_two_step and
+ * lbm_set_multi_step, one workgroup per tile of an instance, bit-identical to
+ * single sweeps), and start in one of them.  Steps per launch, tile rows x
+ * waves: for 4- and 2-byte storage shape 4 = 2 steps, 14 x 8, shape 5 = 2,
+ * 6 x 4, shape 6 = 6, 22 x 16, shape 7 = 4, 10 x 8; for FP64 shape 4 = 2,
+ * 6 x 8, shape 5 = 4, 10 x 8, shape 6 = 6, 22 x 16.  The grid argument is
+ * ignored for them, remaining steps take shorter passes and an odd one shape
+ * 0, and get_shape reports wg = 64 x waves and npt = -rows.  lbm_batch_tune
+ * times them with the others.  LBM_E_INVALID for a shape the batch does not offer. */
 int lbm_batch_set_shape(lbm_batch *b, int shape, unsigned grid, int remap);
 int lbm_batch_get_shape(const lbm_batch *b, int *shape, unsigned *grid, int *remap, int *wg, int *npt);
 

@@ -10,9 +10,9 @@
 // sweeps are replayed from captured HIP graphs.  An autotuner times the
 // candidate (WG, NPT, grid) shapes on the real batch and keeps the fastest;
 // results are cached in a small text file.  Batches without a source whose
-// polynomials have degree <= 2 may instead advance two time steps per launch:
-// a second work list holds one entry per (instance, 62 x TH tile), and each
-// workgroup runs the two-step tile of the single-instance pass on it.
+// polynomials have degree <= 2 may instead advance 2, 4 or 6 time steps per
+// launch: a further work list holds one entry per (instance, tile), and each
+// workgroup runs the tile of the single-instance pass on it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,6 +33,7 @@
 
 #include "../../include/lbm.h"
 #include "lbm_kernels.h"
+#include "lbm_multi.h"
 
 namespace lbm {
 
@@ -49,14 +50,26 @@ struct TileShape {
 constexpr TileShape kShapes[] = {{256, 1}, {256, 2}, {128, 1}, {512, 1}};
 constexpr int kNumShapes = 4;
 
-// two-step shapes (tile rows, waves per workgroup), batch shape indices
-// kNumShapes + i: 4- and 2-byte storage, and FP64
-struct TwoShape {
-    int rows, waves;
+// shapes of passes (time steps, tile rows, waves per workgroup), batch shape
+// indices kNumShapes + i: 4- and 2-byte storage, and FP64.  Longer passes of
+// the single-instance shapes (lbm_multi.h): batches of many instances run in
+// many rounds of workgroups, so only the shapes with the least halo work are
+// here; six steps cost the uneven instances more in ragged tiles (54 x 22
+// nodes) than four in 16 rows (58 x 10), which the tuner weighs.  us per step,
+// 128 instances of 32^2 to 512^2 (10.3 M nodes), two / four / six steps per
+// launch: FP32 80.2 / 54.5 / 46.9, FP64 152 / 113 / 113, FP16 58.3 / 50.1 /
+// 49.3; 8 instances (0.82 M nodes): FP32 6.2 / 5.2 / 4.3, FP64 11.1 / 10.0 /
+// 9.4.  Two steps move the state once per two updates at 0.86 of the copy
+// rate; six are bound by vector issue and the halo.
+struct PassShape {
+    int steps, rows, waves;
 };
-constexpr TwoShape kTwo4[] = {{14, 8}, {6, 4}};
-constexpr TwoShape kTwo8[] = {{6, 8}};
-constexpr int kMaxTwo = 2;
+constexpr PassShape kPass4[] = {{2, 14, 8}, {2, 6, 4}, {6, 22, 16}, {4, 10, 8}};
+constexpr PassShape kPass8[] = {{2, 6, 8}, {4, 10, 8}, {6, 22, 16}};
+constexpr int kMaxPass = 4, kNumPass4 = 4, kNumPass8 = 3;
+// the shape a batch with passes starts with (the fastest of them on 128
+// instances of 32^2 to 512^2, FP32 and FP64)
+constexpr int kDefault4 = 2, kDefault8 = 1;
 
 template <typename TS, typename TC, bool SRC, bool KVAR, int WG, int NPT, int NP>
 __global__ void __launch_bounds__(WG)
@@ -93,6 +106,20 @@ k_batch_sweep2(const BatchInst *__restrict__ inst, const Coefs<TC> *__restrict__
     const Geom g = I.g;
     sweep2_tile<TS, TC, false, KVAR, 3, TH, NW>(g, coefs + e.x, fin + I.f_off, fout + I.f_off, nullptr, nullptr,
                                                e.y & 0xffffu, e.y >> 16, flag);
+}
+
+// T time steps per launch, one workgroup per entry (instance, tx | ty << 16).
+template <typename TS, typename TC, bool KVAR, int T, int TR, int NW>
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 4 ? 8 : 1, 8)))
+k_batch_multi(const BatchInst *__restrict__ inst, const Coefs<TC> *__restrict__ coefs,
+              const uint2 *__restrict__ tiles, int remap, const TS *__restrict__ fin, TS *__restrict__ fout,
+              int *flag) {
+    const uint2 e = tiles[block_index(blockIdx.x, gridDim.x, remap)];
+    const BatchInst &I = inst[e.x];
+    const Geom g = I.g;
+    sweep_multi_tile<TS, TC, false, KVAR, T, TR, NW, false, false, true>(g, coefs + e.x, fin + I.f_off,
+                                                                        fout + I.f_off, nullptr, nullptr,
+                                                                        e.y & 0xffffu, e.y >> 16, flag);
 }
 
 template <typename TS, typename TC, int NP>
@@ -176,12 +203,12 @@ struct lbm_batch {
     // one tile list per shape (tile size differs)
     uint2 *d_tiles[kNumShapes] = {nullptr, nullptr, nullptr, nullptr};
     uint32_t ntiles[kNumShapes] = {0, 0, 0, 0};
-    // two-step work lists, one per two-step shape (tile rows differ)
-    uint2 *d_tiles2[kMaxTwo] = {nullptr, nullptr};
-    uint32_t ntiles2[kMaxTwo] = {0, 0};
-    int ntwo = 0;           // two-step shapes available (0: no source-free 3-term batch)
+    // work lists of the passes, one per pass shape (tiles differ)
+    uint2 *d_tiles2[kMaxPass] = {nullptr, nullptr, nullptr, nullptr};
+    uint32_t ntiles2[kMaxPass] = {0, 0, 0, 0};
+    int npass = 0;          // pass shapes available (0: no source-free 3-term batch)
     int *d_flag = nullptr;
-    int shape = 0;          // index into kShapes, or kNumShapes + a two-step shape
+    int shape = 0;          // index into kShapes, or kNumShapes + a pass shape
     uint32_t grid = 0;      // workgroups per sweep (0 = one per tile)
     int remap = 1;
     void *f[2] = {nullptr, nullptr};
@@ -203,9 +230,9 @@ size_t ssize(int prec) { return prec == 0 ? 8 : (prec == 1 ? 4 : 2); }
 size_t hsize(int prec) { return prec == 0 ? 8 : 4; }
 size_t r256(size_t v) { return (v + 255) & ~size_t(255); }
 
-TwoShape two_shape(const lbm_batch *b, int i) { return b->prec == 0 ? kTwo8[i] : kTwo4[i]; }
+PassShape pass_shape(const lbm_batch *b, int i) { return b->prec == 0 ? kPass8[i] : kPass4[i]; }
 
-bool is_two(const lbm_batch *b) { return b->shape >= kNumShapes; }
+bool is_pass(const lbm_batch *b) { return b->shape >= kNumShapes; }
 
 // one sweep; single-sweep shape `shape` (a two-step batch uses shape 0 for
 // an odd remaining step)
@@ -245,52 +272,64 @@ hipError_t batch_sweep_launch(lbm_batch *b, const void *fin, void *fout, hipStre
     return hipGetLastError();
 }
 
-// two time steps, two-step shape b->shape - kNumShapes
-hipError_t batch_sweep2_launch(lbm_batch *b, const void *fin, void *fout, hipStream_t st) {
-    const int i = b->shape - kNumShapes;
-    const TwoShape sh = two_shape(b, i);
+// one pass in pass shape i
+hipError_t batch_pass_launch(lbm_batch *b, const void *fin, void *fout, hipStream_t st, int i) {
+    const PassShape sh = pass_shape(b, i);
     const dim3 grid(b->ntiles2[i]);
     const uint2 *tl = b->d_tiles2[i];
 #define LBM_B2(TS, TC, K, TH, NW)                                                                       \
     hipLaunchKernelGGL((k_batch_sweep2<TS, TC, K, TH, NW>), grid, dim3(64 * NW), 0, st, b->d_inst,      \
                        (const Coefs<TC> *)b->d_coefs, tl, b->remap, (const TS *)fin, (TS *)fout, b->d_flag)
-#define LBM_B2_SHAPE(TS, TC, K)                                                                         \
-    if (sh.rows == 14) LBM_B2(TS, TC, K, 14, 8);                                                        \
+#define LBM_BM(TS, TC, K, T, TR, NW)                                                                    \
+    hipLaunchKernelGGL((k_batch_multi<TS, TC, K, T, TR, NW>), grid, dim3(64 * NW), 0, st, b->d_inst,    \
+                       (const Coefs<TC> *)b->d_coefs, tl, b->remap, (const TS *)fin, (TS *)fout, b->d_flag)
+#define LBM_B4(TS, TC, K)                                                                               \
+    if (sh.steps == 6) LBM_BM(TS, TC, K, 6, 32, 16);                                                    \
+    else if (sh.steps == 4) LBM_BM(TS, TC, K, 4, 16, 8);                                                \
+    else if (sh.rows == 14) LBM_B2(TS, TC, K, 14, 8);                                                   \
     else LBM_B2(TS, TC, K, 6, 4);
+#define LBM_B8(K)                                                                                       \
+    if (sh.steps == 6) LBM_BM(double, double, K, 6, 32, 16);                                            \
+    else if (sh.steps == 4) LBM_BM(double, double, K, 4, 16, 8);                                        \
+    else LBM_B2(double, double, K, 6, 8);
     if (b->prec == 0) {
-        if (b->kvar) LBM_B2(double, double, true, 6, 8);
-        else LBM_B2(double, double, false, 6, 8);
+        if (b->kvar) { LBM_B8(true) } else { LBM_B8(false) }
     } else if (b->prec == 1) {
-        if (b->kvar) { LBM_B2_SHAPE(float, float, true) }
-        else { LBM_B2_SHAPE(float, float, false) }
+        if (b->kvar) { LBM_B4(float, float, true) } else { LBM_B4(float, float, false) }
     } else {
-        if (b->kvar) { LBM_B2_SHAPE(_Float16, float, true) }
-        else { LBM_B2_SHAPE(_Float16, float, false) }
+        if (b->kvar) { LBM_B4(_Float16, float, true) } else { LBM_B4(_Float16, float, false) }
     }
-#undef LBM_B2_SHAPE
+#undef LBM_B8
+#undef LBM_B4
+#undef LBM_BM
 #undef LBM_B2
     return hipGetLastError();
 }
 
-// `steps` time steps from f[start]: pairs in two-step launches (the odd step,
-// if any, a single sweep); the state ends in f[start ^ (launches & 1)]
+// `steps` time steps from f[start]: passes of the chosen shape, then shorter
+// ones, an odd step a single sweep; the state ends in *end
 hipError_t batch_advance(lbm_batch *b, int start, int steps, hipStream_t st, int *end) {
     hipError_t e = hipSuccess;
     int cur = start;
-    if (is_two(b)) {
-        for (int i = 0; i + 1 < steps && e == hipSuccess; i += 2) {
-            e = batch_sweep2_launch(b, b->f[cur], b->f[cur ^ 1], st);
+    if (is_pass(b)) {
+        const int main = b->shape - kNumShapes;
+        while (steps >= 2 && e == hipSuccess) {
+            int i = main;
+            if (pass_shape(b, i).steps > steps) {
+                // the longest pass that fits (the first of its length)
+                i = 0;
+                for (int j = 0; j < b->npass; ++j)
+                    if (pass_shape(b, j).steps <= steps && pass_shape(b, j).steps > pass_shape(b, i).steps) i = j;
+            }
+            e = batch_pass_launch(b, b->f[cur], b->f[cur ^ 1], st, i);
+            steps -= pass_shape(b, i).steps;
             cur ^= 1;
         }
-        if ((steps & 1) && e == hipSuccess) {
-            e = batch_sweep_launch(b, b->f[cur], b->f[cur ^ 1], st, 0);
-            cur ^= 1;
-        }
-    } else {
-        for (int i = 0; i < steps && e == hipSuccess; ++i) {
-            e = batch_sweep_launch(b, b->f[cur], b->f[cur ^ 1], st, b->shape);
-            cur ^= 1;
-        }
+    }
+    const int shape = is_pass(b) ? 0 : b->shape;
+    for (int i = 0; i < steps && e == hipSuccess; ++i) {
+        e = batch_sweep_launch(b, b->f[cur], b->f[cur ^ 1], st, shape);
+        cur ^= 1;
     }
     *end = cur;
     return e;
@@ -361,7 +400,7 @@ bool cache_lookup(const std::string &key, int &shape, uint32_t &grid, int &remap
     int s, r;
     unsigned g;
     while (in >> k >> s >> g >> r)
-        if (k == key && s >= 0 && s < kNumShapes + kMaxTwo) { shape = s; grid = g; remap = r; return true; }
+        if (k == key && s >= 0 && s < kNumShapes + kMaxPass) { shape = s; grid = g; remap = r; return true; }
     return false;
 }
 
@@ -477,19 +516,19 @@ int lbm_batch_create(const lbm_desc *descs, int count, lbm_batch **out) {
         e = hipMalloc((void **)&b->d_tiles[s], sizeof(uint2) * tl.size());
         if (e == hipSuccess) e = hipMemcpy(b->d_tiles[s], tl.data(), sizeof(uint2) * tl.size(), hipMemcpyHostToDevice);
     }
-    // two-step work lists: source-free batches with 3-term polynomials, every
-    // instance below 65536 tiles per axis (16-bit tile coordinates) and with
-    // planes below 4 GiB (32-bit byte offsets)
+    // work lists of the passes: source-free batches with 3-term polynomials,
+    // every instance below 65536 tiles per axis (16-bit tile coordinates) and
+    // with planes below 4 GiB (32-bit byte offsets)
     bool fits = true;
     for (int i = 0; i < count; ++i)
-        fits = fits && (b->inst[i].g.nx + 61) / 62 < 65536u && b->inst[i].g.ny < 65536u * 6u &&
+        fits = fits && (b->inst[i].g.nx + 53) / 54 < 65536u && b->inst[i].g.ny < 65536u * 6u &&
                (uint64_t)b->inst[i].g.plane * 8u < (1ull << 32);
-    b->ntwo = (!b->src && b->deg3 && fits) ? (b->prec == 0 ? 1 : 2) : 0;
-    for (int s = 0; s < b->ntwo && e == hipSuccess; ++s) {
-        const uint32_t th = (uint32_t)two_shape(b, s).rows;
+    b->npass = (!b->src && b->deg3 && fits) ? (b->prec == 0 ? kNumPass8 : kNumPass4) : 0;
+    for (int s = 0; s < b->npass && e == hipSuccess; ++s) {
+        const uint32_t th = (uint32_t)pass_shape(b, s).rows, tw = 66u - 2u * (uint32_t)pass_shape(b, s).steps;
         std::vector<uint2> tl;
         for (int i = 0; i < count; ++i) {
-            const uint32_t tx = (b->inst[i].g.nx + 61) / 62, ty = (b->inst[i].g.ny + th - 1) / th;
+            const uint32_t tx = (b->inst[i].g.nx + tw - 1) / tw, ty = (b->inst[i].g.ny + th - 1) / th;
             for (uint32_t y = 0; y < ty; ++y)
                 for (uint32_t x = 0; x < tx; ++x) tl.push_back(make_uint2((unsigned)i, x | (y << 16)));
         }
@@ -497,6 +536,7 @@ int lbm_batch_create(const lbm_desc *descs, int count, lbm_batch **out) {
         e = hipMalloc((void **)&b->d_tiles2[s], sizeof(uint2) * tl.size());
         if (e == hipSuccess) e = hipMemcpy(b->d_tiles2[s], tl.data(), sizeof(uint2) * tl.size(), hipMemcpyHostToDevice);
     }
+    if (b->npass) b->shape = kNumShapes + (b->prec == 0 ? kDefault8 : kDefault4);
     if (e != hipSuccess) {
         lbm_batch_destroy(b);
         std::string m = std::string("batch setup: ") + hipGetErrorString(e);
@@ -515,7 +555,7 @@ void lbm_batch_destroy(lbm_batch *b) {
     if (b->d_flag) (void)hipFree(b->d_flag);
     for (int s = 0; s < kNumShapes; ++s)
         if (b->d_tiles[s]) (void)hipFree(b->d_tiles[s]);
-    for (int s = 0; s < kMaxTwo; ++s)
+    for (int s = 0; s < kMaxPass; ++s)
         if (b->d_tiles2[s]) (void)hipFree(b->d_tiles2[s]);
     delete b;
 }
@@ -551,7 +591,7 @@ int lbm_batch_init(lbm_batch *b, const double *phi0, void *f_a, void *f_b, void 
 }
 
 int lbm_batch_set_shape(lbm_batch *b, int shape, unsigned grid, int remap) {
-    if (!b || shape < 0 || shape >= kNumShapes + (b ? b->ntwo : 0))
+    if (!b || shape < 0 || shape >= kNumShapes + (b ? b->npass : 0))
         return api_fail(LBM_E_INVALID, "bad shape index");
     b->shape = shape;
     b->grid = grid;
@@ -565,10 +605,10 @@ int lbm_batch_get_shape(const lbm_batch *b, int *shape, unsigned *grid, int *rem
     if (shape) *shape = b->shape;
     if (grid) *grid = b->grid;
     if (remap) *remap = b->remap;
-    if (is_two(b)) {
-        const TwoShape t = two_shape(b, b->shape - kNumShapes);
+    if (is_pass(b)) {
+        const PassShape t = pass_shape(b, b->shape - kNumShapes);
         if (wg) *wg = 64 * t.waves;
-        if (npt) *npt = -t.rows;    // minus the tile rows: two steps per launch
+        if (npt) *npt = -t.rows;    // minus the tile rows: several steps per launch
     } else {
         if (wg) *wg = kShapes[b->shape].wg;
         if (npt) *npt = kShapes[b->shape].npt;
@@ -581,7 +621,10 @@ int lbm_batch_step(lbm_batch *b, int nsteps, void *stream) {
     if (!b->bound) return api_fail(LBM_E_STATE, "lbm_batch_init has not been called");
     if (nsteps < 0) return api_fail(LBM_E_INVALID, "negative step count");
     hipStream_t st = (hipStream_t)stream;
-    while (nsteps >= kBatchGraphSteps) {
+    // a pass of several steps lasts longer than its launch takes the host, so
+    // only single sweeps and two-step passes are replayed from graphs
+    const bool graphs = !is_pass(b) || pass_shape(b, b->shape - kNumShapes).steps == 2;
+    while (graphs && nsteps >= kBatchGraphSteps) {
         if (!b->gexec[b->cur]) {
             hipError_t e = make_graph(b, b->cur);
             if (e != hipSuccess) return api_fail(LBM_E_HIP, hipGetErrorString(e));
@@ -631,7 +674,7 @@ int lbm_batch_tune(lbm_batch *b, int reps, int use_cache, void *stream, char *re
     std::ostringstream rep;
     int shape = 0, remap = 1;
     uint32_t grid = 0;
-    if (use_cache && cache_lookup(b->key, shape, grid, remap) && shape < kNumShapes + b->ntwo) {
+    if (use_cache && cache_lookup(b->key, shape, grid, remap) && shape < kNumShapes + b->npass) {
         lbm_batch_set_shape(b, shape, grid, remap);
         rep << "cached " << b->key << " shape " << shape << " grid " << grid << " remap " << remap;
     } else {
@@ -649,6 +692,11 @@ int lbm_batch_tune(lbm_batch *b, int reps, int use_cache, void *stream, char *re
         for (int s = 0; s < kNumShapes; ++s)
             for (uint32_t gr : grids)
                 for (int rm = 0; rm < 2; ++rm) {
+                    // with passes to choose from (46.9 us per step against 148
+                    // for the best single sweep on 128 instances of FP32), the
+                    // persistent grids of single sweeps are not worth their
+                    // trials
+                    if (b->npass && gr) continue;
                     b->shape = s; b->grid = gr; b->remap = rm;
                     // sweeps read the current state and write the other buffer only
                     hipError_t e = batch_sweep_launch(b, b->f[b->cur], b->f[b->cur ^ 1], st, s);
@@ -668,14 +716,15 @@ int lbm_batch_tune(lbm_batch *b, int reps, int use_cache, void *stream, char *re
                         << ": " << ms << " ms\n";
                     if (ms < best) { best = ms; shape = s; grid = gr; remap = rm; }
                 }
-        // two steps per launch: time per step
-        for (int i = 0; i < b->ntwo; ++i)
+        // passes of several steps: time per step
+        for (int i = 0; i < b->npass; ++i)
             for (int rm = 0; rm < 2; ++rm) {
                 b->shape = kNumShapes + i; b->grid = 0; b->remap = rm;
-                hipError_t e = batch_sweep2_launch(b, b->f[b->cur], b->f[b->cur ^ 1], st);
+                const PassShape t = pass_shape(b, i);
+                hipError_t e = batch_pass_launch(b, b->f[b->cur], b->f[b->cur ^ 1], st, i);
                 if (e == hipSuccess) e = hipEventRecord(e0, st);
                 for (int r = 0; r < reps && e == hipSuccess; ++r)
-                    e = batch_sweep2_launch(b, b->f[b->cur], b->f[b->cur ^ 1], st);
+                    e = batch_pass_launch(b, b->f[b->cur], b->f[b->cur ^ 1], st, i);
                 if (e == hipSuccess) e = hipEventRecord(e1, st);
                 if (e == hipSuccess) e = hipEventSynchronize(e1);
                 float ms = 0.f;
@@ -684,9 +733,8 @@ int lbm_batch_tune(lbm_batch *b, int reps, int use_cache, void *stream, char *re
                     (void)hipEventDestroy(e0); (void)hipEventDestroy(e1);
                     return api_fail(LBM_E_HIP, hipGetErrorString(e));
                 }
-                ms /= 2 * reps;
-                const TwoShape t = two_shape(b, i);
-                rep << "two steps per launch rows " << t.rows << " waves " << t.waves << " remap " << rm << ": "
+                ms /= t.steps * reps;
+                rep << t.steps << " steps per launch rows " << t.rows << " waves " << t.waves << " remap " << rm << ": "
                     << ms << " ms per step\n";
                 if (ms < best) { best = ms; shape = kNumShapes + i; grid = 0; remap = rm; }
             }

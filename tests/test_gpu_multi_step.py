@@ -104,3 +104,30 @@ def test_divergence_check_with_passes(every):
     with pytest.raises(lbm.LbmError) as e:
         c.step(16)
     assert e.value.code == lbm.LBM_E_DIVERGED
+
+
+@pytest.mark.parametrize("prec,shape", [("f32", 6), ("f32", 7), ("f16", 6), ("f16", 7), ("f64", 5), ("f64", 6)])
+def test_batch_passes_identical(prec, shape):
+    """Uneven instances (narrower and lower than a tile among them) in passes
+    of several steps, forced and by default, against the instances alone."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    sizes = [(100, 37), (3, 2), (54, 22), (131, 70), (33, 200)]
+    specs = [_spec(nx, ny, prec, source="none") for nx, ny in sizes]
+    phi0 = [W.noise_field((ny, nx), 5 + i) for i, (nx, ny) in enumerate(sizes)]
+    b = lbm.Batch(specs).init(phi0)
+    assert b.get_shape()["npt"] < 0
+    b.set_shape(shape, 0, 1)
+    for n in (6, 13, 8, 32):
+        b.step(n)
+    refs = []
+    for sp, p in zip(specs, phi0):
+        a = lbm.Lbm(sp).init(p)
+        a.set_two_step(False)
+        a.step(59)
+        refs.append(a.phi())
+    for got, ref in zip(b.unpack(b.phi()), refs):
+        assert torch.equal(got, ref)
+    with pytest.raises(lbm.LbmError):
+        b.set_shape(shape + (2 if prec != "f64" else 1) if shape == 6 else 9, 0, 1)
