@@ -243,9 +243,9 @@ int lbm_tune(lbm_ctx *ctx, int reps, void *stream, char *report, size_t report_l
  *    and y) feeding a ring of three planes in LDS that phase 2 (step t + 1)
  *    reads one plane behind.  Passes run in pairs; with a Scheme-A source
  *    they alternate the history between p and p2 as in 2-D.
- * Remaining steps use single sweeps.  On by default where it applies (with a
- * Scheme-A source: where p2 is bound); lbm_tune times it against single
- * sweeps.  Not used with per-node fields or Remark III.
+ * Remaining steps use single sweeps.  On by default where it applies and
+ * lbm_set_multi_step does not (with a Scheme-A source: where p2 is bound);
+ * lbm_tune times it against single sweeps.  Not used with per-node fields or Remark III.
  * mode: 0 off; k >= 1 on with tile shape k - 1 (lbm_two_step_shape; shape 0
  * is the default).  The non-default D2Q9 shapes need every polynomial of
  * degree <= 2.
@@ -264,18 +264,23 @@ int lbm_set_two_step(lbm_ctx *ctx, int mode);
  * shape. */
 int lbm_two_step_shape(const lbm_ctx *ctx, int shape, int *rows, int *waves);
 
-/* Passes of several time steps for D2Q9 (polynomials of degree <= 2, 32-bit
- * offsets; periodic or walls on y, equal or unequal rates, any source; with a
- * Scheme-A source where p2 is bound): the scheme of lbm_set_two_step with 8, 6
- * or 4 steps, a halo of as many nodes less one, and the same bits.  Passes run
+/* Passes of several time steps (polynomials of degree <= 2, 32-bit offsets;
+ * periodic or walls on the last axis, any source; with a Scheme-A source where
+ * p2 is bound), with the bits of single sweeps.  D2Q9, equal or unequal rates:
+ * the scheme of lbm_set_two_step with 8, 6 or 4 steps and a halo of as many
+ * nodes less one.  D3Q19, equal rates: two steps in columns of whole 64-node
+ * lines (one shape), which need fewer columns than lbm_set_two_step's of 62
+ * where nx is a multiple of 64.  Passes run
  * in pairs (their lengths may differ), so state and history end where single
  * sweeps leave them; the last one to three steps of a call use single sweeps.
  * On by default where it applies, in a shape picked for the grid, and
- * launched directly (no graphs); lbm_tune times the shapes; lbm_set_two_step
- * turns it off.  Not used with per-node fields or Remark III.
+ * launched directly (no graphs); D3Q19 below 300000 nodes starts with single
+ * sweeps, FP64 with two-step passes where lines save no column.  lbm_tune times
+ * the shapes; lbm_set_two_step turns it off.  Not used with per-node fields or
+ * Remark III.
  * mode: -1 on in the library's pick, 0 off, k >= 1 on in shape k - 1.
  * lbm_multi_step_shape: steps per pass, tile rows and waves per workgroup of a
- * shape (the tile is 66 - 2 steps nodes wide).
+ * shape (the D2Q9 tile is 66 - 2 steps nodes wide).
  * Errors: LBM_E_UNSUPPORTED / LBM_E_INVALID / LBM_E_STATE as lbm_set_two_step. */
 int lbm_multi_step_shape(const lbm_ctx *ctx, int shape, int *steps, int *rows, int *waves);
 int lbm_set_multi_step(lbm_ctx *ctx, int mode);

@@ -64,9 +64,9 @@ struct lbm_ctx {
     // only when the run keeps a history), and whether the path is on
     void *p2 = nullptr;
     bool two_ok = false, two = false;
-    // passes of several steps (D2Q9): whether they apply and are on, the shape
-    // of the main pass (multi_shape_of), the library's pick and the workgroup
-    // order of the passes
+    // passes of several steps (D2Q9; D3Q19: two steps in 64-node lines):
+    // whether they apply and are on, the shape of the main pass
+    // (multi_shape_of), the library's pick and the workgroup order
     bool multi_ok = false, multi = false;
     int multi_shape = 0, multi_auto = 0;
     int multi_remap = 1;
@@ -76,6 +76,7 @@ struct lbm_ctx {
     // D3Q19 passes: resident workgroups per CU of each tile shape's kernel
     // (0: not asked yet) and the device's CU count, for the z-chunk choice
     int occ3[4] = {0, 0, 0, 0};
+    int occ3w = 0;            // the same of the passes in 64-node lines
     int ncu = 0;
     int two_shape = 0;        // tile shape of two-step passes (two_step_shape_of; 0: the default)
     int adj_shape = 0;        // tile shape of the two-sweep adjoint (adjoint2_shape_of)
@@ -443,7 +444,7 @@ bool multi_active(const lbm_ctx *c) { return c->multi && c->multi_ok && two_acti
 // Time steps of a main pass (2: two-step passes).
 int pass_steps(const lbm_ctx *c) {
     int steps = 2, rows = 0, waves = 0;
-    if (multi_active(c)) multi_shape_of(c->dm.prec, c->multi_shape, &steps, &rows, &waves);
+    if (multi_active(c) && c->dm.q == 9) multi_shape_of(c->dm.prec, c->multi_shape, &steps, &rows, &waves);
     return steps;
 }
 
@@ -466,6 +467,10 @@ void query_cus(lbm_ctx *c) {
 void prepare_zchunk(lbm_ctx *c) {
     if (c->dm.q != 19 || !c->two_ok || c->two_shape < 0 || c->two_shape > 3) return;
     query_cus(c);
+    if (c->multi_ok && !c->occ3w) {
+        int occ = 0;
+        if (sweep2w_q19_occupancy(eff_dims(c), c->g, &occ) == hipSuccess && occ > 0) c->occ3w = occ;
+    }
     if (!c->occ3[c->two_shape]) {
         int occ = 0;
         if (sweep2_q19_occupancy(eff_dims(c), c->g, c->two_shape, &occ) == hipSuccess && occ > 0)
@@ -543,6 +548,22 @@ int pick_multi(lbm_ctx *c) {
     return f64 ? 4 : 3;
 }
 
+// D3Q19: single sweeps, two-step passes in 62-node columns or in 64-node lines
+// (us per step, single / 62 / 64, 256^3 FP32 450 / 318 / 277, FP64 with a source
+// 934 / 784 / 719; 128^3 60 / 51.5 / 41.3 and 122 / 127 / 100; 96^3 23.5 / 19.6 /
+// 18.9 and 58 / 44.4 / 46).
+//  - Below about 67^3 nodes a pass has too few columns for the chip, and a
+//    column marches through its planes one after the other: single sweeps
+//    (64^3 FP32 9.2 / 12.5 / 9.2, FP64 with a source 16.0 / 22.9 / 17.0).
+//  - FP64 takes 62-node columns where lines do not save one of them (200 x 180
+//    x 160 216 / 231, with a source 248 / 278): its nine waves per workgroup
+//    put three on one SIMD.
+void pick_lines(lbm_ctx *c) {
+    if (!c->multi_ok) return;
+    if (c->g.N < 300000u) c->two = c->multi = false;
+    else if (c->dm.prec == 0 && (c->g.nx + 63) / 64 == (c->g.nx + 61) / 62) c->multi = false;
+}
+
 // z planes per column of the D3Q19 pass.  Each workgroup lives for its chunk
 // of zc planes plus two, and one workgroup slot per CU (or a few) runs them
 // in rounds, so the pass takes about ceil(workgroups / slots) * (zc + 2)
@@ -550,12 +571,9 @@ int pick_multi(lbm_ctx *c) {
 // FP32 14 x 16, one slot per CU: zc = 32 gives 760 workgroups in 2.97
 // rounds, 52 GLUPS; zc = 24 gave 1045 in 4.08, i.e. five rounds, 44.5).
 // Without the occupancy figures: about 1024 workgroups.
-uint32_t zchunk(const lbm_ctx *c) {
-    int rows = 0, waves = 0;
-    if (!two_step3_shape_of(c->dm.prec, c->two_shape, &rows, &waves)) return c->g.nz;
-    const uint64_t tiles_xy = (uint64_t)((c->g.nx + 61) / 62) * ((c->g.ny + (uint32_t)rows - 1) / (uint32_t)rows);
+uint32_t zchunk_for(const lbm_ctx *c, uint32_t width, uint32_t rows, int occ) {
+    const uint64_t tiles_xy = (uint64_t)((c->g.nx + width - 1) / width) * ((c->g.ny + rows - 1) / rows);
     const uint32_t nz = c->g.nz;
-    const int occ = (c->two_shape >= 0 && c->two_shape < 4) ? c->occ3[c->two_shape] : 0;
     if (occ > 0 && c->ncu > 0) {
         const uint64_t slots = (uint64_t)occ * (uint64_t)c->ncu;
         uint32_t best_zc = nz;
@@ -573,6 +591,12 @@ uint32_t zchunk(const lbm_ctx *c) {
     if (tiles_z > nz) tiles_z = nz;
     if (tiles_z < 1) tiles_z = 1;
     return (uint32_t)((nz + tiles_z - 1) / tiles_z);
+}
+
+uint32_t zchunk(const lbm_ctx *c) {
+    int rows = 0, waves = 0;
+    if (!two_step3_shape_of(c->dm.prec, c->two_shape, &rows, &waves)) return c->g.nz;
+    return zchunk_for(c, 62, (uint32_t)rows, (c->two_shape >= 0 && c->two_shape < 4) ? c->occ3[c->two_shape] : 0);
 }
 
 // One D2Q9 pass of `steps` time steps (two-step passes have their own shapes).
@@ -603,6 +627,16 @@ hipError_t launch_pass_q9(lbm_ctx *c, int steps, const void *fin, void *fout, co
 // stands in for p2.
 hipError_t pass_pair(lbm_ctx *c, int start, int a, int b, hipStream_t st) {
     void *p2 = keeps_history(c) ? c->p2 : c->p;
+    if (c->dm.q == 19 && multi_active(c)) {
+        const uint32_t zc = zchunk_for(c, 64, wide3_rows(c->dm.prec), c->occ3w);
+        const Dims d = eff_dims(c);
+        Geom g = c->g;
+        g.remap = c->multi_remap;
+        hipError_t e = launch_sweep2w_q19(d, g, c->d_coefs, c->f[start], c->f[start ^ 1], c->p, p2, c->d_flag, zc, st);
+        if (e == hipSuccess)
+            e = launch_sweep2w_q19(d, g, c->d_coefs, c->f[start ^ 1], c->f[start], p2, c->p, c->d_flag, zc, st);
+        return e;
+    }
     if (c->dm.q == 19) {
         const uint32_t zc = zchunk(c);
         const Dims d = eff_dims(c);
@@ -847,9 +881,10 @@ int lbm_create(const lbm_desc *desc, lbm_ctx **out) {
     c->two_ok = (dm.q == 9 && ((dm.eqr && !dm.wall) || dm.deg3) && c->dm.o32) ||
                 (dm.q == 19 && dm.deg3 && c->dm.o32);
     c->two = c->two_ok;   // on by default where it applies (bit-identical; lbm_tune re-decides)
-    c->multi_ok = c->multi = dm.q == 9 && dm.deg3 && c->dm.o32;
+    c->multi_ok = c->multi = dm.deg3 && c->dm.o32 && (dm.q == 9 || dm.eqr);
     c->multi_remap = (desc->flags & LBM_FLAG_NO_XCD_REMAP) ? 0 : 1;
-    if (c->multi_ok) c->multi_shape = c->multi_auto = pick_multi(c);
+    if (c->multi_ok && dm.q == 9) c->multi_shape = c->multi_auto = pick_multi(c);
+    if (dm.q == 19) pick_lines(c);
     {
         // the two-sweep adjoint: periodic D2Q9 only; its partial slots cover
         // the 6-row tiling, the finer of the two
@@ -1005,11 +1040,20 @@ int lbm_set_two_step(lbm_ctx *c, int mode) {
     return LBM_OK;
 }
 
+// steps, rows of the region and waves of a multi-step shape of this context
+static bool multi_shape(const lbm_ctx *c, int shape, int *steps, int *rows, int *waves) {
+    if (c->dm.q == 9) return multi_shape_of(c->dm.prec, shape, steps, rows, waves);
+    if (shape != 0) return false;
+    *steps = 2;
+    *rows = (int)wide3_rows(c->dm.prec) + 2;
+    *waves = *rows + 1;
+    return true;
+}
+
 int lbm_multi_step_shape(const lbm_ctx *c, int shape, int *steps, int *rows, int *waves) {
     if (!c || !steps || !rows || !waves) return fail(LBM_E_INVALID, "null argument");
     int t = 0, tr = 0, nw = 0;
-    if (!c->multi_ok || !multi_shape_of(c->dm.prec, shape, &t, &tr, &nw))
-        return fail(LBM_E_INVALID, "no such multi-step shape");
+    if (!c->multi_ok || !multi_shape(c, shape, &t, &tr, &nw)) return fail(LBM_E_INVALID, "no such multi-step shape");
     *steps = t;
     *rows = tr - 2 * (t - 1);
     *waves = nw;
@@ -1019,9 +1063,10 @@ int lbm_multi_step_shape(const lbm_ctx *c, int shape, int *steps, int *rows, int
 int lbm_set_multi_step(lbm_ctx *c, int mode) {
     if (!c) return fail(LBM_E_INVALID, "null context");
     if (!c->multi_ok)
-        return fail(LBM_E_UNSUPPORTED, "passes of several steps need D2Q9, polynomials of degree <= 2 and 32-bit offsets");
+        return fail(LBM_E_UNSUPPORTED,
+                    "passes of several steps need polynomials of degree <= 2, 32-bit offsets and, on D3Q19, equal rates");
     int t = 0, tr = 0, nw = 0;
-    if (mode < -1 || (mode > 0 && !multi_shape_of(c->dm.prec, mode - 1, &t, &tr, &nw)))
+    if (mode < -1 || (mode > 0 && !multi_shape(c, mode - 1, &t, &tr, &nw)))
         return fail(LBM_E_INVALID, "mode must be -1 (the pick), 0 (off) or 1 + a multi-step shape");
     if (mode && c->bound && keeps_history(c) && !c->p2)
         return fail(LBM_E_STATE, "passes with a source need the second history buffer (lbm_init p2)");
@@ -1030,6 +1075,7 @@ int lbm_set_multi_step(lbm_ctx *c, int mode) {
     if (c->multi) {
         c->two = true;   // the remainders of a run take two-step passes
         c->multi_shape = mode < 0 ? c->multi_auto : mode - 1;
+        prepare_zchunk(c);
     }
     return LBM_OK;
 }
@@ -1433,15 +1479,15 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
     if (c->multi_ok && two_ready(c) && !general_path(c)) {
         c->two = c->multi = true;
         int nms = 0, mt = 0, mtr = 0, mnw = 0;
-        while (multi_shape_of(c->dm.prec, nms, &mt, &mtr, &mnw)) ++nms;
+        while (multi_shape(c, nms, &mt, &mtr, &mnw)) ++nms;
         float best_ms = 1e30f;
         for (int ri = 0; ri < remaps * nms; ++ri) {
             const int i = ri / remaps;
             const int shape = i == 0 ? c->multi_auto : (i <= c->multi_auto ? i - 1 : i);
-            multi_shape_of(c->dm.prec, shape, &mt, &mtr, &mnw);
+            multi_shape(c, shape, &mt, &mtr, &mnw);
             const uint64_t tiles = (uint64_t)((c->g.nx + 65 - 2 * mt) / (66 - 2 * mt)) *
                                    ((c->g.ny + (uint32_t)(mtr - 2 * mt + 1)) / (uint32_t)(mtr - 2 * mt + 2));
-            if (shape < 3 && tiles > 4ull * (uint64_t)(c->ncu > 0 ? c->ncu : 256)) continue;
+            if (c->dm.q == 9 && shape < 3 && tiles > 4ull * (uint64_t)(c->ncu > 0 ? c->ncu : 256)) continue;
             c->multi_shape = shape;
             c->multi_remap = (remaps == 2 && ri % remaps == 0) ? 1 : 0;
             const int pair_reps = std::max(2, reps * 2 / mt);

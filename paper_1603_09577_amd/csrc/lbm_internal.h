@@ -180,6 +180,14 @@ hipError_t launch_sweep2_q19(const Dims &dm, const Geom &g, const void *coefs, c
 // resident workgroups per CU of the D3Q19 two-step kernel this run would launch
 hipError_t sweep2_q19_occupancy(const Dims &dm, const Geom &g, int shape, int *blocks_per_cu);
 bool two_step3_shape_of(int prec, int shape, int *rows, int *waves);
+// Two time steps per pass, D3Q19 in columns of 64-node lines (sweep_wide_q19.hip;
+// equal rates): own rows of a column.  One halo wave holds both neighbours of
+// every row, and the LDS ring takes 38 x 66 x (rows + 2) values: 147 KiB in
+// FP32, 157 KiB in FP64.
+inline uint32_t wide3_rows(int prec) { return prec == 0 ? 6u : 13u; }
+hipError_t launch_sweep2w_q19(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
+                              const void *pin, void *pout, int *flag, uint32_t zc, hipStream_t st);
+hipError_t sweep2w_q19_occupancy(const Dims &dm, const Geom &g, int *blocks_per_cu);
 // Two reversed sweeps per pass (sweep s, then s - 1), D2Q9 only, in tile
 // shape `shape` (adjoint2_shape_of); and the resident workgroups per CU of
 // that kernel.

@@ -77,6 +77,7 @@ def test_linear_constant_tensor_and_calls():
         s.set_multi_step(True, 5)
     assert e.value.code == lbm.LBM_E_INVALID
     spec3, _, _ = W.d3q19_walls((8, 8, 8))
+    spec3 = dict(spec3, s=[0.0, 1.3] + [1.0] * 17)
     with pytest.raises(lbm.LbmError) as e:
         lbm.Lbm(spec3).set_multi_step(True)
     assert e.value.code == lbm.LBM_E_UNSUPPORTED
@@ -131,3 +132,38 @@ def test_batch_passes_identical(prec, shape):
         assert torch.equal(got, ref)
     with pytest.raises(lbm.LbmError):
         b.set_shape(shape + (2 if prec != "f64" else 1) if shape == 6 else 9, 0, 1)
+
+
+@pytest.mark.parametrize("n,prec,wall,source", [
+    ((64, 13, 9), "f32", True, "none"), ((128, 20, 22), "f64", True, "A"), ((65, 27, 11), "f32", False, "A"),
+    ((63, 7, 5), "f16", True, "A"), ((3, 2, 2), "f32", True, "none"), ((1, 1, 3), "f64", False, "B"),
+    ((130, 37, 21), "f32", True, "B"), ((64, 6, 1), "f64", True, "A"), ((70, 14, 1), "f16", False, "none")])
+def test_d3q19_lines_bit_identical(n, prec, wall, source):
+    """D3Q19, two steps per pass in columns of 64-node lines with a halo wave:
+    grids of whole and partial lines, lower and narrower than a column, one
+    plane between walls, every source."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    spec, _, _ = W.d3q19_walls_source(n, precision=prec)
+    if source == "none":
+        spec = dict(spec, rpoly=[], kpoly=[1.0])
+    elif source == "B":
+        spec = dict(spec, scheme="B")
+    spec = dict(spec, bc=["periodic", "periodic", "abb" if wall else "periodic"],
+                phi_wall=[[0, 0], [0, 0], [0.3, 0.6]] if wall else [[0, 0]] * 3)
+    phi0 = W.noise_field(n[::-1], 7, mean=0.4, amp=0.2)
+    a = lbm.Lbm(spec).init(phi0)
+    a.set_two_step(False)
+    b = lbm.Lbm(spec).init(phi0)
+    b.set_multi_step(True, 0)
+    for k in (4, 5, 16, 34):
+        a.step(k)
+        b.step(k)
+        w, _ = a.current()
+        assert a.current() == b.current()
+        assert torch.equal(a.storage_view(a.f[w]), b.storage_view(b.f[w])), k
+        assert torch.equal(a.phi(), b.phi()), k
+        if source == "A":
+            nb = a.N * (8 if prec == "f64" else 4)
+            assert torch.equal(a.p[:nb], b.p[:nb]), k
