@@ -181,6 +181,16 @@ int lbm_step(lbm_ctx *ctx, int nsteps, void *stream);
  * bound buffers or the step counter. */
 int lbm_sweep(lbm_ctx *ctx, const void *f_in, void *f_out, void *p, void *stream);
 
+/* nsteps sweeps from (f_in, p_in) with every state kept: the state after sweep
+ * i (from 0) goes to f_out + i f_step bytes, its history to p_out + i p_step
+ * (runs without a Scheme-A source or Remark III neither read nor write a
+ * history).  The steps are multiples of 256 that hold a distribution buffer and
+ * a history; inputs and outputs must not overlap.  Bit for bit nsteps calls of
+ * lbm_sweep; runs that qualify take passes of several steps
+ * (lbm_set_multi_step).  Does not touch the bound buffers or the step counter. */
+int lbm_sweep_record(lbm_ctx *ctx, const void *f_in, const void *p_in, void *f_out, size_t f_step, void *p_out,
+                     size_t p_step, int nsteps, void *stream);
+
 /* phi of the current state (Eq. 10a), FP64 [nz][ny][nx] into phi_dev. */
 int lbm_get_phi(lbm_ctx *ctx, double *phi_dev, void *stream);
 

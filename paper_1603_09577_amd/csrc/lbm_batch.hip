@@ -89,7 +89,7 @@ k_batch_sweep(const BatchInst *__restrict__ inst, const Coefs<TC> *__restrict__ 
             const uint32_t n = e.y + j * WG + threadIdx.x;
             if (n < g.N)
                 sweep_node<9, TS, TC, true, SRC, KVAR, false, NP>(g, cf, fin + I.f_off, fout + I.f_off,
-                                                               p + I.p_off, flag, n);
+                                                               p + I.p_off, p + I.p_off, flag, n);
         }
     }
 }

@@ -10,12 +10,13 @@ namespace lbm {
 
 template <int Q, typename TS, typename TC>
 hipError_t sweep_typed(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
-                       void *p, int *flag, hipStream_t st) {
+                       const void *pin, void *pout, int *flag, hipStream_t st) {
     using TP = typename HistType<TS>::T;
     const auto *cf = (const Coefs<TC> *)coefs;
     const auto *fi = (const TS *)fin;
     auto *fo = (TS *)fout;
-    auto *pp = (TP *)p;
+    const auto *pi = (const TP *)pin;
+    auto *po = (TP *)pout;
     const dim3 grid((g.nblocks + g.chunk - 1) / g.chunk), block(kBlock);
     // Scheme B with a source (dm.sb) keeps no history: the Scheme-A flag is off
     const bool sa = dm.src && !dm.sb;
@@ -28,7 +29,7 @@ hipError_t sweep_typed(const Dims &dm, const Geom &g, const void *coefs, const v
 #define LBM_SWEEP3B(K, W, NT)                                                                         \
     case (NT * 8 + K * 2 + W):                                                                        \
         hipLaunchKernelGGL((k_sweep<Q, TS, TC, true, false, K, W, 3, NT, true, false, true>), grid, block, 0, st, g, \
-                           cf, fi, fo, pp, flag);                                                     \
+                           cf, fi, fo, pi, po, flag);                                                     \
         break;
                 switch (cb) {
                     LBM_SWEEP3B(0, 0, 0) LBM_SWEEP3B(0, 1, 0) LBM_SWEEP3B(1, 0, 0) LBM_SWEEP3B(1, 1, 0)
@@ -47,7 +48,7 @@ hipError_t sweep_typed(const Dims &dm, const Geom &g, const void *coefs, const v
 #define LBM_SWEEP3R(S, K, NT)                                                                         \
     case (NT * 8 + S * 4 + K * 2 + 1):                                                                \
         hipLaunchKernelGGL((k_sweep<Q, TS, TC, true, S, K, true, 3, NT, true, true>), grid, block, 0, st, g, cf, fi, fo, \
-                           pp, flag);                                                                 \
+                           pi, po, flag);                                                                 \
         break;
                     switch (c3) {
                         LBM_SWEEP3R(0, 0, 0) LBM_SWEEP3R(0, 1, 0) LBM_SWEEP3R(1, 0, 0) LBM_SWEEP3R(1, 1, 0)
@@ -60,7 +61,7 @@ hipError_t sweep_typed(const Dims &dm, const Geom &g, const void *coefs, const v
             }
 #define LBM_SWEEP3(S, K, W, NT)                                                                       \
     case (NT * 8 + S * 4 + K * 2 + W):                                                                \
-        hipLaunchKernelGGL((k_sweep<Q, TS, TC, true, S, K, W, 3, NT, true>), grid, block, 0, st, g, cf, fi, fo, pp, flag); \
+        hipLaunchKernelGGL((k_sweep<Q, TS, TC, true, S, K, W, 3, NT, true>), grid, block, 0, st, g, cf, fi, fo, pi, po, flag); \
         break;
             switch (c3) {
                 LBM_SWEEP3(0, 0, 0, 0) LBM_SWEEP3(0, 0, 1, 0) LBM_SWEEP3(0, 1, 0, 0) LBM_SWEEP3(0, 1, 1, 0)
@@ -81,7 +82,7 @@ hipError_t sweep_typed(const Dims &dm, const Geom &g, const void *coefs, const v
                      ((dm.eqr && dm.lowdeg) ? 16 : 0) | ((dm.eqr && dm.lowdeg && dm.nt) ? 32 : 0);
 #define LBM_SWEEP_X(E, S, K, W, NP, NT, TAG)                                                          \
     case (TAG + E * 8 + S * 4 + K * 2 + W):                                                           \
-        hipLaunchKernelGGL((k_sweep<Q, TS, TC, E, S, K, W, NP, NT>), grid, block, 0, st, g, cf, fi, fo, pp, flag); \
+        hipLaunchKernelGGL((k_sweep<Q, TS, TC, E, S, K, W, NP, NT>), grid, block, 0, st, g, cf, fi, fo, pi, po, flag); \
         break;
 #define LBM_SWEEP_NP(E, S, K, W, NP, TAG) LBM_SWEEP_X(E, S, K, W, NP, false, TAG)
 #define LBM_SWEEP(E, S, K, W) LBM_SWEEP_NP(E, S, K, W, 9, 0)
@@ -340,19 +341,20 @@ hipError_t sweep2_3d_typed(const Dims &dm, const Geom &g, const void *coefs, con
 // every polynomial has degree <= 2 and every array spans less than 4 GiB.
 template <int Q, typename TS, typename TC>
 hipError_t sweep_gen_typed(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
-                           void *p, int *flag, const double *kfield, const double *rfield, bool remark3,
+                           const void *pin, void *pout, int *flag, const double *kfield, const double *rfield, bool remark3,
                            hipStream_t st) {
     using TP = typename HistType<TS>::T;
     const auto *cf = (const Coefs<TC> *)coefs;
     const auto *fi = (const TS *)fin;
     auto *fo = (TS *)fout;
-    auto *pp = (TP *)p;
+    const auto *pi = (const TP *)pin;
+    auto *po = (TP *)pout;
     const dim3 grid(g.nblocks), block(kBlock);
     const int code = (dm.eqr ? 4 : 0) | (dm.wall ? 2 : 0) | (dm.sb ? 1 : 0) | (dm.deg3 && dm.o32 ? 8 : 0);
 #define LBM_GEN(E, W, B, NP)                                                                        \
     case ((NP == 3) * 8 + E * 4 + W * 2 + B):                                                       \
-        hipLaunchKernelGGL((k_sweep_gen<Q, TS, TC, E, W, B, NP>), grid, block, 0, st, g, cf, fi, fo, pp, flag, \
-                           kfield, rfield, remark3 ? 1 : 0);                                        \
+        hipLaunchKernelGGL((k_sweep_gen<Q, TS, TC, E, W, B, NP>), grid, block, 0, st, g, cf, fi, fo, pi, po, \
+                           flag, kfield, rfield, remark3 ? 1 : 0);                                        \
         break;
     switch (code) {
         LBM_GEN(0, 0, 0, 9) LBM_GEN(0, 0, 1, 9) LBM_GEN(0, 1, 0, 9) LBM_GEN(0, 1, 1, 9)

@@ -115,9 +115,10 @@ inline uint64_t plane_stride(uint64_t n, int q, size_t elem, int pad_req) {
 // Kernel launchers, one set per lattice (sweep_d2q9.hip, sweep_d3q19.hip).
 #define LBM_LAUNCHERS(SFX)                                                                              \
     hipError_t launch_sweep_##SFX(const Dims &dm, const Geom &g, const void *coefs, const void *fin,   \
-                                  void *fout, void *p, int *flag, hipStream_t st);                      \
+                                  void *fout, const void *pin, void *pout, int *flag, hipStream_t st); \
     hipError_t launch_sweep_gen_##SFX(const Dims &dm, const Geom &g, const void *coefs, const void *fin, \
-                                      void *fout, void *p, int *flag, const double *kfield,             \
+                                      void *fout, const void *pin, void *pout, int *flag,               \
+                                      const double *kfield,                                             \
                                       const double *rfield, bool remark3, hipStream_t st);              \
     hipError_t launch_init_##SFX(const Dims &dm, const Geom &g, const void *coefs, const double *phi0, \
                                  void *f, void *p, const double *rfield, hipStream_t st);               \
@@ -155,6 +156,12 @@ hipError_t launch_sweep2_q9(const Dims &dm, const Geom &g, const void *coefs, co
 // four steps on more rows.
 hipError_t launch_sweep_multi_q9(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
                                  const void *pin, void *pout, int *flag, int shape, hipStream_t st);
+// The same with every step's state recorded: step s (from 0) goes to fout +
+// s f_step bytes and its history to pout + s p_step bytes (FP64 and FP32,
+// equal rates, no Scheme B; 6 steps or 4, `tall` regions or one row per wave).
+hipError_t launch_sweep_record_q9(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
+                                  size_t f_step, const void *pin, void *pout, size_t p_step, int *flag, int steps,
+                                  bool tall, hipStream_t st);
 hipError_t launch_sweep_multi_q9_f64(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
                                      const void *pin, void *pout, int *flag, int shape, hipStream_t st);
 hipError_t launch_sweep_multi_q9_f32(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,

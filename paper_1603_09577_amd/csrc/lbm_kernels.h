@@ -848,7 +848,8 @@ template <int Q, typename TS, typename TC, bool EQR, bool SRC, bool KVAR, bool W
           bool SB = false, bool KF = false, bool O32 = false, bool RW = false>
 __device__ __forceinline__ void sweep_node(const Geom &g, const Coefs<TC> *__restrict__ cf,
                                            const TS *__restrict__ fin, TS *__restrict__ fout,
-                                           typename HistType<TS>::T *p, int *flag, uint32_t n,
+                                           const typename HistType<TS>::T *pin,
+                                           typename HistType<TS>::T *pout, int *flag, uint32_t n,
                                            const double *kfield = nullptr, const double *rfield = nullptr,
                                            bool rem3 = false) {
     TC h[Q];
@@ -861,10 +862,10 @@ __device__ __forceinline__ void sweep_node(const Geom &g, const Coefs<TC> *__res
         gather<Q, WALL, NT, O32>(g, cf, fin, ng, h);
     }
     // history read issued together with the gathers, so its latency overlaps theirs
-    const TC pp_off = (SRC || rem3) ? (TC)*at<O32>(p, n) : TC(0);
+    const TC pp_off = (SRC || rem3) ? (TC)*at<O32>(pin, n) : TC(0);
     TC out[Q];
     const TC phio = collide_node<Q, TC, EQR, SRC, KVAR, NP, SB, KF>(cf, h, pp_off, n, kfield, rfield, rem3, out);
-    if (SRC || rem3) *at<O32>(p, n) = (typename HistType<TS>::T)phio;
+    if (SRC || rem3) *at<O32>(pout, n) = (typename HistType<TS>::T)phio;
 
     if constexpr (O32) {
         store_planes<Q, NT>(fout, g.plane, n, out);
@@ -883,14 +884,15 @@ template <int Q, typename TS, typename TC, bool EQR, bool SRC, bool KVAR, bool W
           bool RW = false, bool SB = false>
 __global__ void __launch_bounds__(kBlock)
 k_sweep(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin,
-        TS *__restrict__ fout, typename HistType<TS>::T *p, int *flag) {
+        TS *__restrict__ fout, const typename HistType<TS>::T *pin, typename HistType<TS>::T *pout, int *flag) {
+    // (pin and pout may be the same buffer: a node reads and writes its own value)
     // each workgroup sweeps `chunk` consecutive blocks; with the XCD-aware
     // order every XCD covers one contiguous slab of the domain
     const uint32_t first = block_index(blockIdx.x, gridDim.x, g.remap) * g.chunk;
     for (uint32_t i = 0; i < g.chunk; ++i) {
         const uint32_t n = (first + i) * kBlock + threadIdx.x;
         if (n >= g.N) return;
-        sweep_node<Q, TS, TC, EQR, SRC, KVAR, WALL, NP, NT, SB, false, O32, RW>(g, cf, fin, fout, p, flag, n);
+        sweep_node<Q, TS, TC, EQR, SRC, KVAR, WALL, NP, NT, SB, false, O32, RW>(g, cf, fin, fout, pin, pout, flag, n);
     }
 }
 
@@ -1340,12 +1342,12 @@ k_sweep2_3d(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict
 template <int Q, typename TS, typename TC, bool EQR, bool WALL, bool SB, int NP>
 __global__ void __launch_bounds__(kBlock)
 k_sweep_gen(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin,
-            TS *__restrict__ fout, typename HistType<TS>::T *p, int *flag, const double *kfield,
-            const double *rfield, int remark3) {
+            TS *__restrict__ fout, const typename HistType<TS>::T *pin, typename HistType<TS>::T *pout, int *flag,
+            const double *kfield, const double *rfield, int remark3) {
     const uint32_t n = block_index(blockIdx.x, gridDim.x, g.remap) * kBlock + threadIdx.x;
     if (n >= g.N) return;
-    sweep_node<Q, TS, TC, EQR, !SB, true, WALL, NP, false, SB, true, NP == 3>(g, cf, fin, fout, p, flag, n, kfield,
-                                                                             rfield, remark3 != 0);
+    sweep_node<Q, TS, TC, EQR, !SB, true, WALL, NP, false, SB, true, NP == 3>(g, cf, fin, fout, pin, pout, flag, n,
+                                                                             kfield, rfield, remark3 != 0);
 }
 
 // ---------------------------------------------------------------------------

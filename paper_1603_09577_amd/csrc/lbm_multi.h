@@ -43,12 +43,16 @@
 
 namespace lbm {
 
-template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, bool EQ>
+// REC: every step's state of the tile is stored, step s at fout + s fstep and
+// its history at pout + s pstep (elements): a run that needs all states (the
+// adjoint's recomputation) then reads one state per pass instead of one per step.
+template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, bool EQ,
+          bool REC = false>
 __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> *__restrict__ cf,
                                                  const TS *__restrict__ fin, TS *__restrict__ fout,
                                                  const typename HistType<TS>::T *__restrict__ pin,
                                                  typename HistType<TS>::T *__restrict__ pout, uint32_t tx,
-                                                 uint32_t ty, int *flag) {
+                                                 uint32_t ty, int *flag, uint64_t fstep = 0, uint64_t pstep = 0) {
     using L = Lattice<9>;
     using TP = typename HistType<TS>::T;
     static_assert(T % 2 == 0 && TR % NW == 0 && std::is_same<TP, TC>::value, "even passes, whole rows per wave");
@@ -67,6 +71,11 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
     const bool own = lane >= H && lane < TX - H && x0 - H + lane < nx;
     SrcLevel<TC> lev[SRC ? NR : 1];
     bool bad = false;
+    auto store = [&](int s, int yl, const TC *out, TC phio) {
+        const uint32_t m = (uint32_t)yl * g.nx + (uint32_t)(x0 - H + lane);
+        store_planes<9, false>(fout + (REC ? (uint64_t)s * fstep : 0), g.plane, m, out);
+        if (SRC) *at<true>(pout + (REC ? (uint64_t)s * pstep : 0), m) = (TP)phio;
+    };
     // step 0: scalar row base plus one of three column offsets per load
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
@@ -85,8 +94,9 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
             h[k] = wl ? -v + cf->ew[cy == 1 ? 0 : 1][k] : v;
         }
         const TC pp = SRC ? (TC)*at<true>(pin, (uint32_t)yg * g.nx + (uint32_t)xg) : TC(0);
-        collide_node<9, TC, EQ, SRC, KVAR, 3, SB>(cf, h, pp, 0u, nullptr, nullptr, false, out,
-                                                  SRC ? &lev[SRC ? i : 0] : nullptr);
+        const TC phi0 = collide_node<9, TC, EQ, SRC, KVAR, 3, SB>(cf, h, pp, 0u, nullptr, nullptr, false, out,
+                                                                  SRC ? &lev[SRC ? i : 0] : nullptr);
+        if (REC && own && r >= H && r < TR - H && yl < ny) store(0, yl, out, phi0);
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
             const int cy = L::cy(k), cx = L::cx(k);
@@ -124,13 +134,12 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
                     const int idx = ODD || wl ? (r * 9 + L::opp(k)) * TX : ((r + cy) * 9 + k) * TX + cx;
                     cell[idx] = to_store<TS>(out[k]);
                 }
+                if (REC && own && r >= H && r < TR - H && yl < ny) store(s, yl, out, phio);
             } else if (own && yl < ny) {
                 // a non-finite phi of an earlier step reaches the same node's
                 // later ones through its rest population
                 bad |= !__builtin_isfinite(phio);
-                const uint32_t m = (uint32_t)yl * g.nx + (uint32_t)(x0 - H + lane);
-                store_planes<9, false>(fout, g.plane, m, out);
-                if (SRC) *at<true>(pout, m) = (TP)phio;
+                store(T - 1, yl, out, phio);
             }
         }
     };
@@ -157,6 +166,17 @@ k_sweep_multi(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restri
     const uint32_t tile = block_index(blockIdx.x, gridDim.x, g.remap);
     const uint32_t ty = tile / tiles_x, tx = tile - ty * tiles_x;
     sweep_multi_tile<TS, TC, SRC, KVAR, T, TR, NW, SB, WALL, EQ>(g, cf, fin, fout, pin, pout, tx, ty, flag);
+}
+
+template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool WALL>
+__global__ void __launch_bounds__(64 * NW)
+k_sweep_record(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin, TS *__restrict__ fout,
+               uint64_t fstep, const typename HistType<TS>::T *__restrict__ pin,
+               typename HistType<TS>::T *__restrict__ pout, uint64_t pstep, uint32_t tiles_x, int *flag) {
+    const uint32_t tile = block_index(blockIdx.x, gridDim.x, g.remap);
+    const uint32_t ty = tile / tiles_x, tx = tile - ty * tiles_x;
+    sweep_multi_tile<TS, TC, SRC, KVAR, T, TR, NW, false, WALL, true, true>(g, cf, fin, fout, pin, pout, tx, ty, flag,
+                                                                           fstep, pstep);
 }
 
 }  // namespace lbm

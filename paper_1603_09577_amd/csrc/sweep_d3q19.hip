@@ -5,8 +5,8 @@
 namespace lbm {
 
 hipError_t launch_sweep_q19(const Dims &dm, const Geom &g, const void *coefs, const void *fin,
-                            void *fout, void *p, int *flag, hipStream_t st) {
-    LBM_BY_PREC(sweep_typed, dm, g, coefs, fin, fout, p, flag, st)
+                            void *fout, const void *pin, void *pout, int *flag, hipStream_t st) {
+    LBM_BY_PREC(sweep_typed, dm, g, coefs, fin, fout, pin, pout, flag, st)
 }
 
 hipError_t launch_init_q19(const Dims &dm, const Geom &g, const void *coefs, const double *phi0,
@@ -25,9 +25,9 @@ hipError_t launch_phi_reduce_q19(const Dims &dm, const Geom &g, const void *coef
 }
 
 hipError_t launch_sweep_gen_q19(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
-                               void *p, int *flag, const double *kfield, const double *rfield, bool remark3,
-                               hipStream_t st) {
-    LBM_BY_PREC(sweep_gen_typed, dm, g, coefs, fin, fout, p, flag, kfield, rfield, remark3, st)
+                               const void *pin, void *pout, int *flag, const double *kfield, const double *rfield,
+                               bool remark3, hipStream_t st) {
+    LBM_BY_PREC(sweep_gen_typed, dm, g, coefs, fin, fout, pin, pout, flag, kfield, rfield, remark3, st)
 }
 
 hipError_t launch_recenter_q19(const Dims &dm, const Geom &g, void *coefs, void *f, void *p, double *part,

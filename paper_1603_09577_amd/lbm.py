@@ -33,7 +33,8 @@ EXPORTS = [
     "lbm_batch_step", "lbm_batch_get_phi", "lbm_batch_tune", "lbm_batch_set_shape",
     "lbm_batch_get_shape", "lbm_batch_destroy", "lbm_probe_copy", "lbm_set_chunk", "lbm_tune",
     "lbm_set_nontemporal", "lbm_recenter", "lbm_set_recenter", "lbm_set_fields", "lbm_set_phi_wall",
-    "lbm_set_two_step", "lbm_two_step_shape", "lbm_set_multi_step", "lbm_multi_step_shape", "lbm_adjoint_step2", "lbm_adjoint_pair_ok", "lbm_set_remap",
+    "lbm_set_two_step", "lbm_two_step_shape", "lbm_set_multi_step", "lbm_multi_step_shape",
+    "lbm_sweep_record", "lbm_adjoint_step2", "lbm_adjoint_pair_ok", "lbm_set_remap",
     "lbm_adjoint_tile_shape", "lbm_set_adjoint_tile", "lbm_adjoint_tile",
     "lbm_reduce_async", "lbm_reduce_state", "lbm_reduce_noalloc",
 ]
@@ -94,6 +95,8 @@ def load():
         "lbm_init": ([_VP, _VP, _VP, _VP, _VP, _VP, _VP], ctypes.c_int),
         "lbm_step": ([_VP, ctypes.c_int, _VP], ctypes.c_int),
         "lbm_sweep": ([_VP, _VP, _VP, _VP, _VP], ctypes.c_int),
+        "lbm_sweep_record": ([_VP, _VP, _VP, _VP, ctypes.c_size_t, _VP, ctypes.c_size_t, ctypes.c_int, _VP],
+                             ctypes.c_int),
         "lbm_get_phi": ([_VP, _VP, _VP], ctypes.c_int),
         "lbm_phi_of": ([_VP, _VP, _VP, _VP], ctypes.c_int),
         "lbm_current": ([_VP, ctypes.POINTER(_VP), ctypes.POINTER(_VP), ctypes.POINTER(ctypes.c_longlong)], ctypes.c_int),
@@ -274,6 +277,14 @@ class Lbm:
 
     def sweep(self, f_in, f_out, p, stream=None):
         _check(self.lib.lbm_sweep(self.ctx, _ptr(f_in), _ptr(f_out), _ptr(p), _stream(stream)))
+
+    def sweep_record(self, f_in, p_in, f_out, p_out, n, stream=None):
+        """n sweeps from (f_in, p_in); f_out and p_out are 2-D uint8 tensors
+        whose row i takes the state and the history after sweep i."""
+        if n > min(f_out.shape[0], p_out.shape[0]):
+            raise ValueError("fewer rows than sweeps")
+        _check(self.lib.lbm_sweep_record(self.ctx, _ptr(f_in), _ptr(p_in), _ptr(f_out), f_out.stride(0), _ptr(p_out),
+                                         p_out.stride(0), int(n), _stream(stream)))
 
     def phi(self, out=None, stream=None):
         import torch

@@ -67,14 +67,15 @@ class LbmRollout(torch.autograd.Function):
         cur_psi, pi = sim.adjoint_buffers()
         psi_other, pi_other = sim.adjoint_buffers()
         sim.adjoint_seed(gphi, cur_psi, pi)
-        ring = [(torch.empty_like(sim.f[0]), torch.empty_like(sim.p)) for _ in range(seg)]
+        # the states of a segment: its checkpoint, then the recomputed ones
+        rows = max(1, min(seg, ctx.nsteps) - 1)
+        fs = torch.empty((rows, sim.f_bytes), dtype=torch.uint8, device=sim.device)
+        ps = torch.empty((rows, sim.p_bytes), dtype=torch.uint8, device=sim.device)
         for t0, fck, pck in reversed(ctx.checkpoints):
             n = min(seg, ctx.nsteps - t0)
-            ring[0][0].copy_(fck)
-            ring[0][1].copy_(pck)
-            for i in range(1, n):
-                ring[i][1].copy_(ring[i - 1][1])
-                sim.sweep(ring[i - 1][0], ring[i][0], ring[i][1])
+            ring = [(fck, pck)] + [(fs[i], ps[i]) for i in range(n - 1)]
+            if n > 1:
+                sim.sweep_record(fck, pck, fs, ps, n - 1)
             i = n - 1
             while i >= 0:
                 if use_pairs and i >= 1:

@@ -167,3 +167,52 @@ def test_d3q19_lines_bit_identical(n, prec, wall, source):
         if source == "A":
             nb = a.N * (8 if prec == "f64" else 4)
             assert torch.equal(a.p[:nb], b.p[:nb]), k
+
+
+@pytest.mark.parametrize("nx,ny,prec,source,wall,rates,n", [
+    (512, 512, "f64", "A", False, "equal", 7), (100, 37, "f64", "A", True, "equal", 8),
+    (59, 31, "f32", "A", False, "equal", 9), (700, 300, "f32", "none", True, "equal", 10),
+    (3, 2, "f64", "none", False, "equal", 5), (1, 5, "f32", "A", True, "equal", 4), (600, 605, "f64", "A", True, "equal", 6),
+    (1100, 1000, "f32", "A", False, "equal", 11), (40, 30, "f64", "B", False, "equal", 6),
+    (40, 30, "f64", "A", False, "unequal", 6), (64, 40, "f16", "A", False, "equal", 6)])
+def test_recorded_states_bit_identical(nx, ny, prec, source, wall, rates, n):
+    """Every recorded state and history against single sweeps; what lies
+    beyond a state in its row stays as it was."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    spec = _spec(nx, ny, prec, source, wall, rates)
+    s = lbm.Lbm(spec).init(W.noise_field((ny, nx), 5))
+    s.step(2)
+    w, _ = s.current()
+    f, p = s.f[w].clone(), s.p.clone()
+    hist = source == "A"
+    fs = torch.full((n, s.f_bytes + 512), 7, dtype=torch.uint8, device="cuda")
+    ps = torch.full((n, s.p_bytes + 256), 7, dtype=torch.uint8, device="cuda")
+    s.sweep_record(f, p, fs, ps, n)
+    nb = nx * ny * (8 if prec == "f64" else 4)
+    for i in range(n):
+        out = torch.empty_like(f)
+        s.sweep(f, out, p)
+        assert torch.equal(s.storage_view(out), s.storage_view(fs[i][:s.f_bytes])), i
+        assert not hist or torch.equal(p[:nb], ps[i][:nb]), i
+        assert (fs[i][s.f_bytes:] == 7).all() and (ps[i][nb:] == 7).all(), i
+        f = out
+
+
+def test_recorded_sweeps_refusals():
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    s = lbm.Lbm(_spec(20, 20, "f64")).init(W.noise_field((20, 20), 5))
+    fs = torch.empty((2, s.f_bytes), dtype=torch.uint8, device="cuda")
+    ps = torch.empty((2, s.p_bytes), dtype=torch.uint8, device="cuda")
+    w, _ = s.current()
+    with pytest.raises(ValueError):
+        s.sweep_record(s.f[w], s.p, fs, ps, 3)
+    for a, b in ((fs[:, :256], ps), (fs, ps[:, :8])):
+        with pytest.raises(lbm.LbmError) as e:
+            s.sweep_record(s.f[w], s.p, a.contiguous(), b.contiguous(), 2)
+        assert e.value.code == lbm.LBM_E_INVALID
+    with pytest.raises(lbm.LbmError):
+        s.sweep_record(fs[0], s.p, fs, ps, 2)
