@@ -50,48 +50,72 @@ __device__ __forceinline__ void eq_derivative(const Coefs<TC> *__restrict__ cf, 
     }
 }
 
-// Adjoint of A = G^-1 for a symmetric Abar (full storage Ab[a][b]):
-// Gbar = -A Abar A (symmetric), returned in symmetric slots.
+// y = A x for a symmetric A.
 template <int DIM, typename TC>
-__device__ __forceinline__ void gbar_of(const TC *A, const TC Ab[3][3], TC *Gb) {
-    TC T[3][3];
+__device__ __forceinline__ void sym_mul(const TC *A, const TC *x, TC *y) {
 #pragma unroll
-    for (int a = 0; a < DIM; ++a)
+    for (int a = 0; a < DIM; ++a) {
+        TC acc = TC(0);
 #pragma unroll
-        for (int b = 0; b < DIM; ++b) {
-            TC acc = TC(0);
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) acc += A[sym(a, c)] * TC(0.5) * (Ab[c][b] + Ab[b][c]);
-            T[a][b] = acc;
-        }
-#pragma unroll
-    for (int i = 0; i < 6; ++i) Gb[i] = TC(0);
-#pragma unroll
-    for (int a = 0; a < DIM; ++a)
-#pragma unroll
-        for (int b = a; b < DIM; ++b) {
-            TC acc = TC(0);
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) acc += T[a][c] * A[sym(c, b)];
-            Gb[sym(a, b)] = -acc;
-        }
+        for (int b = 0; b < DIM; ++b) acc += A[sym(a, b)] * x[b];
+        y[a] = acc;
+    }
 }
 
-// Contribution of Gbar at a phi value to dL/dphi (when k varies) and to the
-// per-node K0 accumulator (symmetric parametrisation: off-diagonal entries
-// count twice).
-template <int DIM, bool KVAR, int NP, typename TC>
-__device__ __forceinline__ TC gbar_scatter(const Coefs<TC> *__restrict__ cf, TC phi, const TC *Gb, TC *gk) {
-    const TC kv = KVAR ? poly<NP>(cf->kp, phi) : cf->kp[0];
-    // g0 = 3 K0 / d, so dG/dK0_ab = (3/d) k(phi); g0 / K0 = 3 / d is folded on the host
+// The adjoint of G in A = G^-1 is Gbar = -A Abar A.  Every Abar here is a
+// dyad -u v^T, so Gbar is the symmetric part of (A u) (A v)^T, and A u and A v
+// are needed by the rest of the node anyway.  Adds (A u) (A v)^T to P in
+// symmetric slots, an off-diagonal entry with both of its terms (in G and in
+// K0 it stands for two entries).
+template <int DIM, typename TC>
+__device__ __forceinline__ void add_dyad(const TC *au, const TC *av, TC *P) {
 #pragma unroll
-    for (int i = 0; i < 6; ++i) gk[i] += Gb[i] * kv * (i < 3 ? TC(1) : TC(2));
-    if (!KVAR) return TC(0);
-    const TC kd = poly<PolyLen<NP>::ND>(cf->kdp, phi);
+    for (int a = 0; a < DIM; ++a) {
+        P[a] += au[a] * av[a];
+#pragma unroll
+        for (int b = a + 1; b < DIM; ++b) P[sym(a, b)] += au[a] * av[b] + au[b] * av[a];
+    }
+}
+
+// Contribution of P at a phi value to dL/dphi (when k varies) and to the
+// per-node K0 accumulator.  g0 = 3 K0 / d, so dG/dK0_ab = (3/d) k(phi); 3 / d
+// is applied once per workgroup (k0_partials).
+template <int DIM, bool KVAR, int NP, typename TC>
+__device__ __forceinline__ TC gbar_scatter(const Coefs<TC> *__restrict__ cf, TC phi, const TC *P, TC *gk) {
+    const TC kv = KVAR ? poly<NP>(cf->kp, phi) : cf->kp[0];
     TC acc = TC(0);
 #pragma unroll
-    for (int i = 0; i < 6; ++i) acc += Gb[i] * cf->g0[i] * (i < 3 ? TC(1) : TC(2));
-    return acc * kd;
+    for (int i = 0; i < 6; ++i) {
+        if (DIM == 2 && i != 0 && i != 1 && i != 3) continue;
+        gk[i] += P[i] * kv;
+        if (KVAR) acc += P[i] * cf->g0[i];
+    }
+    return KVAR ? acc * poly<PolyLen<NP>::ND>(cf->kdp, phi) : TC(0);
+}
+
+// Reverse of the source of one time level, S = al R (M0 + 3 M1 . Bt) with the
+// moments M0 = sum w lam, M1 = sum w c lam, Bt = (I - A/2) B', at phi: returns
+// dS/dphi without the part through A and adds that part's dyad to P:
+//   dS/dphi = al R' (M0 + 3 M1 . Bt) + 3 al R M1 . (B'' - A B'' / 2 - A' B' / 2).
+template <int D, int NP, typename TC>
+__device__ __forceinline__ TC source_adjoint(const Coefs<TC> *__restrict__ cf, TC phi, const TC *A, TC al, TC M0,
+                                             const TC *M1, TC *P) {
+    TC Bp[3], AB[3], AM[3];
+#pragma unroll
+    for (int a = 0; a < D; ++a) Bp[a] = poly<PolyLen<NP>::ND>(cf->bp[a], phi);
+    sym_mul<D>(A, Bp, AB);
+    sym_mul<D>(A, M1, AM);
+    TC mb = TC(0), mq = TC(0);
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        mb += M1[a] * (Bp[a] - TC(0.5) * AB[a]);
+        mq += (M1[a] - TC(0.5) * AM[a]) * poly<PolyLen<NP>::ND2>(cf->bpp[a], phi);
+    }
+    const TC r3 = TC(3) * al * poly<NP>(cf->r, phi);
+#pragma unroll
+    for (int a = 0; a < D; ++a) AM[a] *= TC(0.5) * r3;
+    add_dyad<D>(AM, AB, P);
+    return (al * M0 + TC(3) * al * mb) * poly<PolyLen<NP>::ND>(cf->rp, phi) + r3 * mq;
 }
 
 // lambda_k(x) = psi_{s+1,k}(x + c_k): the transposed streaming of the pull
@@ -137,169 +161,144 @@ __device__ __forceinline__ void gather_adjoint_rw(const Geom &g, const TC *__res
 // kernels: from the gathered forward populations h (offset form), the history
 // pp_off = p_s(x), lam_k = psi_{s+1,k}(x + c_k) and pin = pi_{s+1}(x), writes
 // psi_s(x) to out and returns pi_s(x); adds this node's K0 terms to gk.
+// The two-sweep kernel holds few waves per SIMD and issues this arithmetic on
+// its critical path.  Sums and differences over opposite pairs and one dyad
+// per A (no 2 x 2 products) take 240 FP64 operations for a node with K(phi)
+// and the Scheme-A source, 343 before.
 template <int Q, typename TC, bool EQR, bool SRC, bool KVAR, int NP>
 __device__ __forceinline__ TC adjoint_node(const Coefs<TC> *__restrict__ cf, const TC *h, TC pp_off,
                                            const TC *lam, TC pin, TC *out, TC *gk) {
     using L = Lattice<Q>;
-    constexpr int D = L::dim;
-    TC phio = TC(0);
+    constexpr int D = L::dim, NPL = D * (D - 1) / 2, NPAIR = (Q - 1) / 2;
+    constexpr double w0 = L::w(0), w1 = L::w(1), w2 = L::w(Q - 1);
+    TC hs[NPAIR + 1];
+    hs[0] = h[0];
 #pragma unroll
-    for (int k = 0; k < Q; ++k) phio += h[k];
+    for (int i = 0; i < NPAIR; ++i) hs[i + 1] = h[L::pair(i)] + h[L::opp(L::pair(i))];
+    const TC phio = tree_sum<NPAIR + 1>(hs);
     const TC phi = cf->phi_ref + phio;
     TC A[6];
     ablock<D, KVAR, NP>(cf, phi, A);
 
-    TC Ab[3][3];
+    // Moments of lambda over the axis pairs (c = +-e_a) and the two diagonal
+    // pairs of each plane a < b (c = +-(e_a + e_b), +-(e_a - e_b)):
+    //   M0 = sum w lam, M1 = sum w c lam, L1 = sum c lam,
+    //   M2 = sum w c c lam (symmetric slots).
+    TC M0, L1[3], M1[3], M2[6];
+    {
+        TC sa = TC(0), sd = TC(0), dd[3] = {TC(0), TC(0), TC(0)};
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+        for (int a = 0; a < D; ++a) {
+            const int k = L::axis(a);
+            const TC e = lam[k] + lam[L::opp(k)];
+            M2[a] = TC(w1) * e;
+            sa += e;
+        }
 #pragma unroll
-        for (int b = 0; b < 3; ++b) Ab[a][b] = TC(0);
+        for (int i = 0; i < NPL; ++i) {
+            const int a = i == 1 ? 1 : 0, b = i == 0 ? 1 : 2;
+            const int kp = L::diag(i, 1), km = L::diag(i, -1);
+            const TC ep = lam[kp] + lam[L::opp(kp)], em = lam[km] + lam[L::opp(km)];
+            const TC op = lam[kp] - lam[L::opp(kp)], om = lam[km] - lam[L::opp(km)];
+            const TC e = ep + em;
+            sd += e;
+            M2[a] += TC(w2) * e;
+            M2[b] += TC(w2) * e;
+            M2[3 + i] = TC(w2) * (ep - em);
+            dd[a] += op + om;
+            dd[b] += op - om;
+        }
+        M0 = TC(w0) * lam[0] + (TC(w1) * sa + TC(w2) * sd);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            const int k = L::axis(a);
+            const TC o = lam[k] - lam[L::opp(k)];
+            L1[a] = o + dd[a];
+            M1[a] = TC(w1) * o + TC(w2) * dd[a];
+        }
+    }
+
+    TC P[6] = {TC(0), TC(0), TC(0), TC(0), TC(0), TC(0)};   // dyads of A(phi)
     TC phib = TC(0), pb = TC(0);
-    TC hb[Q];
+    if (SRC) {
+        // time level t: 3/2 R_k(phi); level t - 1: -1/2 R_k(p)
+        phib = source_adjoint<D, NP>(cf, phi, A, TC(1.5), M0, M1, P);
+        TC Ap[6], Pp[6] = {TC(0), TC(0), TC(0), TC(0), TC(0), TC(0)};
+        const TC pp = cf->phi_ref + pp_off;
+        ablock<D, KVAR, NP>(cf, pp, Ap);
+        pb = source_adjoint<D, NP>(cf, pp, Ap, TC(-0.5), M0, M1, Pp);
+        pb += gbar_scatter<D, KVAR, NP>(cf, pp, Pp, gk);
+    }
 
     if (EQR) {
-        // Forward (see sweep_node):
+        // Forward (see collide_node):
         //   out_k = (1 - s) g_k + w_k (s phio + Se + 9/2 s (E : c_k c_k - tr E / 3))
         //           + c_k . (w_k (3 s B + Vo) - v),  v = (A - s I)(j - B) / |c_a|^2,
-        //   Se = 3/2 R - 1/2 Rp, Vo = 9/2 R Bt - 3/2 Rp Btp, Bt = (I - A/2) B'.
-        // Its adjoint needs only moments of lambda:
-        //   L0w = sum w lam, L1 = sum c lam, L1w = sum w c lam, L2w = sum w c c lam.
+        // with the source terms above in Se and Vo.  u = (A - s I) L1 / |c|^2 is
+        // minus the adjoint of j and part of that of B; Abar = -L1 (j - B)^T / |c|^2.
         const TC s = cf->srate;
         constexpr TC inv_nc = TC(1.0 / L::jnorm);
-        TC L0w = TC(0), L1[3] = {TC(0), TC(0), TC(0)}, L1w[3] = {TC(0), TC(0), TC(0)};
-        TC L2w[6] = {TC(0), TC(0), TC(0), TC(0), TC(0), TC(0)};
-#pragma unroll
-        for (int k = 0; k < Q; ++k) {
-            const TC wl = TC(L::w(k)) * lam[k];
-            L0w += wl;
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                const int c = L::c(k, a);
-                if (c) { L1[a] += TC(c) * lam[k]; L1w[a] += TC(c) * wl; }
-            }
-#pragma unroll
-            for (int a = 0; a < D; ++a)
-#pragma unroll
-                for (int b = a; b < D; ++b) {
-                    const int cc = L::c(k, a) * L::c(k, b);
-                    if (cc) L2w[sym(a, b)] += TC(cc) * wl;
-                }
-        }
-        // forward pieces at phi
-        TC B[3], Bp[3], Bpp[3], jd[3];
+        TC u[3], jd[3], au[3], aj[3];
 #pragma unroll
         for (int a = 0; a < D; ++a) {
-            B[a] = poly<NP>(cf->b[a], phi);
-            Bp[a] = poly<PolyLen<NP>::ND>(cf->bp[a], phi);
-            Bpp[a] = poly<PolyLen<NP>::ND2>(cf->bpp[a], phi);
-            TC acc = TC(0);
+            const int k = L::axis(a);
+            TC acc = h[k] - h[L::opp(k)];
 #pragma unroll
-            for (int k = 0; k < Q; ++k) {
-                const int c = L::c(k, a);
-                if (c == 1) acc += h[k];
-                else if (c == -1) acc -= h[k];
+            for (int i = 0; i < NPL; ++i) {
+                const int p = i == 1 ? 1 : 0, q = i == 0 ? 1 : 2;
+                const int kp = L::diag(i, 1), km = L::diag(i, -1);
+                if (a == p) acc += (h[kp] - h[L::opp(kp)]) + (h[km] - h[L::opp(km)]);
+                if (a == q) acc += (h[kp] - h[L::opp(kp)]) - (h[km] - h[L::opp(km)]);
             }
-            jd[a] = acc - B[a];
+            jd[a] = acc - poly<NP>(cf->b[a], phi);
         }
-        // u = (A - s I) L1 / |c|^2: adjoint of j (with a minus) and of B
-        TC u[3];
+        sym_mul<D>(A, L1, au);
+        sym_mul<D>(A, jd, aj);
 #pragma unroll
         for (int a = 0; a < D; ++a) {
-            TC acc = TC(0);
+            au[a] *= inv_nc;
+            u[a] = au[a] - (s * inv_nc) * L1[a];
+        }
+        add_dyad<D>(au, aj, P);
+        // phio, B and E (dE_aa/dphi = Cbar'_aa - 1/3, weight 9/2 s (M2_aa - M0 / 3))
+        TC tr = TC(0), fb = TC(0);
 #pragma unroll
-            for (int b = 0; b < D; ++b) acc += (A[sym(a, b)] - (a == b ? s : TC(0))) * L1[b];
-            u[a] = acc * inv_nc;
+        for (int a = 0; a < D; ++a) {
+            const TC bp = poly<PolyLen<NP>::ND>(cf->bp[a], phi);
+            fb += (TC(3) * s * M1[a] + u[a]) * bp;
+            const TC cbd = poly<PolyLen<NP>::NCD>(cf->cbd[a], phi) - TC(1.0 / 3.0);
+            tr += (M2[a] - M0 * TC(1.0 / 3.0)) * cbd;
         }
 #pragma unroll
-        for (int a = 0; a < D; ++a)
+        for (int i = 0; i < NPL; ++i)
+            tr += TC(2) * M2[3 + i] * poly<PolyLen<NP>::NCD>(cf->cbd[3 + i], phi);
+        phib += s * (M0 + TC(4.5) * tr) + fb;
+        phib += gbar_scatter<D, KVAR, NP>(cf, phi, P, gk);
+        const TC oms = cf->oms, base = phib + pin;
+        out[0] = oms * lam[0] + base;
 #pragma unroll
-            for (int b = 0; b < D; ++b) Ab[a][b] -= L1[a] * jd[b] * inv_nc;
-        // phio, B, E
-        phib = s * L0w;
-#pragma unroll
-        for (int a = 0; a < D; ++a) phib += (TC(3) * s * L1w[a] + u[a]) * Bp[a];
-        {
-            const TC s45 = TC(4.5) * s;
-            TC tr = TC(0);
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                // dE_aa/dphi = Cbar'_aa - 1/3, weight 9/2 s (L2w_aa - L0w / 3)
-                const TC cbd = poly<PolyLen<NP>::NCD>(cf->cbd[a], phi) - TC(1.0 / 3.0);
-                tr += s45 * (L2w[a] - L0w * TC(1.0 / 3.0)) * cbd;
-            }
-#pragma unroll
-            for (int a = 0; a < D; ++a)
-#pragma unroll
-                for (int b = a + 1; b < D; ++b)
-                    tr += s45 * TC(2) * L2w[sym(a, b)] * poly<PolyLen<NP>::NCD>(cf->cbd[sym(a, b)], phi);
-            phib += tr;
+        for (int a = 0; a < D; ++a) {
+            const int k = L::axis(a);
+            out[k] = oms * lam[k] + (base - u[a]);
+            out[L::opp(k)] = oms * lam[L::opp(k)] + (base + u[a]);
         }
-        if (SRC) {
-            TC Bt[3], R, Btp[3], Rp, Ap[6];
-            source_terms<D, NP>(cf, phi, A, Bt, R);
-            const TC pp = cf->phi_ref + pp_off;
-            ablock<D, KVAR, NP>(cf, pp, Ap);
-            source_terms<D, NP>(cf, pp, Ap, Btp, Rp);
-            TC t1 = TC(0), t1p = TC(0);
 #pragma unroll
-            for (int a = 0; a < D; ++a) { t1 += L1w[a] * Bt[a]; t1p += L1w[a] * Btp[a]; }
-            const TC Rb = TC(1.5) * L0w + TC(4.5) * t1;
-            const TC Rpb = TC(-0.5) * L0w - TC(1.5) * t1p;
-            phib += Rb * poly<PolyLen<NP>::ND>(cf->rp, phi);
-            pb += Rpb * poly<PolyLen<NP>::ND>(cf->rp, pp);
-            TC Btb[3], Btpb[3], Bpq[3], Bppq[3];
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                Btb[a] = TC(4.5) * R * L1w[a];
-                Btpb[a] = TC(-1.5) * Rp * L1w[a];
-                Bpq[a] = poly<PolyLen<NP>::ND>(cf->bp[a], pp);
-                Bppq[a] = poly<PolyLen<NP>::ND2>(cf->bpp[a], pp);
-            }
-            TC Apb[3][3];
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 3; ++b) Apb[a][b] = TC(0);
-#pragma unroll
-            for (int b = 0; b < D; ++b) {
-                TC acc = Btb[b], accp = Btpb[b];
-#pragma unroll
-                for (int a = 0; a < D; ++a) {
-                    acc -= TC(0.5) * A[sym(a, b)] * Btb[a];
-                    accp -= TC(0.5) * Ap[sym(a, b)] * Btpb[a];
-                }
-                phib += acc * Bpp[b];
-                pb += accp * Bppq[b];
-            }
-#pragma unroll
-            for (int a = 0; a < D; ++a)
-#pragma unroll
-                for (int b = 0; b < D; ++b) {
-                    Ab[a][b] -= TC(0.5) * Btb[a] * Bp[b];
-                    Apb[a][b] -= TC(0.5) * Btpb[a] * Bpq[b];
-                }
-            TC Gbp[6];
-            gbar_of<D>(Ap, Apb, Gbp);
-            pb += gbar_scatter<D, KVAR, NP>(cf, pp, Gbp, gk);
-        }
-        const TC oms = TC(1) - s;
-#pragma unroll
-        for (int k = 0; k < Q; ++k) {
-            TC cu = TC(0);
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                const int c = L::c(k, a);
-                if (c) cu += TC(c) * u[a];
-            }
-            hb[k] = oms * lam[k] - cu;
+        for (int i = 0; i < NPL; ++i) {
+            const int a = i == 1 ? 1 : 0, b = i == 0 ? 1 : 2;
+            const int kp = L::diag(i, 1), km = L::diag(i, -1);
+            const TC up = u[a] + u[b], um = u[a] - u[b];
+            out[kp] = oms * lam[kp] + (base - up);
+            out[L::opp(kp)] = oms * lam[L::opp(kp)] + (base + up);
+            out[km] = oms * lam[km] + (base - um);
+            out[L::opp(km)] = oms * lam[L::opp(km)] + (base + um);
         }
     } else {
-        TC feq[Q], dlt[Q];
+        TC feq[Q], dlt[Q], hb[Q];
         equilibrium<Q, NP>(cf, phi, phio, feq);
 #pragma unroll
         for (int k = 0; k < Q; ++k) dlt[k] = h[k] - feq[k];
         // out = h - M^T N^-1 S M dlt: u = N^-1 M lambda, rbar = -u,
-        // mbar = S^T rbar, dbar = M^T mbar, Abar_ab += rbar_ja m_jb
+        // mbar = S^T rbar, dbar = M^T mbar, Abar_ab = rbar_ja m_jb
         TC m[Q], u[Q], db[Q];
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
@@ -312,20 +311,16 @@ __device__ __forceinline__ TC adjoint_node(const Coefs<TC> *__restrict__ cf, con
             m[i] = acc;
             u[i] = accl * TC(1.0 / L::N(i));
         }
-        TC mb[Q];
+        TC mb[Q], uj[3], mj[3], au[3], am[3];
+#pragma unroll
+        for (int a = 0; a < D; ++a) { uj[a] = u[L::jrow[a]]; mj[a] = m[L::jrow[a]]; }
+        sym_mul<D>(A, uj, au);
+        sym_mul<D>(A, mj, am);
 #pragma unroll
         for (int i = 0; i < Q; ++i) mb[i] = -cf->s[i] * u[i];
 #pragma unroll
-        for (int a = 0; a < D; ++a) {
-            TC acc = TC(0);
-#pragma unroll
-            for (int b = 0; b < D; ++b) acc -= A[sym(b, a)] * u[L::jrow[b]];
-            mb[L::jrow[a]] = acc;
-        }
-#pragma unroll
-        for (int a = 0; a < D; ++a)
-#pragma unroll
-            for (int b = 0; b < D; ++b) Ab[a][b] -= u[L::jrow[a]] * m[L::jrow[b]];
+        for (int a = 0; a < D; ++a) mb[L::jrow[a]] = -au[a];
+        add_dyad<D>(au, am, P);
 #pragma unroll
         for (int k = 0; k < Q; ++k) {
             TC acc = TC(0);
@@ -340,83 +335,14 @@ __device__ __forceinline__ TC adjoint_node(const Coefs<TC> *__restrict__ cf, con
         // dlt with a minus sign, and feq depends on phi only
 #pragma unroll
         for (int k = 0; k < Q; ++k) hb[k] = lam[k] + db[k];
-        {
-            TC dfe[Q];
-            eq_derivative<Q, NP>(cf, phi, dfe);
+        TC dfe[Q];
+        eq_derivative<Q, NP>(cf, phi, dfe);
 #pragma unroll
-            for (int k = 0; k < Q; ++k) phib -= db[k] * dfe[k];
-        }
-        if (SRC) {
-            TC Bt[3], R, Btp[3], Rp, Ap[6];
-            source_terms<D, NP>(cf, phi, A, Bt, R);
-            const TC pp = cf->phi_ref + pp_off;
-            ablock<D, KVAR, NP>(cf, pp, Ap);
-            source_terms<D, NP>(cf, pp, Ap, Btp, Rp);
-            TC S1 = TC(0), T1[3] = {TC(0), TC(0), TC(0)};
+        for (int k = 0; k < Q; ++k) phib -= db[k] * dfe[k];
+        phib += gbar_scatter<D, KVAR, NP>(cf, phi, P, gk);
 #pragma unroll
-            for (int k = 0; k < Q; ++k) {
-                const TC wl = TC(L::w(k)) * lam[k];
-                S1 += wl;
-#pragma unroll
-                for (int a = 0; a < D; ++a) {
-                    const int c = L::c(k, a);
-                    if (c) T1[a] += TC(c) * wl;
-                }
-            }
-            // time level t: + 3/2 R (S1 + 3 T1.Bt);  level t-1: - 1/2 Rp (S1 + 3 T1.Btp)
-            TC tb = TC(0), tbp = TC(0);
-#pragma unroll
-            for (int a = 0; a < D; ++a) { tb += T1[a] * Bt[a]; tbp += T1[a] * Btp[a]; }
-            const TC Rb = TC(1.5) * (S1 + TC(3) * tb);
-            const TC Rpb = TC(-0.5) * (S1 + TC(3) * tbp);
-            TC Btb[3], Btpb[3];
-#pragma unroll
-            for (int a = 0; a < D; ++a) { Btb[a] = TC(4.5) * R * T1[a]; Btpb[a] = TC(-1.5) * Rp * T1[a]; }
-            phib += Rb * poly<PolyLen<NP>::ND>(cf->rp, phi);
-            pb += Rpb * poly<PolyLen<NP>::ND>(cf->rp, pp);
-            TC Bp[3], Bpp[3], Bpq[3], Bppq[3];
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                Bp[a] = poly<PolyLen<NP>::ND>(cf->bp[a], phi);
-                Bpp[a] = poly<PolyLen<NP>::ND2>(cf->bpp[a], phi);
-                Bpq[a] = poly<PolyLen<NP>::ND>(cf->bp[a], pp);
-                Bppq[a] = poly<PolyLen<NP>::ND2>(cf->bpp[a], pp);
-            }
-            TC Apb[3][3];
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 3; ++b) Apb[a][b] = TC(0);
-#pragma unroll
-            for (int b = 0; b < D; ++b) {
-                TC acc = Btb[b], accp = Btpb[b];
-#pragma unroll
-                for (int a = 0; a < D; ++a) {
-                    acc -= TC(0.5) * A[sym(a, b)] * Btb[a];
-                    accp -= TC(0.5) * Ap[sym(a, b)] * Btpb[a];
-                }
-                phib += acc * Bpp[b];
-                pb += accp * Bppq[b];
-            }
-#pragma unroll
-            for (int a = 0; a < D; ++a)
-#pragma unroll
-                for (int b = 0; b < D; ++b) {
-                    Ab[a][b] -= TC(0.5) * Btb[a] * Bp[b];
-                    Apb[a][b] -= TC(0.5) * Btpb[a] * Bpq[b];
-                }
-            TC Gbp[6];
-            gbar_of<D>(Ap, Apb, Gbp);
-            pb += gbar_scatter<D, KVAR, NP>(cf, pp, Gbp, gk);
-        }
+        for (int k = 0; k < Q; ++k) out[k] = hb[k] + phib + pin;
     }
-    {
-        TC Gb[6];
-        gbar_of<D>(A, Ab, Gb);
-        phib += gbar_scatter<D, KVAR, NP>(cf, phi, Gb, gk);
-    }
-#pragma unroll
-    for (int k = 0; k < Q; ++k) out[k] = hb[k] + phib + pin;
     return pb;
 }
 
@@ -535,10 +461,16 @@ __device__ __forceinline__ constexpr int shared_rows_first(int j) {
 // registers), what their workgroup memory allows anyway (3 workgroups of 4
 // waves per CU); with 9-term polynomials that limit would spill.  10-row
 // tiles fit 2 workgroups per CU, and take no register limit.
+// Bound by memory on large grids (1024^2 FP64: 330 MB of states, psi and pi per
+// pair, 5 TB/s) and by a wave's chain of loads and arithmetic on small ones,
+// so each row's loads go ahead of the arithmetic of the one before.  us per
+// reversed sweep before the pair sums and the early loads -> after, with a
+// source: FP64 10 x 4 512^2 9.8 -> 9.1, 6 x 4 300^2 5.6 -> 4.7, 1024^2 35.2 ->
+// 33.5; FP32 10 x 12 512^2 5.5 -> 5.2, 6 x 4 400^2 4.8 -> 4.1.
 template <typename TS, typename TC, bool SRC, bool KVAR, int NP, int TH, int NW>
 __global__ void __launch_bounds__(NW * 64)
 __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 && NP <= 4 && TH == 6 ? 3 : 1, 8)))
-k_adjoint2(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ f1,
+k_adjoint2(const Geom g, const Coefs<TC> *__restrict__ cfa, const TS *__restrict__ f1,
            const typename HistType<TS>::T *__restrict__ p1, const TS *__restrict__ f0,
            const typename HistType<TS>::T *__restrict__ p0, const TC *__restrict__ psi_next,
            const double *__restrict__ pi_next, TC *__restrict__ psi_out, double *__restrict__ pi_out,
@@ -572,23 +504,43 @@ k_adjoint2(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict_
     w.colb[2] = (uint32_t)(xg == nx - 1 ? 0 : xg + 1) * (uint32_t)sizeof(TS);
     w.lo = w.hi = false;
     const uint32_t rowb = g.nx * (uint32_t)sizeof(TS);
-    // FP32 unrolls the rows (all loads in flight); FP64 takes them one by one
-    // (about 165 registers per lane as it is: 3 waves per SIMD)
-    constexpr int kUnroll = sizeof(TC) == 4 ? TR / NW : 1;
-#pragma unroll kUnroll
-    for (int i = 0; i < TR / NW; ++i) {
-        const int r = shared_rows_first<TR, NW>(wv + i * NW);
-        const int yg = wrap_coord(y0 - 1 + r, ny);
-        const uint32_t n = (uint32_t)yg * g.nx + (uint32_t)xg;
+    // The loads of a row: phase 1 (f_s, psi_{s+1} and their histories), phase 2
+    // (f_{s-1} and its history).
+    auto rows = [&](int y, uint32_t n) {
         w.n = n;
-        w.rowb[0] = (uint32_t)(yg == 0 ? ny - 1 : yg - 1) * rowb;
-        w.rowb[1] = (uint32_t)yg * rowb;
-        w.rowb[2] = (uint32_t)(yg == ny - 1 ? 0 : yg + 1) * rowb;
-        TC h[9], lam[9], out[9];
-        gather_rw<false, false>(g, cf, f1, w, h);
+        w.rowb[0] = (uint32_t)(y == 0 ? ny - 1 : y - 1) * rowb;
+        w.rowb[1] = (uint32_t)y * rowb;
+        w.rowb[2] = (uint32_t)(y == ny - 1 ? 0 : y + 1) * rowb;
+    };
+    auto load1 = [&](int i, TC *h, TC *lam, TC &pp, TC &pin) {
+        const int yg = wrap_coord(y0 - 1 + shared_rows_first<TR, NW>(wv + i * NW), ny);
+        rows(yg, (uint32_t)yg * g.nx + (uint32_t)xg);
+        gather_rw<false, false>(g, cfa, f1, w, h);
         gather_adjoint_rw<false, false>(g, psi_next, w, lam);
-        const TC pp_off = SRC ? (TC)*at<true>(p1, n) : TC(0);
-        const TC pin = (TC)*at<true>(pi_next, n);
+        pp = SRC ? (TC)*at<true>(p1, w.n) : TC(0);
+        pin = (TC)*at<true>(pi_next, w.n);
+    };
+    auto load2 = [&](int y, TC *h, TC &pp) {
+        rows(y, (uint32_t)y * g.nx + (uint32_t)xg);
+        gather_rw<false, false>(g, cfa, f0, w, h);
+        pp = SRC ? (TC)*at<true>(p0, w.n) : TC(0);
+    };
+    // Each row's loads are issued before the arithmetic of the row before it,
+    // phase 2's first ones before the barrier.  FP32 unrolls the rows, FP64
+    // takes them one by one (161 registers per lane with a source).
+    constexpr int NR = TR / NW;
+    TC hn[9], lamn[9], ppn, pinn;
+    load1(0, hn, lamn, ppn, pinn);
+    constexpr int kUnroll = sizeof(TC) == 4 ? NR : 1;
+#pragma unroll kUnroll
+    for (int i = 0; i < NR; ++i) {
+        TC h[9], lam[9], out[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) { h[k] = hn[k]; lam[k] = lamn[k]; }
+        const TC pp_off = ppn, pin = pinn;
+        if (i + 1 < NR) load1(i + 1, hn, lamn, ppn, pinn);
+        const int r = shared_rows_first<TR, NW>(wv + i * NW);
+        const Coefs<TC> *cf = cfa + opaque_zero();
         TC gkn[6] = {TC(0), TC(0), TC(0), TC(0), TC(0), TC(0)};
         const TC pb = adjoint_node<9, TC, true, SRC, KVAR, NP>(cf, h, pp_off, lam, pin, out, gkn);
         if (xown && r >= 1 && r <= TH && y0 + r - 1 < ny) {
@@ -599,29 +551,29 @@ k_adjoint2(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict_
         for (int k = 0; k < 9; ++k) lpsi[k][r][lane] = out[k];
         lpi[r][lane] = pb;
     }
-    __syncthreads();
     // phase 2: the tile's own nodes, psi_s gathered from x + c_k in the tile
-    if (xown) {
-        const uint32_t x = (uint32_t)(x0 + lane - 1);
-        for (int r = 1 + wv; r <= TH && y0 + r - 1 < ny; r += NW) {
-            const int y = y0 + r - 1;
-            const uint32_t n = (uint32_t)y * g.nx + x;
-            w.n = n;
-            w.rowb[0] = (uint32_t)(y == 0 ? ny - 1 : y - 1) * rowb;
-            w.rowb[1] = (uint32_t)y * rowb;
-            w.rowb[2] = (uint32_t)(y == ny - 1 ? 0 : y + 1) * rowb;
-            TC h[9], lam[9], out[9];
-            gather_rw<false, false>(g, cf, f0, w, h);
+    // (every lane's column and row below ny are in the grid: xg is wrapped)
+    const int rend = ny - y0 < TH ? ny - y0 : TH;
+    if (wv < rend) load2(y0 + wv, hn, ppn);
+    __syncthreads();
+    for (int r = 1 + wv; r <= rend; r += NW) {
+        TC h[9], lam[9], out[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) h[k] = hn[k];
+        const TC pp_off = ppn;
+        if (r + NW <= rend) load2(y0 + r + NW - 1, hn, ppn);
+        if (xown) {
+            const uint32_t n = (uint32_t)(y0 + r - 1) * g.nx + (uint32_t)xg;
+            const Coefs<TC> *cf = cfa + opaque_zero();
 #pragma unroll
             for (int k = 0; k < 9; ++k) lam[k] = lpsi[k][r + L::cy(k)][lane + L::cx(k)];
-            const TC pp_off = SRC ? (TC)*at<true>(p0, n) : TC(0);
             const TC pb = adjoint_node<9, TC, true, SRC, KVAR, NP>(cf, h, pp_off, lam, lpi[r][lane], out, gk);
             store_planes<9, false>(psi_out, g.plane, n, out);
             *at<true>(pi_out, n) = (double)pb;
         }
     }
     __syncthreads();   // the tile buffer becomes the reduction scratch
-    k0_partials<2, NW>(cf, gk, gk_part, blockIdx.x, reinterpret_cast<double(*)[NW]>(&lpsi[0][0][0]));
+    k0_partials<2, NW>(cfa, gk, gk_part, blockIdx.x, reinterpret_cast<double(*)[NW]>(&lpsi[0][0][0]));
 }
 
 // zero the per-workgroup K0 slots (a kernel, so that the adjoint can be

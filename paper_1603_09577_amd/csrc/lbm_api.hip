@@ -482,15 +482,14 @@ void prepare_zchunk(lbm_ctx *c) {
 // waves).  Its workgroups run in rounds of (resident workgroups per CU) x
 // CUs, and a partial last round costs a whole one.  10-row tiles recompute
 // fewer halo rows but fit fewer workgroups per CU; they win where they need
-// fewer rounds than 6-row tiles (512^2 FP64: 9.3 against 10.9 us per reversed
-// sweep; 768^2 FP32: 9.5 against 10.0), and 6-row tiles win at equal rounds
-// (1024^2 FP64: 34.7 against 36.8).  An FP32 launch too small to give every
+// fewer rounds than 6-row tiles (512^2 FP64: 9.1 against 10.4 us per reversed
+// sweep), and 6-row tiles win at equal rounds (1024^2 FP64: 33.5 against 34.6).  An FP32 launch too small to give every
 // SIMD several waves (at most 6 waves per SIMD with 12 per 10-row tile) runs
 // 10-row tiles with one row per wave when that at least halves the tiles
-// per CU (512^2: 2 against 4; 5.3 against 6.1 us); with as many tiles per CU
-// the 6-row tiles' smaller work per tile wins (384^2: 4.8 against 4.3 us).
+// per CU (512^2: 2 against 4; 5.2 against 6.0 us); with as many tiles per CU
+// the 6-row tiles' smaller work per tile wins (400^2: 4.6 against 4.1 us).
 // FP64, held to 2 or 3 waves per SIMD by its registers, gains nothing from
-// the extra waves (512^2: 10.3 against 9.3).
+// the extra waves with a source (512^2: 10.3 against 9.1).
 void pick_adj_shape(lbm_ctx *c) {
     query_cus(c);
     c->adj_shape = 0;

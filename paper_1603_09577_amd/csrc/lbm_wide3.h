@@ -30,16 +30,6 @@ __device__ __forceinline__ void wall_fix(const Coefs<TC> *__restrict__ cf, const
         if (Lattice<19>::cz(k) == CZ) h[k] = -own[k] + cf->ew[CZ == 1 ? 0 : 1][k];
 }
 
-// A scalar zero the compiler cannot see through, added to a table's address:
-// otherwise every coefficient and plane base is kept in scalar registers over
-// the loop, and what does not fit there is moved through lanes of vector
-// registers (FP64 with a source: 76 such moves per plane, now 46).
-__device__ __forceinline__ uint32_t opaque_zero() {
-    uint32_t z = 0;
-    asm volatile("" : "+s"(z));
-    return z;
-}
-
 template <typename TS, typename TC, bool KVAR, bool WALL, int NP, int TY, bool SB, bool SRC, bool EQ>
 __global__ void __launch_bounds__(64 * (TY + 3))
 k_sweep2_3dw(const Geom g, const Coefs<TC> *__restrict__ cfa, const TS *__restrict__ fin, TS *__restrict__ fout,
