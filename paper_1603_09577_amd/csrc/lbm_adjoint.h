@@ -82,7 +82,7 @@ __device__ __forceinline__ void add_dyad(const TC *au, const TC *av, TC *P) {
 // is applied once per workgroup (k0_partials).
 template <int DIM, bool KVAR, int NP, typename TC>
 __device__ __forceinline__ TC gbar_scatter(const Coefs<TC> *__restrict__ cf, TC phi, const TC *P, TC *gk) {
-    const TC kv = KVAR ? poly<NP>(cf->kp, phi) : cf->kp[0];
+    const TC kv = KVAR ? poly<NP, DIM == 2>(cf->kp, phi) : cf->kp[0];
     TC acc = TC(0);
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
@@ -90,7 +90,7 @@ __device__ __forceinline__ TC gbar_scatter(const Coefs<TC> *__restrict__ cf, TC 
         gk[i] += P[i] * kv;
         if (KVAR) acc += P[i] * cf->g0[i];
     }
-    return KVAR ? acc * poly<PolyLen<NP>::ND>(cf->kdp, phi) : TC(0);
+    return KVAR ? acc * poly<PolyLen<NP>::ND, DIM == 2>(cf->kdp, phi) : TC(0);
 }
 
 // Reverse of the source of one time level, S = al R (M0 + 3 M1 . Bt) with the
@@ -102,20 +102,20 @@ __device__ __forceinline__ TC source_adjoint(const Coefs<TC> *__restrict__ cf, T
                                              const TC *M1, TC *P) {
     TC Bp[3], AB[3], AM[3];
 #pragma unroll
-    for (int a = 0; a < D; ++a) Bp[a] = poly<PolyLen<NP>::ND>(cf->bp[a], phi);
+    for (int a = 0; a < D; ++a) Bp[a] = poly<PolyLen<NP>::ND, D == 2>(cf->bp[a], phi);
     sym_mul<D>(A, Bp, AB);
     sym_mul<D>(A, M1, AM);
     TC mb = TC(0), mq = TC(0);
 #pragma unroll
     for (int a = 0; a < D; ++a) {
         mb += M1[a] * (Bp[a] - TC(0.5) * AB[a]);
-        mq += (M1[a] - TC(0.5) * AM[a]) * poly<PolyLen<NP>::ND2>(cf->bpp[a], phi);
+        mq += (M1[a] - TC(0.5) * AM[a]) * poly<PolyLen<NP>::ND2, D == 2>(cf->bpp[a], phi);
     }
-    const TC r3 = TC(3) * al * poly<NP>(cf->r, phi);
+    const TC r3 = TC(3) * al * poly<NP, D == 2>(cf->r, phi);
 #pragma unroll
     for (int a = 0; a < D; ++a) AM[a] *= TC(0.5) * r3;
     add_dyad<D>(AM, AB, P);
-    return (al * M0 + TC(3) * al * mb) * poly<PolyLen<NP>::ND>(cf->rp, phi) + r3 * mq;
+    return (al * M0 + TC(3) * al * mb) * poly<PolyLen<NP>::ND, D == 2>(cf->rp, phi) + r3 * mq;
 }
 
 // lambda_k(x) = psi_{s+1,k}(x + c_k): the transposed streaming of the pull
@@ -250,7 +250,7 @@ __device__ __forceinline__ TC adjoint_node(const Coefs<TC> *__restrict__ cf, con
                 if (a == p) acc += (h[kp] - h[L::opp(kp)]) + (h[km] - h[L::opp(km)]);
                 if (a == q) acc += (h[kp] - h[L::opp(kp)]) - (h[km] - h[L::opp(km)]);
             }
-            jd[a] = acc - poly<NP>(cf->b[a], phi);
+            jd[a] = acc - poly<NP, D == 2>(cf->b[a], phi);
         }
         sym_mul<D>(A, L1, au);
         sym_mul<D>(A, jd, aj);
@@ -264,14 +264,14 @@ __device__ __forceinline__ TC adjoint_node(const Coefs<TC> *__restrict__ cf, con
         TC tr = TC(0), fb = TC(0);
 #pragma unroll
         for (int a = 0; a < D; ++a) {
-            const TC bp = poly<PolyLen<NP>::ND>(cf->bp[a], phi);
+            const TC bp = poly<PolyLen<NP>::ND, D == 2>(cf->bp[a], phi);
             fb += (TC(3) * s * M1[a] + u[a]) * bp;
-            const TC cbd = poly<PolyLen<NP>::NCD>(cf->cbd[a], phi) - TC(1.0 / 3.0);
+            const TC cbd = poly<PolyLen<NP>::NCD, D == 2>(cf->cbd[a], phi) - TC(1.0 / 3.0);
             tr += (M2[a] - M0 * TC(1.0 / 3.0)) * cbd;
         }
 #pragma unroll
         for (int i = 0; i < NPL; ++i)
-            tr += TC(2) * M2[3 + i] * poly<PolyLen<NP>::NCD>(cf->cbd[3 + i], phi);
+            tr += TC(2) * M2[3 + i] * poly<PolyLen<NP>::NCD, D == 2>(cf->cbd[3 + i], phi);
         phib += s * (M0 + TC(4.5) * tr) + fb;
         phib += gbar_scatter<D, KVAR, NP>(cf, phi, P, gk);
         const TC oms = cf->oms, base = phib + pin;

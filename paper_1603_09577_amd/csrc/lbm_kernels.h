@@ -93,14 +93,33 @@ __device__ __forceinline__ void store_planes(TS *__restrict__ base, uint64_t pla
     }
 }
 
+// a * x + c, one rounding, for a coefficient c that is the same in the whole
+// wave.  S, FP64: the instruction is spelled out.  The compiler picks the form
+// that overwrites its addend and copies each scalar coefficient to two vector
+// registers first: 34 copies per node of a D2Q9 pass with K(phi) and a source
+// among 116 FP64 operations, 16 left (us per step 512^2 3.63 -> 3.50, 1024^2
+// 12.30 -> 12.00).  Neither a nor x is the direct result of a transcendental
+// instruction, nor is the result a DPP operand, so no wait state is due.
+template <bool S>
+__device__ __forceinline__ float mul_add(float a, float x, float c) { return a * x + c; }
+template <bool S>
+__device__ __forceinline__ double mul_add(double a, double x, double c) {
+    if (!S) return a * x + c;
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(x), "s"(c));
+    return r;
+}
+
 // sum_{p < N} c[p] x^p by Horner over a compile-time length: no branches;
 // the host picks the short length whenever every polynomial fits in it (the
 // coefficients beyond a polynomial's degree are zero).
-template <int N, typename T>
+// S: the spelled-out step, for D2Q9; D3Q19 kernels are short of registers, and
+// with it FP64 two-step passes with a source spilled (128^3 98.6 -> 149 us).
+template <int N, bool S = false, typename T>
 __device__ __forceinline__ T poly(const T *c, T x) {
     T acc = c[N - 1];
 #pragma unroll
-    for (int p = N - 2; p >= 0; --p) acc = acc * x + c[p];
+    for (int p = N - 2; p >= 0; --p) acc = mul_add<S && N <= 6>(acc, x, c[p]);
     return acc;
 }
 
@@ -119,18 +138,18 @@ struct PolyLen {
 // cf->nq > 0) is evaluated only by the 9-term kernels, which the host selects
 // for it; the shorter kernels evaluate the polynomial P_a alone.  B' by the
 // quotient rule, (P'_a - B_a Q') / Q.
-template <int NP, typename TC>
+template <int NP, bool S = false, typename TC>
 __device__ __forceinline__ TC flux_b(const Coefs<TC> *__restrict__ cf, int a, TC phi) {
-    const TC num = poly<NP>(cf->b[a], phi);
+    const TC num = poly<NP, S>(cf->b[a], phi);
     if constexpr (NP == kMaxP) {
         if (cf->nq) return num / poly<NP>(cf->bq, phi);
     }
     return num;
 }
 
-template <int NP, typename TC>
+template <int NP, bool S = false, typename TC>
 __device__ __forceinline__ TC flux_bp(const Coefs<TC> *__restrict__ cf, int a, TC phi) {
-    const TC dnum = poly<PolyLen<NP>::ND>(cf->bp[a], phi);
+    const TC dnum = poly<PolyLen<NP>::ND, S>(cf->bp[a], phi);
     if constexpr (NP == kMaxP) {
         if (cf->nq) {
             const TC q = poly<NP>(cf->bq, phi);
@@ -184,7 +203,7 @@ __device__ __forceinline__ void sym_inverse(const T *G, T *A, T scale = T(1)) {
 template <int DIM, bool KVAR, int NP, typename TC>
 __device__ __forceinline__ void ablock(const Coefs<TC> *__restrict__ cf, TC phi, TC *A) {
     if (KVAR) {
-        const TC kv = poly<NP>(cf->kp, phi);
+        const TC kv = poly<NP, DIM == 2>(cf->kp, phi);
         TC G[6];
 #pragma unroll
         for (int i = 0; i < 6; ++i) G[i] = cf->g0[i] * kv + (i < 3 ? TC(0.5) : TC(0));
@@ -253,7 +272,7 @@ __device__ __forceinline__ void equilibrium(const Coefs<TC> *__restrict__ cf, TC
 template <int DIM, bool KVAR, int NP, typename TC>
 __device__ __forceinline__ void ablock_half(const Coefs<TC> *__restrict__ cf, TC phi, TC *Ah) {
     if (KVAR) {
-        const TC kv = poly<NP>(cf->kp, phi);
+        const TC kv = poly<NP, DIM == 2>(cf->kp, phi);
         TC G[6];
 #pragma unroll
         for (int i = 0; i < 6; ++i) G[i] = cf->g0[i] * kv + (i < 3 ? TC(0.5) : TC(0));
@@ -266,7 +285,7 @@ __device__ __forceinline__ void ablock_half(const Coefs<TC> *__restrict__ cf, TC
 
 template <int DIM, int NP, typename TC>
 __device__ __forceinline__ void ablock_half_field(const Coefs<TC> *__restrict__ cf, const TC *g0n, TC phi, TC *Ah) {
-    const TC kv = poly<NP>(cf->kp, phi);
+    const TC kv = poly<NP, DIM == 2>(cf->kp, phi);
     TC G[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) G[i] = g0n[i] * kv + (i < 3 ? TC(0.5) : TC(0));
@@ -442,8 +461,8 @@ __device__ __forceinline__ SrcLevel<TC> src_level(const Coefs<TC> *__restrict__ 
     SrcLevel<TC> lv;
     TC Bp[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) Bp[a] = (a < D) ? flux_bp<NP>(cf, a, phi) : TC(0);
-    lv.Rh = poly<NP>(cf->rh, phi);
+    for (int a = 0; a < 3; ++a) Bp[a] = (a < D) ? flux_bp<NP, D == 2>(cf, a, phi) : TC(0);
+    lv.Rh = poly<NP, D == 2>(cf->rh, phi);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         TC acc = Bp[a];
@@ -528,7 +547,7 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
     TC B[3], j[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        B[a] = (a < D) ? flux_b<NP>(cf, a, phi) : TC(0);
+        B[a] = (a < D) ? flux_b<NP, D == 2>(cf, a, phi) : TC(0);
         j[a] = TC(0);
 #pragma unroll
         for (int i = 0; i < P; ++i) {
@@ -556,7 +575,7 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
         const TC pp = cf->phi_ref + pp_off;
         TC dB[3] = {TC(0), TC(0), TC(0)};
 #pragma unroll
-        for (int a = 0; a < D; ++a) dB[a] = B[a] - flux_b<NP>(cf, a, pp);
+        for (int a = 0; a < D; ++a) dB[a] = B[a] - flux_b<NP, D == 2>(cf, a, pp);
 #pragma unroll
         for (int a = 0; a < D; ++a) {
             TC acc = dB[a];
@@ -595,7 +614,7 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
             Rs = (TC(1) - sh) * Rx;
 #pragma unroll
             for (int a = 0; a < D; ++a) {
-                const TC bp = flux_bp<NP>(cf, a, phi);
+                const TC bp = flux_bp<NP, D == 2>(cf, a, phi);
                 V[a] += Rs * bp;
                 j[a] += TC(0.5) * Rx * bp;
             }
@@ -618,11 +637,11 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
         TC ea[D], es[NPL], eo[NPL];
         if constexpr (NC <= 6) {
 #pragma unroll
-            for (int a = 0; a < D; ++a) ea[a] = poly<NC>(cf->ce[a], phi);
+            for (int a = 0; a < D; ++a) ea[a] = poly<NC, D == 2>(cf->ce[a], phi);
 #pragma unroll
             for (int i = 0; i < NPL; ++i) {
-                es[i] = poly<NC>(cf->ce[3 + i], phi);
-                eo[i] = poly<NC>(cf->ce[6 + i], phi);
+                es[i] = poly<NC, D == 2>(cf->ce[3 + i], phi);
+                eo[i] = poly<NC, D == 2>(cf->ce[6 + i], phi);
             }
         } else {
             // long polynomials: one Horner chain per tensor entry costs less
@@ -678,8 +697,8 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
         // uses the same pairs.  No 9 x 9 transform of g, feq and r: about 110
         // operations instead of 230 for a node without a source.
         const TC ax = hs[1] + hs[2], di = hs[3] + hs[4];   // axis and diagonal pairs
-        const TC Et = poly<PolyLen<NP>::NC>(cf->cm[0], phi), Ed = poly<PolyLen<NP>::NC>(cf->cm[1], phi),
-                 Ex = poly<PolyLen<NP>::NC>(cf->cm[2], phi);
+        const TC Et = poly<PolyLen<NP>::NC, true>(cf->cm[0], phi), Ed = poly<PolyLen<NP>::NC, true>(cf->cm[1], phi),
+                 Ex = poly<PolyLen<NP>::NC, true>(cf->cm[2], phi);
         const TC me = (TC(2) * di - TC(4) * h[0] - ax) - (Et - TC(2) * phio);
         const TC mp = (TC(4) * h[0] - TC(2) * ax + di) - (phio - Et);
         TC re = cf->sn[1] * me, rp = cf->sn[2] * mp;
@@ -705,7 +724,7 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
             rp -= Rx * (TC(1.0 / 36.0) - TC(0.5) * cf->sn[2]);
             r0 = TC(-1.0 / 9.0) * Rx;
 #pragma unroll
-            for (int a = 0; a < 2; ++a) jn[a] = Rx * flux_bp<NP>(cf, a, phi);
+            for (int a = 0; a < 2; ++a) jn[a] = Rx * flux_bp<NP, D == 2>(cf, a, phi);
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
                 rj[a] -= TC(1.0 / 6.0) * (jn[a] - (Ah[a] * jn[a] + Ah[3] * jn[1 - a]));
@@ -761,7 +780,7 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
             // r -= (I - S/2) M R_k, R_k = w_k R (1 + 3 c_k . B') (Eq. 9, Btilde = B')
             TC Bp[3] = {TC(0), TC(0), TC(0)};
 #pragma unroll
-            for (int a = 0; a < D; ++a) Bp[a] = flux_bp<NP>(cf, a, phi);
+            for (int a = 0; a < D; ++a) Bp[a] = flux_bp<NP, D == 2>(cf, a, phi);
             TC Rk[Q], mR[Q], sR[Q];
 #pragma unroll
             for (int k = 0; k < Q; ++k) {
