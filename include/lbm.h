@@ -290,7 +290,8 @@ int lbm_two_step_shape(const lbm_ctx *ctx, int shape, int *rows, int *waves);
  * Remark III.
  * mode: -1 on in the library's pick, 0 off, k >= 1 on in shape k - 1.
  * lbm_multi_step_shape: steps per pass, tile rows and waves per workgroup of a
- * shape (the D2Q9 tile is 66 - 2 steps nodes wide).
+ * shape (the D2Q9 tile is 66 - 2 steps nodes wide, 34 - 2 steps in shapes 5
+ * to 7).
  * Errors: LBM_E_UNSUPPORTED / LBM_E_INVALID / LBM_E_STATE as lbm_set_two_step. */
 int lbm_multi_step_shape(const lbm_ctx *ctx, int shape, int *steps, int *rows, int *waves);
 int lbm_set_multi_step(lbm_ctx *ctx, int mode);

@@ -511,39 +511,54 @@ void pick_adj_shape(lbm_ctx *c) {
     c->adj_shape_auto = c->adj_shape;
 }
 
+// Workgroups of a D2Q9 pass of several steps in shape `shape`.
+uint64_t multi_tiles(const lbm_ctx *c, int shape) {
+    int t = 2, tr = 4, nw = 0, tx = 64;
+    multi_shape_of(c->dm.prec, shape, &t, &tr, &nw, &tx);
+    const uint32_t tw = (uint32_t)(tx - 2 * (t - 1)), th = (uint32_t)(tr - 2 * (t - 1));
+    return (uint64_t)((c->g.nx + tw - 1) / tw) * ((c->g.ny + th - 1) / th);
+}
+
 // Shape of the D2Q9 passes of several steps.  A pass costs one launch (1.6 us
 // between dependent launches, plus the first loads and the last stores), one
 // collision per step on the chain of its waves, and the halo: T - 1 nodes on
-// each side of a 64 x TR region.
+// each side of a region of 64 x TR or 32 x TR nodes.
 //  - While the grid gives every CU at most one workgroup, nothing else runs on
-//    that CU and the halo is free: the pass of the most steps that still fits
-//    one round wins, with one row per wave (us per step, FP32 with source /
-//    FP64 without: 64^2 T = 8 0.99 / 1.11, 6 1.15 / 1.33, 4 1.47 / 1.86, two
-//    steps per pass 2.46 / 2.38; 256^2 T = 8, three rounds, 2.03 / 2.97, 6
-//    1.24 / 1.49, 4 1.52 / 1.85; 320^2 T = 6, two rounds, 1.72 / 2.49, 4 1.59 /
-//    1.92).
+//    that CU and the halo is free; a step costs about 0.9 us with the four rows
+//    per SIMD of a 64 x 16 region and 0.5 us with half of them (FP64).  So the
+//    32-wide region with the most steps that still fits one round wins: us per
+//    step, FP64 without / FP32 with a source, 64^2 32-wide T = 8 0.89 / 0.82, 6
+//    1.03 / 0.93, 64-wide T = 8 1.14 / 1.01; 128^2 32-wide T = 8, two rounds,
+//    1.24 / 1.03, 6 1.07 / 0.95, 64-wide 8 1.21 / 1.04; FP64 200^2 32-wide 4
+//    1.40, 64-wide 6 1.44.
+//  - FP32 and FP16 gain less from the shorter steps, and their second and third
+//    32-wide workgroup on a CU costs less: six steps up to two of them (200^2
+//    1.19, one 64 x 16 region with six steps 1.21), and up to three rather than
+//    four steps in 64 x 16 (300^2 1.53 against 1.62).
+//  - Then 64 x 16 with six, then with four steps in one round (256^2 1.26 / 1.76
+//    against 1.46 / 2.09 32-wide with four).
 //  - Then the tall region with six steps (512^2 FP32 2.18 against 2.43 for four
-//    steps in 16 rows, FP64 3.42 against 4.08), or with four where that fits
+//    steps in 16 rows, FP64 3.35 against 3.92), or with four where that fits
 //    one round of resident workgroups and six steps do not (1000 x 723 FP32
 //    with walls 5.14 against 5.65).
 //  - Beyond one round the halo work counts: FP32 and FP16 keep six steps in the
 //    tall region (2048^2 FP32 20.4 against 24.1 for four and 22.6 for four in
 //    16 rows), FP64, whose tall region leaves one workgroup per CU, takes four
-//    steps in 16 rows (1024^2 12.5 against 13.0).
+//    steps in 16 rows (1024^2 12.0 against 12.6).
 int pick_multi(lbm_ctx *c) {
     query_cus(c);
     const uint64_t ncu = c->ncu > 0 ? (uint64_t)c->ncu : 256;
-    auto tiles = [&](int shape) {
-        int t = 2, tr = 0, nw = 0;
-        multi_shape_of(c->dm.prec, shape, &t, &tr, &nw);
-        const uint64_t tw = 64 - 2 * (t - 1), th = (uint64_t)(tr - 2 * (t - 1));
-        return ((c->g.nx + tw - 1) / tw) * ((c->g.ny + th - 1) / th);
-    };
-    for (int shape = 0; shape < 3; ++shape)
-        if (tiles(shape) <= ncu) return shape;
+    auto fits = [&](int shape, uint64_t per_cu) { return multi_tiles(c, shape) <= per_cu * ncu; };
     const bool f64 = c->dm.prec == 0;
-    if (tiles(3) <= (f64 ? ncu : 2 * ncu)) return 3;
-    if (tiles(4) <= 2 * ncu) return 4;
+    if (fits(5, 1)) return 5;
+    if (fits(6, f64 ? 1 : 2)) return 6;
+    if (fits(0, 1)) return 0;
+    if (f64 && fits(7, 1)) return 7;
+    if (fits(1, 1)) return 1;
+    if (!f64 && fits(6, 3)) return 6;
+    if (fits(2, 1)) return 2;
+    if (fits(3, f64 ? 1 : 2)) return 3;
+    if (fits(4, 2)) return 4;
     return f64 ? 4 : 3;
 }
 
@@ -604,14 +619,15 @@ hipError_t launch_pass_q9(lbm_ctx *c, int steps, const void *fin, void *fout, co
     const Dims d = eff_dims(c);
     if (steps == 2)
         return launch_sweep2_q9(d, c->g, c->d_coefs, fin, fout, pin, pout, c->d_flag, c->two_shape, st);
-    int t = 0, tr = 0, nw = 0, main_tr = 0;
-    multi_shape_of(c->dm.prec, c->multi_shape, &t, &main_tr, &nw);
+    int t = 0, tr = 0, nw = 0, tx = 0, main_tr = 0, main_tx = 0;
+    multi_shape_of(c->dm.prec, c->multi_shape, &t, &main_tr, &nw, &main_tx);
     int shape = c->multi_shape;
     if (t != steps) {
         // a shorter pass of a remainder: the rows of the main pass where a
-        // shape of that length has them, else the last shape of the length
-        for (int i = 0; multi_shape_of(c->dm.prec, i, &t, &tr, &nw); ++i)
-            if (t == steps) {
+        // shape of that length and width has them, else the last shape of the
+        // length and width
+        for (int i = 0; multi_shape_of(c->dm.prec, i, &t, &tr, &nw, &tx); ++i)
+            if (t == steps && tx == main_tx) {
                 shape = i;
                 if (tr == main_tr) break;
             }
@@ -1152,7 +1168,7 @@ int lbm_sweep_record(lbm_ctx *c, const void *f_in, const void *p_in, void *f_out
         if (passes && left >= 4) n = (left == 4 || left == 5 || left == 8 || left == 9) ? 4 : 6;
         hipError_t e = n == 1 ? sweep(c, fi, fo, pi, po, st)
                               : launch_sweep_record_q9(d, g, c->d_coefs, fi, fo, f_step, pi, po, p_step, c->d_flag, n,
-                                                       c->multi_shape >= 3, st);
+                                                       c->multi_shape == 3 || c->multi_shape == 4, st);
         if (e != hipSuccess) return hip_fail(e, "recorded sweep kernel");
         fo += (size_t)n * f_step;
         po += (size_t)n * p_step;
@@ -1521,9 +1537,10 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
             const int i = ri / remaps;
             const int shape = i == 0 ? c->multi_auto : (i <= c->multi_auto ? i - 1 : i);
             multi_shape(c, shape, &mt, &mtr, &mnw);
-            const uint64_t tiles = (uint64_t)((c->g.nx + 65 - 2 * mt) / (66 - 2 * mt)) *
-                                   ((c->g.ny + (uint32_t)(mtr - 2 * mt + 1)) / (uint32_t)(mtr - 2 * mt + 2));
-            if (c->dm.q == 9 && shape < 3 && tiles > 4ull * (uint64_t)(c->ncu > 0 ? c->ncu : 256)) continue;
+            if (c->dm.q == 9 && shape != 3 && shape != 4 &&
+                multi_tiles(c, shape) > (shape < 3 ? 4ull : 8ull) * (uint64_t)(c->ncu > 0 ? c->ncu : 256))
+                continue;
+            const int width = c->dm.q == 9 && shape >= 5 ? 34 - 2 * mt : (c->dm.q == 9 ? 66 - 2 * mt : 64);
             c->multi_shape = shape;
             c->multi_remap = (remaps == 2 && ri % remaps == 0) ? 1 : 0;
             const int pair_reps = std::max(2, reps * 2 / mt);
@@ -1544,8 +1561,8 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
                 if (t < 0.f || ms < t) t = ms;
             }
             char line[112];
-            std::snprintf(line, sizeof(line), "%d steps per pass rows %d waves %d remap %d: %.4f ms per step\n", mt,
-                          mtr - 2 * mt + 2, mnw, c->multi_remap, t);
+            std::snprintf(line, sizeof(line), "%d steps per pass %d x %d nodes waves %d remap %d: %.4f ms per step\n",
+                          mt, width, mtr - 2 * mt + 2, mnw, c->multi_remap, t);
             rep += line;
             if (t < 0.98f * best_ms) {
                 best_ms = t;

@@ -168,11 +168,19 @@ hipError_t launch_sweep_multi_q9_f32(const Dims &dm, const Geom &g, const void *
                                      const void *pin, void *pout, int *flag, int shape, hipStream_t st);
 hipError_t launch_sweep_multi_q9_f16(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
                                      const void *pin, void *pout, int *flag, int shape, hipStream_t st);
-inline bool multi_shape_of(int prec, int shape, int *steps, int *rows, int *waves) {
+inline bool multi_shape_of(int prec, int shape, int *steps, int *rows, int *waves, int *width = nullptr) {
     constexpr int t[3][5][3] = {{{8, 16, 16}, {6, 16, 16}, {4, 16, 16}, {6, 32, 16}, {4, 16, 8}},     // FP64
                                 {{8, 16, 16}, {6, 16, 16}, {4, 16, 16}, {6, 32, 16}, {4, 32, 16}},    // FP32
                                 {{8, 16, 16}, {6, 16, 16}, {4, 16, 16}, {6, 48, 16}, {4, 32, 16}}};   // FP16
-    if (prec < 0 || prec > 2 || shape < 0 || shape >= 5) return false;
+    constexpr int half[3] = {8, 6, 4};   // steps of the 32-wide shapes, 16 rows on 8 waves
+    if (prec < 0 || prec > 2 || shape < 0 || shape >= 8) return false;
+    if (width) *width = shape < 5 ? 64 : 32;
+    if (shape >= 5) {
+        *steps = half[shape - 5];
+        *rows = 16;
+        *waves = 8;
+        return true;
+    }
     *steps = t[prec][shape][0];
     *rows = t[prec][shape][1];
     *waves = t[prec][shape][2];

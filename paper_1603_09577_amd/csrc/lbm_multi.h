@@ -1,8 +1,9 @@
 // T time steps per pass for D2Q9 (T even; 3-term polynomials): the state
 // crosses memory once per T steps and a pass costs one launch.
 //
-// A workgroup owns a tile of (64 - 2H) x (TR - 2H) nodes, H = T - 1, and keeps
-// a region of 64 x TR nodes, the tile and H nodes around it, in LDS.  Step 0
+// A workgroup owns a tile of (TX - 2H) x (TR - 2H) nodes, H = T - 1, and keeps
+// a region of TX x TR nodes (TX = 64: a row per wave, or 32: two rows), the tile
+// and H nodes around it, in LDS.  Step 0
 // gathers the region from the stored state; step s runs on the rows and
 // columns at least s inside the region, so that after T steps the tile is
 // complete, and the last step stores it.  Every node update is the
@@ -29,8 +30,8 @@
 // six steps the bytes per step fall to a third and what is left is vector
 // issue (about 110 operations per node and step, 1.45 times that with the
 // halo) and the barriers.  us per step before -> after, FP32 with K(phi) and a
-// source unless noted: 64^2 FP64 unequal rates 2.41 -> 1.11; 256^2 3.5 -> 1.24;
-// 1024^2 8.0 -> 5.9, FP64 14.3 -> 12.5; 1000 x 723 channel with unequal rates
+// source unless noted: 64^2 FP64 unequal rates 2.41 -> 1.14, 32-wide 0.89;
+// 256^2 3.5 -> 1.24; 1024^2 8.0 -> 5.9, FP64 14.3 -> 12.0; 1000 x 723 channel with unequal rates
 // 7.9 -> 5.1; 2048^2 44 -> 20.4, FP64 80 -> 51; 4000 x 2500 FP16 54 -> 44.5.
 //
 // A Scheme-A run reads phi(t - 1) of the region from pin, hands each node's
@@ -47,7 +48,7 @@ namespace lbm {
 // its history at pout + s pstep (elements): a run that needs all states (the
 // adjoint's recomputation) then reads one state per pass instead of one per step.
 template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, bool EQ,
-          bool REC = false>
+          bool REC = false, int TX = 64>
 __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> *__restrict__ cf,
                                                  const TS *__restrict__ fin, TS *__restrict__ fout,
                                                  const typename HistType<TS>::T *__restrict__ pin,
@@ -55,12 +56,20 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
                                                  uint32_t ty, int *flag, uint64_t fstep = 0, uint64_t pstep = 0) {
     using L = Lattice<9>;
     using TP = typename HistType<TS>::T;
-    static_assert(T % 2 == 0 && TR % NW == 0 && std::is_same<TP, TC>::value, "even passes, whole rows per wave");
-    constexpr int H = T - 1, TX = 64, TH = TR - 2 * H, NR = TR / NW;
-    __shared__ TS raw[TR * 9 * TX + 2];
-    const int lane = threadIdx.x & 63;
+    constexpr bool HALF = TX == 32;   // two region rows per wave
+    constexpr int H = T - 1, TH = TR - 2 * H, NR = TR / NW / (HALF ? 2 : 1), PAD = HALF ? 1 : 0;
+    static_assert(T % 2 == 0 && NR * NW * (HALF ? 2 : 1) == TR && std::is_same<TP, TC>::value, "whole rows per wave");
+    __shared__ TS raw[(TR + 2 * PAD) * 9 * TX + 2];
+    const int lane = threadIdx.x & (TX - 1);               // column of the region
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    TS *const cell = raw + 1 + lane;                       // slot k of region row r: cell[(r * 9 + k) * TX]
+    TS *const cell = raw + 1 + lane + PAD * 9 * TX;        // slot k of region row r: cell[(r * 9 + k) * TX]
+    // Row i of this wave: r0 = wv + i NW, in half-width regions the upper half
+    // of the wave takes TR - 1 - r0, so that both halves leave the shrinking
+    // region at the same step.
+    auto row_of = [&](int r0) {
+        if constexpr (HALF) return (threadIdx.x & 32) ? TR - 1 - r0 : r0;
+        else return r0;
+    };
     const int nx = (int)g.nx, ny = (int)g.ny;
     const int x0 = (int)(tx * (TX - 2 * H)), y0 = (int)(ty * TH);
     const int xg = wrap_coord(x0 - H + lane, nx);
@@ -79,7 +88,7 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
     // step 0: scalar row base plus one of three column offsets per load
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-        const int r = wv + i * NW, yl = y0 - H + r;
+        const int r = row_of(wv + i * NW), yl = y0 - H + r;
         if (WALL && (yl < 0 || yl >= ny)) continue;        // beyond a wall
         const int yg = WALL ? yl : wrap_coord(yl, ny);
         const int ym = yg == 0 ? ny - 1 : yg - 1, yp = yg == ny - 1 ? 0 : yg + 1;
@@ -90,7 +99,9 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
             const bool wl = WALL && ((cy == 1 && yg == 0) || (cy == -1 && yg == ny - 1));
             const uint32_t row = (uint32_t)(wl ? yg : (cy == 1 ? ym : (cy == -1 ? yp : yg)));
             const TS *pl = fin + (uint64_t)(wl ? L::opp(k) : k) * g.plane;
-            const TC v = (TC)*row_elem(pl, row * row_bytes, cb[wl ? 1 : 1 - L::cx(k)]);
+            const TC v = HALF ? (TC)*reinterpret_cast<const TS *>(reinterpret_cast<const char *>(pl) +
+                                                                  (row * row_bytes + cb[wl ? 1 : 1 - L::cx(k)]))
+                              : (TC)*row_elem(pl, row * row_bytes, cb[wl ? 1 : 1 - L::cx(k)]);
             h[k] = wl ? -v + cf->ew[cy == 1 ? 0 : 1][k] : v;
         }
         const TC pp = SRC ? (TC)*at<true>(pin, (uint32_t)yg * g.nx + (uint32_t)xg) : TC(0);
@@ -102,7 +113,7 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
             const int cy = L::cy(k), cx = L::cx(k);
             const bool wl = WALL && ((cy == -1 && yg == 0) || (cy == 1 && yg == ny - 1));
             if (wl) cell[(r * 9 + L::opp(k)) * TX] = to_store<TS>(out[k]);
-            else if (r + cy >= 0 && r + cy < TR) cell[((r + cy) * 9 + k) * TX + cx] = to_store<TS>(out[k]);
+            else if (HALF || (r + cy >= 0 && r + cy < TR)) cell[((r + cy) * 9 + k) * TX + cx] = to_store<TS>(out[k]);
         }
     }
     // Steps 1 .. T - 2 in pairs (odd, even), then the last, odd one.  The pair
@@ -112,8 +123,8 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
         constexpr bool ODD = decltype(odd)::value, LAST = decltype(last)::value;
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
-            const int r = wv + i * NW, yl = y0 - H + r;
-            if (r < s || r >= TR - s || (WALL && (yl < 0 || yl >= ny))) continue;
+            const int r0 = wv + i * NW, r = row_of(r0), yl = y0 - H + r;
+            if (r0 < s || (!HALF && r0 >= TR - s) || (WALL && (yl < 0 || yl >= ny))) continue;
             TC h[9], out[9];
 #pragma unroll
             for (int k = 0; k < 9; ++k) {
@@ -158,14 +169,15 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
 // FP32 arithmetic with at most two rows per wave fits 64 vector registers, so
 // that LDS decides the waves per CU; the attribute keeps the scalar registers
 // within 8 waves per SIMD too (one more would cost a whole workgroup).
-template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, bool EQ>
+template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, bool EQ, int TX>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 4 ? 8 : 1, 8)))
 k_sweep_multi(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin, TS *__restrict__ fout,
               const typename HistType<TS>::T *__restrict__ pin, typename HistType<TS>::T *__restrict__ pout,
               uint32_t tiles_x, int *flag) {
     const uint32_t tile = block_index(blockIdx.x, gridDim.x, g.remap);
     const uint32_t ty = tile / tiles_x, tx = tile - ty * tiles_x;
-    sweep_multi_tile<TS, TC, SRC, KVAR, T, TR, NW, SB, WALL, EQ>(g, cf, fin, fout, pin, pout, tx, ty, flag);
+    sweep_multi_tile<TS, TC, SRC, KVAR, T, TR, NW, SB, WALL, EQ, false, TX>(g, cf, fin, fout, pin, pout, tx, ty,
+                                                                                    flag);
 }
 
 template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool WALL>

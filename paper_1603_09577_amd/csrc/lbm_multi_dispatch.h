@@ -6,18 +6,18 @@
 
 namespace lbm {
 
-template <typename TS, typename TC, int T, int TR, int NW>
+template <typename TS, typename TC, int T, int TR, int NW, int TX = 64>
 hipError_t multi_shape(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout, const void *pin,
                        void *pout, int *flag, hipStream_t st) {
     using TP = typename HistType<TS>::T;
-    constexpr uint32_t TW = 64 - 2 * (T - 1), TH = TR - 2 * (T - 1);
+    constexpr uint32_t TW = TX - 2 * (T - 1), TH = TR - 2 * (T - 1);
     const uint32_t tiles_x = (g.nx + TW - 1) / TW, tiles_y = (g.ny + TH - 1) / TH;
     const dim3 grid(tiles_x * tiles_y), block(64 * NW);
     // source: none, Scheme A (history pin -> pout) or Scheme B (no history)
     const int code = (dm.sb ? 2 : (dm.src ? 1 : 0)) * 8 + (dm.kvar ? 4 : 0) + (dm.wall ? 2 : 0) + (dm.eqr ? 1 : 0);
 #define LBM_MULTI(S, K, W, E)                                                                             \
     case (S * 8 + K * 4 + W * 2 + E):                                                                     \
-        hipLaunchKernelGGL((k_sweep_multi<TS, TC, S == 1, K, T, TR, NW, S == 2, W, E>), grid, block, 0, st, g, \
+        hipLaunchKernelGGL((k_sweep_multi<TS, TC, S == 1, K, T, TR, NW, S == 2, W, E, TX>), grid, block, 0, st, g, \
                            (const Coefs<TC> *)coefs, (const TS *)fin, (TS *)fout, (const TP *)pin, (TP *)pout, \
                            tiles_x, flag);                                                                \
         break;
@@ -42,6 +42,9 @@ hipError_t multi_typed(const Dims &dm, const Geom &g, const void *coefs, const v
         case 2: return multi_shape<TS, TC, 4, 16, 16>(dm, g, coefs, fin, fout, pin, pout, flag, st);
         case 3: return multi_shape<TS, TC, 6, R3, 16>(dm, g, coefs, fin, fout, pin, pout, flag, st);
         case 4: return multi_shape<TS, TC, 4, R4, N4>(dm, g, coefs, fin, fout, pin, pout, flag, st);
+        case 5: return multi_shape<TS, TC, 8, 16, 8, 32>(dm, g, coefs, fin, fout, pin, pout, flag, st);
+        case 6: return multi_shape<TS, TC, 6, 16, 8, 32>(dm, g, coefs, fin, fout, pin, pout, flag, st);
+        case 7: return multi_shape<TS, TC, 4, 16, 8, 32>(dm, g, coefs, fin, fout, pin, pout, flag, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -50,7 +50,7 @@ def _compare(spec, set_pass, steps=STEPS):
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
-@pytest.mark.parametrize("shape", range(5))
+@pytest.mark.parametrize("shape", range(8))
 @pytest.mark.parametrize("nx,ny,source,wall,rates", [
     (100, 37, "A", False, "equal"), (59, 31, "A", True, "unequal"), (131, 70, "none", False, "unequal"),
     (54, 22, "B", True, "equal"), (3, 2, "A", False, "equal"), (1, 5, "B", False, "unequal"), (66, 1, "A", True, "equal"),
@@ -59,7 +59,8 @@ def test_every_shape_bit_identical(prec, shape, nx, ny, source, wall, rates):
     _compare(_spec(nx, ny, prec, source, wall, rates), lambda s: s.set_multi_step(True, shape))
 
 
-@pytest.mark.parametrize("nx,ny,prec", [(64, 64, "f64"), (250, 250, "f32"), (300, 310, "f64"), (500, 500, "f32"),
+@pytest.mark.parametrize("nx,ny,prec", [(64, 64, "f64"), (130, 120, "f64"), (200, 200, "f64"), (120, 90, "f32"),
+                                         (190, 200, "f16"), (300, 300, "f32"), (250, 250, "f32"), (300, 310, "f64"), (500, 500, "f32"),
                                          (1000, 723, "f32"), (1100, 1200, "f16"), (1100, 1200, "f64")])
 def test_default_pass_bit_identical(nx, ny, prec):
     """The shape each grid gets by default (one workgroup per CU, one round,
@@ -72,9 +73,9 @@ def test_linear_constant_tensor_and_calls():
     from paper_1603_09577_amd import lbm
     _compare(_spec(70, 40, "f64", source="none", rates="unequal", linear=True), lambda s: s.set_multi_step(True))
     s = lbm.Lbm(_spec(64, 64, "f32"))
-    assert [t[0] for t in s.multi_step_shapes()] == [8, 6, 4, 6, 4]
+    assert [t[0] for t in s.multi_step_shapes()] == [8, 6, 4, 6, 4, 8, 6, 4]
     with pytest.raises(lbm.LbmError) as e:
-        s.set_multi_step(True, 5)
+        s.set_multi_step(True, 8)
     assert e.value.code == lbm.LBM_E_INVALID
     spec3, _, _ = W.d3q19_walls((8, 8, 8))
     spec3 = dict(spec3, s=[0.0, 1.3] + [1.0] * 17)
