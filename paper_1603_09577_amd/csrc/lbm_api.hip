@@ -366,6 +366,7 @@ int validate(const lbm_desc *d, Dims &dm) {
     dm.q = q;
     dm.prec = d->precision;
     dm.eqr = eq && !(d->flags & LBM_FLAG_MOMENT_PATH);
+    dm.unit = dm.eqr && d->s[1] == 1.0;
     dm.src = src;
     dm.kvar = kvar;
     dm.wall = wall;

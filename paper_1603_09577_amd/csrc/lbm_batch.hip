@@ -109,7 +109,7 @@ k_batch_sweep2(const BatchInst *__restrict__ inst, const Coefs<TC> *__restrict__
 }
 
 // T time steps per launch, one workgroup per entry (instance, tx | ty << 16).
-template <typename TS, typename TC, bool KVAR, int T, int TR, int NW>
+template <typename TS, typename TC, bool KVAR, int T, int TR, int NW, int EQ>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 4 ? 8 : 1, 8)))
 k_batch_multi(const BatchInst *__restrict__ inst, const Coefs<TC> *__restrict__ coefs,
               const uint2 *__restrict__ tiles, int remap, const TS *__restrict__ fin, TS *__restrict__ fout,
@@ -117,7 +117,7 @@ k_batch_multi(const BatchInst *__restrict__ inst, const Coefs<TC> *__restrict__ 
     const uint2 e = tiles[block_index(blockIdx.x, gridDim.x, remap)];
     const BatchInst &I = inst[e.x];
     const Geom g = I.g;
-    sweep_multi_tile<TS, TC, false, KVAR, T, TR, NW, false, false, true>(g, coefs + e.x, fin + I.f_off,
+    sweep_multi_tile<TS, TC, false, KVAR, T, TR, NW, false, false, EQ>(g, coefs + e.x, fin + I.f_off,
                                                                         fout + I.f_off, nullptr, nullptr,
                                                                         e.y & 0xffffu, e.y >> 16, flag);
 }
@@ -194,6 +194,7 @@ struct lbm_batch {
     int count = 0;
     int prec = 0;
     bool src = false, kvar = false, lowdeg = true, deg3 = true;
+    bool unit = true;   // all non-flux rates of all instances 1
     size_t coef_stride = 0;
     std::vector<BatchInst> inst;
     std::vector<int> nx, ny;
@@ -281,16 +282,19 @@ hipError_t batch_pass_launch(lbm_batch *b, const void *fin, void *fout, hipStrea
     hipLaunchKernelGGL((k_batch_sweep2<TS, TC, K, TH, NW>), grid, dim3(64 * NW), 0, st, b->d_inst,      \
                        (const Coefs<TC> *)b->d_coefs, tl, b->remap, (const TS *)fin, (TS *)fout, b->d_flag)
 #define LBM_BM(TS, TC, K, T, TR, NW)                                                                    \
-    hipLaunchKernelGGL((k_batch_multi<TS, TC, K, T, TR, NW>), grid, dim3(64 * NW), 0, st, b->d_inst,    \
+    if (b->unit) LBM_BME(TS, TC, K, T, TR, NW, 2);                                                      \
+    else LBM_BME(TS, TC, K, T, TR, NW, 1)
+#define LBM_BME(TS, TC, K, T, TR, NW, E)                                                                \
+    hipLaunchKernelGGL((k_batch_multi<TS, TC, K, T, TR, NW, E>), grid, dim3(64 * NW), 0, st, b->d_inst,    \
                        (const Coefs<TC> *)b->d_coefs, tl, b->remap, (const TS *)fin, (TS *)fout, b->d_flag)
 #define LBM_B4(TS, TC, K)                                                                               \
-    if (sh.steps == 6) LBM_BM(TS, TC, K, 6, 32, 16);                                                    \
-    else if (sh.steps == 4) LBM_BM(TS, TC, K, 4, 16, 8);                                                \
+    if (sh.steps == 6) { LBM_BM(TS, TC, K, 6, 32, 16); }                                                \
+    else if (sh.steps == 4) { LBM_BM(TS, TC, K, 4, 16, 8); }                                            \
     else if (sh.rows == 14) LBM_B2(TS, TC, K, 14, 8);                                                   \
     else LBM_B2(TS, TC, K, 6, 4);
 #define LBM_B8(K)                                                                                       \
-    if (sh.steps == 6) LBM_BM(double, double, K, 6, 32, 16);                                            \
-    else if (sh.steps == 4) LBM_BM(double, double, K, 4, 16, 8);                                        \
+    if (sh.steps == 6) { LBM_BM(double, double, K, 6, 32, 16); }                                        \
+    else if (sh.steps == 4) { LBM_BM(double, double, K, 4, 16, 8); }                                    \
     else LBM_B2(double, double, K, 6, 8);
     if (b->prec == 0) {
         if (b->kvar) { LBM_B8(true) } else { LBM_B8(false) }
@@ -302,6 +306,7 @@ hipError_t batch_pass_launch(lbm_batch *b, const void *fin, void *fout, hipStrea
 #undef LBM_B8
 #undef LBM_B4
 #undef LBM_BM
+#undef LBM_BME
 #undef LBM_B2
     return hipGetLastError();
 }
@@ -467,6 +472,7 @@ int lbm_batch_create(const lbm_desc *descs, int count, lbm_batch **out) {
         b->kvar = b->kvar || kvar;
         b->lowdeg = b->lowdeg && low;
         b->deg3 = b->deg3 && d3;
+        b->unit = b->unit && d.s[1] == 1.0;
         coefs.insert(coefs.end(), tmp.begin(), tmp.begin() + cb);
         BatchInst I;
         std::memset(&I, 0, sizeof(I));

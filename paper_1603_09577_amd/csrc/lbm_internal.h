@@ -90,6 +90,7 @@ struct Dims {
     bool o32 = false;     // every indexed array spans < 4 GiB: 32-bit byte offsets (the 3-term and two-step kernels)
     bool nt;              // non-temporal distribution accesses
     bool sb;              // Scheme B (Eq. 33-35): stored fbar, explicit source
+    bool unit = false;    // all non-flux rates 1 (the passes of several steps have kernels for it)
     bool rat = false;     // rational B (Remark III): the 9-term kernels evaluate P / Q
 };
 

@@ -516,7 +516,9 @@ __device__ __forceinline__ T tree_sum(const T *v) {
 // pp_off.  A caller that passes the terms of the same node one step later
 // gets the values the rebuild would give (the same function of the same phi)
 // without its arithmetic.
-template <int Q, typename TC, bool EQR, bool SRC, bool KVAR, int NP, bool SB = false, bool KF = false>
+// EQR: 0 unequal rates (moment space), 1 all non-flux rates equal, 2 all equal to
+// 1 (the populations enter only through their moments; the same bits as 1).
+template <int Q, typename TC, int EQR, bool SRC, bool KVAR, int NP, bool SB = false, bool KF = false>
 __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, const TC *h, TC pp_off, uint32_t n,
                                            const double *kfield, const double *rfield, bool rem3, TC *out,
                                            SrcLevel<TC> *cur = nullptr, const SrcLevel<TC> *prev = nullptr) {
@@ -601,11 +603,14 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
         // part is 3 w1 c_k . d on the axes and 3 w1 c_k . q on the diagonals,
         // d = T - v / (3 w1), q = d - (1 - w2 / w1) T: the factor 3 w1 goes
         // into the last multiply-add of each population.
+        // With s = 1 the first term is gone.
         // Bound by vector issue on large grids: 105 instead of 131 operations
         // of a D2Q9 node with K(phi) and the Scheme-A source before the factors
         // moved to the host.
         constexpr double w1 = L::w(1), w2 = L::w(Q - 1), kj = 1.0 / (L::jnorm * 1.5 * w1);
-        const TC s = cf->srate, sh = cf->shalf, oms = cf->oms;
+        constexpr bool ONE = EQR == 2;
+        const TC s = ONE ? TC(1) : cf->srate, sh = ONE ? TC(0.5) : cf->shalf;
+        auto relax = [&](TC hk, TC even) { return ONE ? even : cf->oms * hk + even; };   // (1 - s) h + even
         TC T[3], d[3], q[3], ju[3];
         TC Rs = Se;                      // even source part: Scheme A Se, Scheme B (1 - s/2) R
         if (SB) {
@@ -671,8 +676,8 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
             // the axis pair (c = e_a, -e_a)
             const int k = L::axis(a), kb = L::opp(k);
             const TC even = ea[a] + wb1;
-            out[k] = TC(3.0 * w1) * d[a] + (oms * h[k] + even);
-            out[kb] = TC(-3.0 * w1) * d[a] + (oms * h[kb] + even);
+            out[k] = TC(3.0 * w1) * d[a] + relax(h[k], even);
+            out[kb] = TC(-3.0 * w1) * d[a] + relax(h[kb], even);
         }
 #pragma unroll
         for (int i = 0; i < D * (D - 1) / 2; ++i) {
@@ -682,10 +687,10 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
             const int kp = L::diag(i, 1), km = L::diag(i, -1);   // c = e_a + e_b, e_a - e_b
             const TC op = q[a] + q[b], om = q[a] - q[b];
             const TC ep = e0 + eo[i], em = e0 - eo[i];
-            out[kp] = TC(3.0 * w1) * op + (oms * h[kp] + ep);
-            out[L::opp(kp)] = TC(-3.0 * w1) * op + (oms * h[L::opp(kp)] + ep);
-            out[km] = TC(3.0 * w1) * om + (oms * h[km] + em);
-            out[L::opp(km)] = TC(-3.0 * w1) * om + (oms * h[L::opp(km)] + em);
+            out[kp] = TC(3.0 * w1) * op + relax(h[kp], ep);
+            out[L::opp(kp)] = TC(-3.0 * w1) * op + relax(h[L::opp(kp)], ep);
+            out[km] = TC(3.0 * w1) * om + relax(h[km], em);
+            out[L::opp(km)] = TC(-3.0 * w1) * om + relax(h[L::opp(km)], em);
         }
     } else if constexpr (Q == 9) {
         // Unequal rates: S acts on the moments of Eq. 15.  The even moments

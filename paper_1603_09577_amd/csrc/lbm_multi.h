@@ -47,7 +47,7 @@ namespace lbm {
 // REC: every step's state of the tile is stored, step s at fout + s fstep and
 // its history at pout + s pstep (elements): a run that needs all states (the
 // adjoint's recomputation) then reads one state per pass instead of one per step.
-template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, bool EQ,
+template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, int EQ,
           bool REC = false, int TX = 64>
 __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> *__restrict__ cf,
                                                  const TS *__restrict__ fin, TS *__restrict__ fout,
@@ -169,7 +169,7 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
 // FP32 arithmetic with at most two rows per wave fits 64 vector registers, so
 // that LDS decides the waves per CU; the attribute keeps the scalar registers
 // within 8 waves per SIMD too (one more would cost a whole workgroup).
-template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, bool EQ, int TX>
+template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool SB, bool WALL, int EQ, int TX>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 4 ? 8 : 1, 8)))
 k_sweep_multi(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin, TS *__restrict__ fout,
               const typename HistType<TS>::T *__restrict__ pin, typename HistType<TS>::T *__restrict__ pout,
@@ -180,14 +180,14 @@ k_sweep_multi(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restri
                                                                                     flag);
 }
 
-template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool WALL>
+template <typename TS, typename TC, bool SRC, bool KVAR, int T, int TR, int NW, bool WALL, int EQ>
 __global__ void __launch_bounds__(64 * NW)
 k_sweep_record(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin, TS *__restrict__ fout,
                uint64_t fstep, const typename HistType<TS>::T *__restrict__ pin,
                typename HistType<TS>::T *__restrict__ pout, uint64_t pstep, uint32_t tiles_x, int *flag) {
     const uint32_t tile = block_index(blockIdx.x, gridDim.x, g.remap);
     const uint32_t ty = tile / tiles_x, tx = tile - ty * tiles_x;
-    sweep_multi_tile<TS, TC, SRC, KVAR, T, TR, NW, false, WALL, true, true>(g, cf, fin, fout, pin, pout, tx, ty, flag,
+    sweep_multi_tile<TS, TC, SRC, KVAR, T, TR, NW, false, WALL, EQ, true>(g, cf, fin, fout, pin, pout, tx, ty, flag,
                                                                            fstep, pstep);
 }
 

@@ -30,7 +30,7 @@ __device__ __forceinline__ void wall_fix(const Coefs<TC> *__restrict__ cf, const
         if (Lattice<19>::cz(k) == CZ) h[k] = -own[k] + cf->ew[CZ == 1 ? 0 : 1][k];
 }
 
-template <typename TS, typename TC, bool KVAR, bool WALL, int NP, int TY, bool SB, bool SRC, bool EQ>
+template <typename TS, typename TC, bool KVAR, bool WALL, int NP, int TY, bool SB, bool SRC, int EQ>
 __global__ void __launch_bounds__(64 * (TY + 3))
 k_sweep2_3dw(const Geom g, const Coefs<TC> *__restrict__ cfa, const TS *__restrict__ fin, TS *__restrict__ fout,
              const typename HistType<TS>::T *__restrict__ pin, typename HistType<TS>::T *__restrict__ pout,

@@ -12,19 +12,21 @@ hipError_t record_shape(const Dims &dm, const Geom &g, const void *coefs, const 
     constexpr uint32_t TW = 64 - 2 * (T - 1), TH = TR - 2 * (T - 1);
     const uint32_t tiles_x = (g.nx + TW - 1) / TW, tiles_y = (g.ny + TH - 1) / TH;
     const dim3 grid(tiles_x * tiles_y), block(64 * NW);
-    const int code = (dm.src ? 4 : 0) + (dm.kvar ? 2 : 0) + (dm.wall ? 1 : 0);
-#define LBM_REC(S, K, W)                                                                                  \
-    case (S * 4 + K * 2 + W):                                                                             \
-        hipLaunchKernelGGL((k_sweep_record<TS, TC, S, K, T, TR, NW, W>), grid, block, 0, st, g,           \
+    const int code = (dm.unit ? 8 : 0) + (dm.src ? 4 : 0) + (dm.kvar ? 2 : 0) + (dm.wall ? 1 : 0);
+#define LBM_RECE(S, K, W, E)                                                                                \
+    case ((E == 2 ? 8 : 0) + S * 4 + K * 2 + W):                                                                           \
+        hipLaunchKernelGGL((k_sweep_record<TS, TC, S, K, T, TR, NW, W, E>), grid, block, 0, st, g,           \
                            (const Coefs<TC> *)coefs, (const TS *)fin, (TS *)fout, (uint64_t)(f_step / sizeof(TS)), \
                            (const TP *)pin, (TP *)pout, (uint64_t)(p_step / sizeof(TP)), tiles_x, flag);  \
         break;
+#define LBM_REC(S, K, W) LBM_RECE(S, K, W, 1) LBM_RECE(S, K, W, 2)
     switch (code) {
         LBM_REC(0, 0, 0) LBM_REC(0, 0, 1) LBM_REC(0, 1, 0) LBM_REC(0, 1, 1)
         LBM_REC(1, 0, 0) LBM_REC(1, 0, 1) LBM_REC(1, 1, 0) LBM_REC(1, 1, 1)
         default: return hipErrorInvalidValue;
     }
 #undef LBM_REC
+#undef LBM_RECE
     return hipGetLastError();
 }
 

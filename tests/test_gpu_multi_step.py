@@ -25,6 +25,8 @@ def _spec(nx, ny, prec, source="A", wall=False, rates="equal", linear=False):
         spec = dict(spec, bc=["periodic", "abb", "periodic"], phi_wall=[[0.0, 0.0], [0.3, 0.7], [0.0, 0.0]])
     if rates == "unequal":
         spec = dict(spec, s=UNEQUAL)
+    elif rates == "1.3":                     # equal, but not 1
+        spec = dict(spec, s=[0.0] + [1.3] * 8)
     return spec
 
 
@@ -54,7 +56,7 @@ def _compare(spec, set_pass, steps=STEPS):
 @pytest.mark.parametrize("nx,ny,source,wall,rates", [
     (100, 37, "A", False, "equal"), (59, 31, "A", True, "unequal"), (131, 70, "none", False, "unequal"),
     (54, 22, "B", True, "equal"), (3, 2, "A", False, "equal"), (1, 5, "B", False, "unequal"), (66, 1, "A", True, "equal"),
-    (50, 45, "none", True, "equal")])
+    (50, 45, "none", True, "equal"), (70, 40, "A", True, "1.3"), (70, 40, "B", False, "1.3")])
 def test_every_shape_bit_identical(prec, shape, nx, ny, source, wall, rates):
     _compare(_spec(nx, ny, prec, source, wall, rates), lambda s: s.set_multi_step(True, shape))
 
@@ -108,15 +110,16 @@ def test_divergence_check_with_passes(every):
     assert e.value.code == lbm.LBM_E_DIVERGED
 
 
+@pytest.mark.parametrize("rates", ["equal", "1.3"])
 @pytest.mark.parametrize("prec,shape", [("f32", 6), ("f32", 7), ("f16", 6), ("f16", 7), ("f64", 5), ("f64", 6)])
-def test_batch_passes_identical(prec, shape):
+def test_batch_passes_identical(prec, shape, rates):
     """Uneven instances (narrower and lower than a tile among them) in passes
     of several steps, forced and by default, against the instances alone."""
     import torch
 
     from paper_1603_09577_amd import lbm
     sizes = [(100, 37), (3, 2), (54, 22), (131, 70), (33, 200)]
-    specs = [_spec(nx, ny, prec, source="none") for nx, ny in sizes]
+    specs = [_spec(nx, ny, prec, source="none", rates=rates) for nx, ny in sizes]
     phi0 = [W.noise_field((ny, nx), 5 + i) for i, (nx, ny) in enumerate(sizes)]
     b = lbm.Batch(specs).init(phi0)
     assert b.get_shape()["npt"] < 0
@@ -139,7 +142,8 @@ def test_batch_passes_identical(prec, shape):
     ((64, 13, 9), "f32", True, "none"), ((128, 20, 22), "f64", True, "A"), ((65, 27, 11), "f32", False, "A"),
     ((63, 7, 5), "f16", True, "A"), ((3, 2, 2), "f32", True, "none"), ((1, 1, 3), "f64", False, "B"),
     ((130, 37, 21), "f32", True, "B"), ((64, 6, 1), "f64", True, "A"), ((70, 14, 1), "f16", False, "none")])
-def test_d3q19_lines_bit_identical(n, prec, wall, source):
+@pytest.mark.parametrize("rate", [1.0, 1.3])
+def test_d3q19_lines_bit_identical(n, prec, wall, source, rate):
     """D3Q19, two steps per pass in columns of 64-node lines with a halo wave:
     grids of whole and partial lines, lower and narrower than a column, one
     plane between walls, every source."""
@@ -151,7 +155,7 @@ def test_d3q19_lines_bit_identical(n, prec, wall, source):
         spec = dict(spec, rpoly=[], kpoly=[1.0])
     elif source == "B":
         spec = dict(spec, scheme="B")
-    spec = dict(spec, bc=["periodic", "periodic", "abb" if wall else "periodic"],
+    spec = dict(spec, s=[0.0] + [rate] * 18, bc=["periodic", "periodic", "abb" if wall else "periodic"],
                 phi_wall=[[0, 0], [0, 0], [0.3, 0.6]] if wall else [[0, 0]] * 3)
     phi0 = W.noise_field(n[::-1], 7, mean=0.4, amp=0.2)
     a = lbm.Lbm(spec).init(phi0)
@@ -175,7 +179,8 @@ def test_d3q19_lines_bit_identical(n, prec, wall, source):
     (59, 31, "f32", "A", False, "equal", 9), (700, 300, "f32", "none", True, "equal", 10),
     (3, 2, "f64", "none", False, "equal", 5), (1, 5, "f32", "A", True, "equal", 4), (600, 605, "f64", "A", True, "equal", 6),
     (1100, 1000, "f32", "A", False, "equal", 11), (40, 30, "f64", "B", False, "equal", 6),
-    (40, 30, "f64", "A", False, "unequal", 6), (64, 40, "f16", "A", False, "equal", 6)])
+    (40, 30, "f64", "A", False, "unequal", 6), (64, 40, "f16", "A", False, "equal", 6),
+    (90, 60, "f64", "A", True, "1.3", 7)])
 def test_recorded_states_bit_identical(nx, ny, prec, source, wall, rates, n):
     """Every recorded state and history against single sweeps; what lies
     beyond a state in its row stays as it was."""
