@@ -563,20 +563,22 @@ int pick_multi(lbm_ctx *c) {
     return f64 ? 4 : 3;
 }
 
-// D3Q19: single sweeps, two-step passes in 62-node columns or in 64-node lines
-// (us per step, single / 62 / 64, 256^3 FP32 450 / 318 / 277, FP64 with a source
-// 934 / 784 / 719; 128^3 60 / 51.5 / 41.3 and 122 / 127 / 100; 96^3 23.5 / 19.6 /
-// 18.9 and 58 / 44.4 / 46).
-//  - Below about 67^3 nodes a pass has too few columns for the chip, and a
-//    column marches through its planes one after the other: single sweeps
-//    (64^3 FP32 9.2 / 12.5 / 9.2, FP64 with a source 16.0 / 22.9 / 17.0).
-//  - FP64 takes 62-node columns where lines do not save one of them (200 x 180
-//    x 160 216 / 231, with a source 248 / 278): its nine waves per workgroup
-//    put three on one SIMD.
+// D3Q19: single sweeps or two-step passes in 64-node lines (which beat 62-node
+// columns at every size: us per step 62 / 64, FP64 with a source 96^3 47.2 /
+// 41.6, 200 x 180 x 160 271 / 258, 256^3 813 / 672; FP32 256^3 462 / 291).  A pass
+// has one workgroup per column and chunk of planes, a wave computes 64 nodes
+// whether the grid has them or not, and both planes of the halo are extra: it
+// wins once enough nodes share that, more of them the emptier the lines are.
+// With f the filled part of the lines, N f^2 separates the two: us per step
+// single / lines, FP64 with a source and walls, 56^3 (134k) 12.7 / 14.2, 72^3
+// (118k) 23.2 / 26.4, 60^3 (190k) 15.2 / 14.8, 80^3 (200k) 29.5 / 28.8, 60 x 100^2
+// (527k) 32.9 / 26.8; FP32 64^3 (262k) 9.9 / 10.9, 100 x 60^2 (220k) 12.1 / 13.5,
+// 128 x 64 x 40 (327k) 11.3 / 11.5, 60 x 100^2 18.4 / 16.4; FP16 10.5 / 10.8 and
+// 16.4 / 15.0 for the last two.
 void pick_lines(lbm_ctx *c) {
     if (!c->multi_ok) return;
-    if (c->g.N < 300000u) c->two = c->multi = false;
-    else if (c->dm.prec == 0 && (c->g.nx + 63) / 64 == (c->g.nx + 61) / 62) c->multi = false;
+    const double f = (double)c->g.nx / (64.0 * ((c->g.nx + 63) / 64));
+    if (c->g.N * f * f < (c->dm.prec == 0 ? 190e3 : 350e3)) c->two = c->multi = false;
 }
 
 // z planes per column of the D3Q19 pass.  Each workgroup lives for its chunk
