@@ -284,9 +284,8 @@ int lbm_two_step_shape(const lbm_ctx *ctx, int shape, int *rows, int *waves);
  * in pairs (their lengths may differ), so state and history end where single
  * sweeps leave them; the last one to three steps of a call use single sweeps.
  * On by default where it applies, in a shape picked for the grid, and
- * launched directly (no graphs); small D3Q19 grids start with single sweeps
- * (N f^2 below 190000 in FP64, 350000 in FP32 and FP16, f the filled part of the
- * 64-node lines).  lbm_tune times
+ * launched directly (no graphs); small D3Q19 grids start with single sweeps,
+ * and where lines save no column mostly with lbm_set_two_step's.  lbm_tune times
  * the shapes; lbm_set_two_step turns it off.  Not used with per-node fields or
  * Remark III.
  * mode: -1 on in the library's pick, 0 off, k >= 1 on in shape k - 1.

@@ -70,6 +70,7 @@ struct lbm_ctx {
     bool multi_ok = false, multi = false;
     int multi_shape = 0, multi_auto = 0;
     int multi_remap = 1;
+    int two_remap = 1;        // workgroup order of D3Q19 two-step passes in 62-node columns
     // lbm_step replays captured graphs of kGraphSteps sweeps (lbm_tune may
     // find direct launches faster)
     bool use_graphs = true;
@@ -563,22 +564,32 @@ int pick_multi(lbm_ctx *c) {
     return f64 ? 4 : 3;
 }
 
-// D3Q19: single sweeps or two-step passes in 64-node lines (which beat 62-node
-// columns at every size: us per step 62 / 64, FP64 with a source 96^3 47.2 /
-// 41.6, 200 x 180 x 160 271 / 258, 256^3 813 / 672; FP32 256^3 462 / 291).  A pass
-// has one workgroup per column and chunk of planes, a wave computes 64 nodes
-// whether the grid has them or not, and both planes of the halo are extra: it
-// wins once enough nodes share that, more of them the emptier the lines are.
-// With f the filled part of the lines, N f^2 separates the two: us per step
-// single / lines, FP64 with a source and walls, 56^3 (134k) 12.7 / 14.2, 72^3
-// (118k) 23.2 / 26.4, 60^3 (190k) 15.2 / 14.8, 80^3 (200k) 29.5 / 28.8, 60 x 100^2
-// (527k) 32.9 / 26.8; FP32 64^3 (262k) 9.9 / 10.9, 100 x 60^2 (220k) 12.1 / 13.5,
-// 128 x 64 x 40 (327k) 11.3 / 11.5, 60 x 100^2 18.4 / 16.4; FP16 10.5 / 10.8 and
-// 16.4 / 15.0 for the last two.
+// D3Q19: single sweeps, two-step passes in 62-node columns or in 64-node lines.
+// A pass has one workgroup per column and chunk of planes, a wave computes 64
+// nodes whether the grid has them or not, and the planes of the halo are extra.
+//  - It wins over single sweeps once enough nodes share that, more of them the
+//    emptier the lines are: with f the filled part of the lines, N f^2 separates
+//    the two.  us per step single / lines, FP64 with a source and walls, 56^3
+//    (134k) 12.7 / 14.2, 72^3 (118k) 23.2 / 26.4, 60^3 (190k) 15.2 / 14.8, 80^3
+//    (200k) 29.5 / 28.8; FP32 64^3 (262k) 9.9 / 10.9, 128 x 64 x 40 (327k) 11.3 /
+//    11.5, 60 x 100^2 (527k) 18.4 / 16.4; FP16 with walls 100^3 (610k) 19.2 / 18.9,
+//    80 x 120 x 140 (525k) 26.4 / 28.1; without, where single sweeps move half the
+//    bytes at full occupancy, 130^3 (1.0M) 31 / 43, 128^3 (2.1M) 30.5 / 30.0.
+//  - Lines where they save a column (256^3 FP32 291 against 325, FP64 82 against 108
+//    on 128^3).  Where they do not, a 62-node column is the better one in FP64 (its
+//    lines have an odd wave: 200 x 180 x 160 224 / 215, with a source 247 / 228), in
+//    FP32 with a source or beyond a million nodes (216 x 157 x 128 105 / 82, 80 x 120
+//    x 140 with a source 32.2 / 28.4; 96^3 without 18.4 / 19.6) and in FP16 with a
+//    source beyond four million (216 x 157 x 128 87 / 72; 130^3 43 / 46).
 void pick_lines(lbm_ctx *c) {
     if (!c->multi_ok) return;
-    const double f = (double)c->g.nx / (64.0 * ((c->g.nx + 63) / 64));
-    if (c->g.N * f * f < (c->dm.prec == 0 ? 190e3 : 350e3)) c->two = c->multi = false;
+    const uint32_t nx = c->g.nx, n = c->g.N, lines = (nx + 63) / 64;
+    const double f = (double)nx / (64.0 * lines);
+    const bool src = c->dm.src && !c->dm.sb;
+    const double small = c->dm.prec == 0 ? 190e3 : (c->dm.prec == 1 ? 350e3 : (c->dm.wall ? 600e3 : 2e6));
+    if (n * f * f < small) { c->two = c->multi = false; return; }
+    if (lines < (nx + 61) / 62) return;
+    c->multi = !(c->dm.prec == 0 || (c->dm.prec == 1 ? src || n > 1000000u : src && n > 4000000u));
 }
 
 // z planes per column of the D3Q19 pass.  Each workgroup lives for its chunk
@@ -658,10 +669,15 @@ hipError_t pass_pair(lbm_ctx *c, int start, int a, int b, hipStream_t st) {
     if (c->dm.q == 19) {
         const uint32_t zc = zchunk(c);
         const Dims d = eff_dims(c);
-        hipError_t e = launch_sweep2_q19(d, c->g, c->d_coefs, c->f[start], c->f[start ^ 1], c->p, p2, c->d_flag,
+        // Columns in the XCD order also where single sweeps take the hardware's:
+        // a pass rereads halo rows and planes its XCD has in L2 (us per step,
+        // FP32 145 x 175 x 126 81 -> 63, 200^3 218 -> 141).
+        Geom g = c->g;
+        g.remap = c->two_remap;
+        hipError_t e = launch_sweep2_q19(d, g, c->d_coefs, c->f[start], c->f[start ^ 1], c->p, p2, c->d_flag,
                                          c->two_shape, zc, st);
         if (e == hipSuccess)
-            e = launch_sweep2_q19(d, c->g, c->d_coefs, c->f[start ^ 1], c->f[start], p2, c->p, c->d_flag,
+            e = launch_sweep2_q19(d, g, c->d_coefs, c->f[start ^ 1], c->f[start], p2, c->p, c->d_flag,
                                   c->two_shape, zc, st);
         return e;
     }
@@ -900,7 +916,7 @@ int lbm_create(const lbm_desc *desc, lbm_ctx **out) {
                 (dm.q == 19 && dm.deg3 && c->dm.o32);
     c->two = c->two_ok;   // on by default where it applies (bit-identical; lbm_tune re-decides)
     c->multi_ok = c->multi = dm.deg3 && c->dm.o32 && (dm.q == 9 || dm.eqr);
-    c->multi_remap = (desc->flags & LBM_FLAG_NO_XCD_REMAP) ? 0 : 1;
+    c->multi_remap = c->two_remap = (desc->flags & LBM_FLAG_NO_XCD_REMAP) ? 0 : 1;
     if (c->multi_ok && dm.q == 9) c->multi_shape = c->multi_auto = pick_multi(c);
     if (dm.q == 19) pick_lines(c);
     {
@@ -1398,7 +1414,7 @@ int lbm_set_nontemporal(lbm_ctx *c, int on) {
 int lbm_set_remap(lbm_ctx *c, int on) {
     if (!c) return fail(LBM_E_INVALID, "null context");
     c->g.remap = on ? 1u : 0u;
-    c->multi_remap = on ? 1 : 0;
+    c->multi_remap = c->two_remap = on ? 1 : 0;
     drop_graphs(c);
     return LBM_OK;
 }
@@ -1455,7 +1471,7 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
     // two steps per pass: time pairs of passes (four steps), per step
     c->multi = false;
     bool best_two = false;
-    int best_shape = 0;
+    int best_shape = 0, best_two_remap = c->two_remap;
     c->g.chunk = (uint32_t)best_chunk;
     c->dm.nt = best_nt;
     if (two_ready(c) && !general_path(c)) {
@@ -1482,6 +1498,7 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
                 c->two_shape = shape;
                 prepare_zchunk(c);
                 c->g.remap = (remaps == 2 && ri % remaps == 0) ? 1u : 0u;
+                c->two_remap = (int)c->g.remap;
                 hipError_t e = pass_pair(c, c->cur, 2, 2, st);
                 if (e == hipSuccess) e = hipEventRecord(e0, st);
                 for (int r = 0; r < pair_reps && e == hipSuccess; ++r) e = pass_pair(c, c->cur, 2, 2, st);
@@ -1517,11 +1534,13 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
             if (ms < 0.98f * best_two_ms) {
                 best_two_ms = ms;
                 best_shape = shape;
+                best_two_remap = (int)remap;
                 if (ms < best) { best = ms; best_two = true; best_remap = remap; }
             }
         }
     }
     c->g.remap = best_remap;
+    c->two_remap = best_two_remap;
     c->two = best_two;
     c->two_shape = best_shape;
     prepare_zchunk(c);

@@ -860,7 +860,7 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
     return phio;
 }
 
-template <int Q, typename TS, typename TC, bool EQR, bool SRC, bool KVAR, bool WALL, int NP, bool NT = false,
+template <int Q, typename TS, typename TC, int EQR, bool SRC, bool KVAR, bool WALL, int NP, bool NT = false,
           bool SB = false, bool KF = false, bool O32 = false, bool RW = false>
 __device__ __forceinline__ void sweep_node(const Geom &g, const Coefs<TC> *__restrict__ cf,
                                            const TS *__restrict__ fin, TS *__restrict__ fout,
@@ -896,9 +896,15 @@ __device__ __forceinline__ void sweep_node(const Geom &g, const Coefs<TC> *__res
 // RW: every wave lies within one grid row (D2Q9 with nx a multiple of 64;
 // the host checks), and the gathers take the row-wave form.
 // SB: Scheme B with R(phi) and no fields (the fields take k_sweep_gen).
-template <int Q, typename TS, typename TC, bool EQR, bool SRC, bool KVAR, bool WALL, int NP, bool NT, bool O32 = false,
+// FP16 D3Q19 is bound by the loads in flight: held to the registers of 8 waves
+// per SIMD with walls and 6 without (256^3 us per step 386 -> 314, no source or
+// walls 242 -> 218); FP64 with a source and no walls to those of 4 (130^3 136.7
+// -> 128.7).  FP32 gains nothing from a limit.
+template <int Q, typename TS, typename TC, int EQR, bool SRC, bool KVAR, bool WALL, int NP, bool NT, bool O32 = false,
           bool RW = false, bool SB = false>
 __global__ void __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(Q != 19 || NP != 3 || sizeof(TS) == 4 ? 1 :
+                                     (sizeof(TS) == 2 ? (WALL ? 8 : 6) : (SRC && !WALL ? 4 : 1)), 8)))
 k_sweep(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin,
         TS *__restrict__ fout, const typename HistType<TS>::T *pin, typename HistType<TS>::T *pout, int *flag) {
     // (pin and pout may be the same buffer: a node reads and writes its own value)
@@ -1167,7 +1173,7 @@ struct Zc3 {
 // EQ: the equal-rate collision; otherwise the moment-space one (unequal
 // non-flux rates).
 template <typename TS, typename TC, bool KVAR, bool WALL, int NP, int TY, int NW, bool SB = false, bool SRC = false,
-          bool EQ = true>
+          int EQ = 1>
 __global__ void __launch_bounds__(64 * NW)
 k_sweep2_3d(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fin, TS *__restrict__ fout,
             const typename HistType<TS>::T *__restrict__ pin, typename HistType<TS>::T *__restrict__ pout,
