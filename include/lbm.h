@@ -191,6 +191,12 @@ int lbm_sweep(lbm_ctx *ctx, const void *f_in, void *f_out, void *p, void *stream
 int lbm_sweep_record(lbm_ctx *ctx, const void *f_in, const void *p_in, void *f_out, size_t f_step, void *p_out,
                      size_t p_step, int nsteps, void *stream);
 
+/* nsteps time steps of the bound state with the states before each of them
+ * kept: row i (f_rows + i f_step, p_rows + i p_step, as above) holds the state i
+ * steps on, the bound buffers end as lbm_step would leave them.
+ * LBM_E_UNSUPPORTED with lbm_set_check or re-centring on. */
+int lbm_step_record(lbm_ctx *ctx, void *f_rows, size_t f_step, void *p_rows, size_t p_step, int nsteps, void *stream);
+
 /* phi of the current state (Eq. 10a), FP64 [nz][ny][nx] into phi_dev. */
 int lbm_get_phi(lbm_ctx *ctx, double *phi_dev, void *stream);
 

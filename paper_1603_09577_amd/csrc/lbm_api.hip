@@ -1222,6 +1222,35 @@ int lbm_current(const lbm_ctx *c, void **f, void **p, long long *t) {
     return LBM_OK;
 }
 
+int lbm_step_record(lbm_ctx *c, void *f_rows, size_t f_step, void *p_rows, size_t p_step, int nsteps, void *stream) {
+    if (!c || !f_rows || !p_rows) return fail(LBM_E_INVALID, "null argument");
+    if (!c->bound) return fail(LBM_E_STATE, "lbm_init has not been called");
+    if (nsteps < 1) return fail(LBM_E_INVALID, "at least one step");
+    if (c->check_every || c->recenter_every)
+        return fail(LBM_E_UNSUPPORTED, "recorded steps take no divergence check and no re-centring");
+    hipStream_t st = (hipStream_t)stream;
+    if ((f_step & 255) || (p_step & 255) || f_step < (size_t)c->dm.q * c->g.plane * storage_size(c->dm.prec) ||
+        p_step < (size_t)c->g.N * hist_size(c->dm.prec))
+        return fail(LBM_E_INVALID, "steps must be multiples of 256 bytes that hold a state and a history");
+    hipError_t e = hipMemcpyAsync(f_rows, c->f[c->cur], (size_t)c->dm.q * c->g.plane * storage_size(c->dm.prec),
+                                  hipMemcpyDeviceToDevice, st);
+    if (e == hipSuccess && keeps_history(c))
+        e = hipMemcpyAsync(p_rows, c->p, (size_t)c->g.N * hist_size(c->dm.prec), hipMemcpyDeviceToDevice, st);
+    if (e != hipSuccess) return hip_fail(e, "recorded steps, first state");
+    if (nsteps > 1) {
+        const int rc = lbm_sweep_record(c, f_rows, p_rows, (char *)f_rows + f_step, f_step, (char *)p_rows + p_step,
+                                        p_step, nsteps - 1, stream);
+        if (rc != LBM_OK) return rc;
+    }
+    const size_t last = (size_t)(nsteps - 1);
+    const int to = c->cur ^ (nsteps & 1);
+    e = sweep(c, (char *)f_rows + last * f_step, c->f[to], (char *)p_rows + last * p_step, c->p, st);
+    if (e != hipSuccess) return hip_fail(e, "recorded steps, last sweep");
+    c->cur = to;
+    c->t += nsteps;
+    return LBM_OK;
+}
+
 int lbm_set_current(lbm_ctx *c, int which, long long t) {
     if (!c) return fail(LBM_E_INVALID, "null context");
     if (!c->bound) return fail(LBM_E_STATE, "lbm_init has not been called");

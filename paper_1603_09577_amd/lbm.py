@@ -34,7 +34,7 @@ EXPORTS = [
     "lbm_batch_get_shape", "lbm_batch_destroy", "lbm_probe_copy", "lbm_set_chunk", "lbm_tune",
     "lbm_set_nontemporal", "lbm_recenter", "lbm_set_recenter", "lbm_set_fields", "lbm_set_phi_wall",
     "lbm_set_two_step", "lbm_two_step_shape", "lbm_set_multi_step", "lbm_multi_step_shape",
-    "lbm_sweep_record", "lbm_adjoint_step2", "lbm_adjoint_pair_ok", "lbm_set_remap",
+    "lbm_sweep_record", "lbm_step_record", "lbm_adjoint_step2", "lbm_adjoint_pair_ok", "lbm_set_remap",
     "lbm_adjoint_tile_shape", "lbm_set_adjoint_tile", "lbm_adjoint_tile",
     "lbm_reduce_async", "lbm_reduce_state", "lbm_reduce_noalloc",
 ]
@@ -97,6 +97,7 @@ def load():
         "lbm_sweep": ([_VP, _VP, _VP, _VP, _VP], ctypes.c_int),
         "lbm_sweep_record": ([_VP, _VP, _VP, _VP, ctypes.c_size_t, _VP, ctypes.c_size_t, ctypes.c_int, _VP],
                              ctypes.c_int),
+        "lbm_step_record": ([_VP, _VP, ctypes.c_size_t, _VP, ctypes.c_size_t, ctypes.c_int, _VP], ctypes.c_int),
         "lbm_get_phi": ([_VP, _VP, _VP], ctypes.c_int),
         "lbm_phi_of": ([_VP, _VP, _VP, _VP], ctypes.c_int),
         "lbm_current": ([_VP, ctypes.POINTER(_VP), ctypes.POINTER(_VP), ctypes.POINTER(ctypes.c_longlong)], ctypes.c_int),
@@ -285,6 +286,19 @@ class Lbm:
             raise ValueError("fewer rows than sweeps")
         _check(self.lib.lbm_sweep_record(self.ctx, _ptr(f_in), _ptr(p_in), _ptr(f_out), f_out.stride(0), _ptr(p_out),
                                          p_out.stride(0), int(n), _stream(stream)))
+
+    def step_record(self, f_rows, p_rows, n, stream=None):
+        """step(n) that keeps the state before each step: row i of the 2-D uint8
+        tensors takes the state and the history i steps on.  False where the
+        library does not record (a divergence check or re-centring is on)."""
+        if n > min(f_rows.shape[0], p_rows.shape[0]):
+            raise ValueError("fewer rows than steps")
+        rc = self.lib.lbm_step_record(self.ctx, _ptr(f_rows), f_rows.stride(0), _ptr(p_rows), p_rows.stride(0), int(n),
+                                      _stream(stream))
+        if rc == LBM_E_UNSUPPORTED:
+            return False
+        _check(rc)
+        return True
 
     def phi(self, out=None, stream=None):
         import torch

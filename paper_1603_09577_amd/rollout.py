@@ -2,10 +2,13 @@
 
 ``rollout(sim, phi0, k0, nsteps)`` runs the fused sweep nsteps times and
 returns phi(T); its backward runs the hand-written reversed sweep
-(lbm_adjoint_step) with two-level checkpointing: a copy of the state every
-``seg`` steps (seg = ceil(sqrt(T)) by default) in the forward pass, and in the
-backward pass each segment is recomputed into a ring of seg states and then
-walked backwards.  Memory: about 2 sqrt(T) states.  Where two reversed
+(lbm_adjoint_step).  Without ``seg``, the forward pass keeps all T states where
+they take at most an eighth of the memory that is free at that moment, and
+the backward pass only walks them: 512^2 FP64 with a source, 64 steps (1.3 GB),
+1290 us instead of 1500.  Otherwise two-level checkpointing: a copy of the
+state every ``seg`` steps (ceil(sqrt(T)) by default) in the forward pass, and
+in the backward pass each segment is recomputed into a ring of seg states and
+then walked backwards.  Memory: about 2 sqrt(T) states.  Where two reversed
 sweeps per launch apply (lbm_adjoint_pair_ok) and a timed trial finds them
 faster (Lbm.adjoint_pairs_faster), the walk takes them (lbm_adjoint_step2);
 psi and pi are the same bit for bit either way.
@@ -36,11 +39,14 @@ def _k0_matrix(k0):
 
 class LbmRollout(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, phi0, k0, sim, nsteps, seg, pairs):
+    def forward(ctx, phi0, k0, sim, nsteps, seg, pairs, keep_all):
         sim.set_k0(_k0_matrix(k0))
         sim.init(phi0.detach())
         checkpoints = []
         t = 0
+        ctx.states = _record(sim, nsteps) if keep_all else None
+        if ctx.states:
+            t = nsteps
         while t < nsteps:
             which, _ = sim.current()
             checkpoints.append((t, sim.f[which].clone(), sim.p.clone()))
@@ -67,16 +73,8 @@ class LbmRollout(torch.autograd.Function):
         cur_psi, pi = sim.adjoint_buffers()
         psi_other, pi_other = sim.adjoint_buffers()
         sim.adjoint_seed(gphi, cur_psi, pi)
-        # the states of a segment: its checkpoint, then the recomputed ones
-        rows = max(1, min(seg, ctx.nsteps) - 1)
-        fs = torch.empty((rows, sim.f_bytes), dtype=torch.uint8, device=sim.device)
-        ps = torch.empty((rows, sim.p_bytes), dtype=torch.uint8, device=sim.device)
-        for t0, fck, pck in reversed(ctx.checkpoints):
-            n = min(seg, ctx.nsteps - t0)
-            ring = [(fck, pck)] + [(fs[i], ps[i]) for i in range(n - 1)]
-            if n > 1:
-                sim.sweep_record(fck, pck, fs, ps, n - 1)
-            i = n - 1
+        for ring in _segments(ctx, sim, seg):
+            i = len(ring) - 1
             while i >= 0:
                 if use_pairs and i >= 1:
                     sim.adjoint_step2(ring[i][0], ring[i][1], ring[i - 1][0], ring[i - 1][1],
@@ -91,7 +89,35 @@ class LbmRollout(torch.autograd.Function):
         gk = sim.adjoint_grad_k0()
         keys = ("xx", "xy", "yy") if ctx.k0_len == 3 else ("xx", "xy", "yy", "xz", "yz", "zz")
         gk_t = torch.tensor([gk[k] for k in keys], dtype=torch.float64, device=ctx.k0_device)
-        return gphi0, gk_t, None, None, None, None
+        return gphi0, gk_t, None, None, None, None, None
+
+
+def _record(sim, nsteps):
+    """The states before each of the next nsteps steps, which are taken, or None
+    where they do not fit or the run does not record."""
+    dev = sim.device
+    need = nsteps * (sim.f_bytes + sim.p_bytes)
+    if nsteps < 1 or 8 * need > torch.cuda.mem_get_info(dev)[0]:
+        return None
+    fs = torch.empty((nsteps, sim.f_bytes), dtype=torch.uint8, device=dev)
+    ps = torch.empty((nsteps, sim.p_bytes), dtype=torch.uint8, device=dev)
+    return (fs, ps) if sim.step_record(fs, ps, nsteps) else None
+
+
+def _segments(ctx, sim, seg):
+    """Lists of consecutive (state, history), the last steps first."""
+    if ctx.states:
+        yield list(zip(*ctx.states))
+        return
+    # the states of a segment: its checkpoint, then the recomputed ones
+    rows = max(1, min(seg, ctx.nsteps) - 1)
+    fs = torch.empty((rows, sim.f_bytes), dtype=torch.uint8, device=sim.device)
+    ps = torch.empty((rows, sim.p_bytes), dtype=torch.uint8, device=sim.device)
+    for t0, fck, pck in reversed(ctx.checkpoints):
+        n = min(seg, ctx.nsteps - t0)
+        if n > 1:
+            sim.sweep_record(fck, pck, fs, ps, n - 1)
+        yield [(fck, pck)] + [(fs[i], ps[i]) for i in range(n - 1)]
 
 
 def rollout(sim, phi0, k0, nsteps, seg=None, pairs="auto"):
@@ -99,10 +125,12 @@ def rollout(sim, phi0, k0, nsteps, seg=None, pairs="auto"):
     ((xx, xy, yy) in 2-D), differentiable in phi0 and k0.  ``pairs``: "auto"
     (time both launch forms once), True (two reversed sweeps per launch where
     they apply) or False (one per launch)."""
+    # a run that needs no gradient keeps no states
+    keep_all = seg is None and torch.is_grad_enabled() and (phi0.requires_grad or k0.requires_grad)
     seg = seg or max(1, int(math.ceil(math.sqrt(nsteps))))
     if pairs != "auto":
         pairs = bool(pairs)
-    return LbmRollout.apply(phi0, k0, sim, int(nsteps), int(seg), pairs)
+    return LbmRollout.apply(phi0, k0, sim, int(nsteps), int(seg), pairs, keep_all)
 
 
 __all__ = ["rollout", "LbmRollout"]

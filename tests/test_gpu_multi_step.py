@@ -222,3 +222,30 @@ def test_recorded_sweeps_refusals():
         assert e.value.code == lbm.LBM_E_INVALID
     with pytest.raises(lbm.LbmError):
         s.sweep_record(fs[0], s.p, fs, ps, 2)
+
+
+@pytest.mark.parametrize("lat,prec,T", [(9, "f64", 14), (9, "f32", 7), (9, "f64", 1), (19, "f64", 6)])
+def test_rollout_with_all_states_equals_checkpoints(lat, prec, T):
+    """The gradient from kept states and from checkpoints (bit for bit: the same
+    launches in the same order), the state afterwards, and the way back to
+    checkpoints where the library does not record."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    from paper_1603_09577_amd.rollout import rollout
+    spec = _spec(70, 33, prec) if lat == 9 else W.d3q19_walls_source((12, 9, 7), precision=prec)[0]
+    n = spec["shape"][::-1]
+    phi0 = W.noise_field(n, 4, mean=0.4, amp=0.2)
+    out = []
+    for seg, check in ((None, 0), (4, 0), (None, 50)):
+        s = lbm.Lbm(spec)
+        s.set_check(check)
+        p0 = torch.tensor(phi0, dtype=torch.float64, device="cuda", requires_grad=True)
+        k0 = torch.tensor([0.1, 0.01, 0.12] if lat == 9 else [0.1, 0.01, 0.12, 0.02, 0.015, 0.11], dtype=torch.float64,
+                          requires_grad=True)
+        ph = rollout(s, p0, k0, T, seg, pairs=False)
+        (ph ** 2).sum().backward()
+        assert s.current() == (T % 2, T) and torch.equal(s.phi(), ph.detach())
+        out.append((ph.detach(), p0.grad, k0.grad))
+    for o in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], o))
