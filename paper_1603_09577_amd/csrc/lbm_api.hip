@@ -543,10 +543,13 @@ uint64_t multi_tiles(const lbm_ctx *c, int shape) {
 //    steps in 16 rows, FP64 3.35 against 3.92), or with four where that fits
 //    one round of resident workgroups and six steps do not (1000 x 723 FP32
 //    with walls 5.14 against 5.65).
+//  - FP16 takes four steps in 32 rows up to eight workgroups per CU (512^2 3.07
+//    against 3.24 for six in 48 rows, 1024^2 6.02 / 6.79, 1600^2 12.2 / 12.6; 2048^2
+//    19.2 / 18.2).
 //  - Beyond one round the halo work counts: FP32 and FP16 keep six steps in the
-//    tall region (2048^2 FP32 20.4 against 24.1 for four and 22.6 for four in
-//    16 rows), FP64, whose tall region leaves one workgroup per CU, takes four
-//    steps in 16 rows (1024^2 12.0 against 12.6).
+//    tall region (2048^2 FP32 18.9 against 22.3 for four), FP64, whose tall region
+//    leaves one workgroup per CU, takes four steps in 16 rows (1024^2 12.0 against
+//    12.6).
 int pick_multi(lbm_ctx *c) {
     query_cus(c);
     const uint64_t ncu = c->ncu > 0 ? (uint64_t)c->ncu : 256;
@@ -559,6 +562,7 @@ int pick_multi(lbm_ctx *c) {
     if (fits(1, 1)) return 1;
     if (!f64 && fits(6, 3)) return 6;
     if (fits(2, 1)) return 2;
+    if (c->dm.prec == 2) return fits(4, 8) ? 4 : 3;
     if (fits(3, f64 ? 1 : 2)) return 3;
     if (fits(4, 2)) return 4;
     return f64 ? 4 : 3;
@@ -571,25 +575,26 @@ int pick_multi(lbm_ctx *c) {
 //    emptier the lines are: with f the filled part of the lines, N f^2 separates
 //    the two.  us per step single / lines, FP64 with a source and walls, 56^3
 //    (134k) 12.7 / 14.2, 72^3 (118k) 23.2 / 26.4, 60^3 (190k) 15.2 / 14.8, 80^3
-//    (200k) 29.5 / 28.8; FP32 64^3 (262k) 9.9 / 10.9, 128 x 64 x 40 (327k) 11.3 /
-//    11.5, 60 x 100^2 (527k) 18.4 / 16.4; FP16 with walls 100^3 (610k) 19.2 / 18.9,
+//    (200k) 29.5 / 28.8; FP32 100 x 60^2 (220k) 11.3 / 11.9, 64^3 (262k) 9.1 / 9.4, 50 x
+//    100 x 80 (244k) 12.7 / 11.9, 64^2 x 80 (327k) 11.0 / 10.0; FP16 with walls 100^3 (610k) 19.2 / 18.9,
 //    80 x 120 x 140 (525k) 26.4 / 28.1; without, where single sweeps move half the
 //    bytes at full occupancy, 130^3 (1.0M) 31 / 43, 128^3 (2.1M) 30.5 / 30.0.
 //  - Lines where they save a column (256^3 FP32 291 against 325, FP64 82 against 108
 //    on 128^3).  Where they do not, a 62-node column is the better one in FP64 (its
 //    lines have an odd wave: 200 x 180 x 160 224 / 215, with a source 247 / 228), in
-//    FP32 with a source or beyond a million nodes (216 x 157 x 128 105 / 82, 80 x 120
-//    x 140 with a source 32.2 / 28.4; 96^3 without 18.4 / 19.6) and in FP16 with a
+//    FP32 with a source and no walls or beyond a million nodes (216 x 157 x 128 105 /
+//    82, 100 x 80 x 60 with a source 15.3 / 13.4; 96^3 without 18.4 / 19.6) and in FP16 with a
 //    source beyond four million (216 x 157 x 128 87 / 72; 130^3 43 / 46).
 void pick_lines(lbm_ctx *c) {
     if (!c->multi_ok) return;
     const uint32_t nx = c->g.nx, n = c->g.N, lines = (nx + 63) / 64;
     const double f = (double)nx / (64.0 * lines);
     const bool src = c->dm.src && !c->dm.sb;
-    const double small = c->dm.prec == 0 ? 190e3 : (c->dm.prec == 1 ? 350e3 : (c->dm.wall ? 600e3 : 2e6));
+    const double small = c->dm.prec == 0 ? 190e3 : (c->dm.prec == 1 ? 240e3 : (c->dm.wall ? 600e3 : 2e6));
     if (n * f * f < small) { c->two = c->multi = false; return; }
     if (lines < (nx + 61) / 62) return;
-    c->multi = !(c->dm.prec == 0 || (c->dm.prec == 1 ? src || n > 1000000u : src && n > 4000000u));
+    c->multi = !(c->dm.prec == 0 ||
+                 (c->dm.prec == 1 ? (src && !c->dm.wall) || n > 1000000u : src && n > 4000000u));
 }
 
 // z planes per column of the D3Q19 pass.  Each workgroup lives for its chunk
