@@ -387,9 +387,17 @@ __device__ __forceinline__ void k0_partials(const Coefs<TC> *__restrict__ cf, co
 // is allowed down to 2.
 // RW: every wave lies within one grid row (D2Q9 with nx a multiple of 64;
 // the host checks), and the loads take the row-wave form above.
+// Streaming D3Q19 states (NT) are also held below an upper limit: more waves than
+// these widen the window of planes in flight, and halo rows are read again (256^3
+// with a source and walls 739 -> 701 us per reversed sweep, FP64 1478 -> 1395).
+constexpr int adjoint_max_waves(int q, bool nt, bool src, int size) {
+    return q != 19 || !nt ? 8 : (src ? (size == 4 ? 4 : 2) : (size == 4 ? 7 : 3));
+}
+
 template <int Q, typename TS, typename TC, bool EQR, bool SRC, bool KVAR, bool WALL, int NP, bool O32 = false,
           bool NT = false, bool RW = false>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Q == 9 ? 4 : 2, 8)))
+__global__ void __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(Q == 9 ? 4 : 2, adjoint_max_waves(Q, NT, SRC, (int)sizeof(TC)))))
 k_adjoint(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict__ fs,
           const typename HistType<TS>::T *__restrict__ ps, const TC *__restrict__ psi_next,
           const double *pi_next, TC *__restrict__ psi_out, double *pi_out, double *__restrict__ gk_part) {
