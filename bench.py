@@ -400,24 +400,18 @@ def cpu_baseline(spec, phi0, target_s=12.0, single_s=6.0):
 
 PROFILE_COMMANDS = {
     "trace": "rocprofv3 --kernel-trace --stats -d gpurun_out/prof_trace -o trace --output-format csv -- "
-             "python3 bench.py --no-cpu --steps 1000 --warmup 50 --two-step-shape 1 --two-step-3d 14x16,6x8 "
-             "--adjoint-tile-pick",
+             "python3 bench.py --no-cpu --steps 1000 --warmup 50 --adjoint-tile-pick",
     "fetch": "rocprofv3 --pmc FETCH_SIZE -d gpurun_out/pmc_fetch -o fetch --output-format csv -- "
-             "python3 bench.py --no-cpu --steps 20 --warmup 0 --only adjoint,d3q19,batch --two-step-shape 1 --two-step-3d 14x16,6x8 "
-             "--adjoint-tile-pick",
+             "python3 bench.py --no-cpu --steps 20 --warmup 0 --only adjoint,d3q19,batch --adjoint-tile-pick",
     "write": "rocprofv3 --pmc WRITE_SIZE -d gpurun_out/pmc_write -o write --output-format csv -- "
-             "python3 bench.py --no-cpu --steps 20 --warmup 0 --only adjoint,d3q19,batch --two-step-shape 1 --two-step-3d 14x16,6x8 "
-             "--adjoint-tile-pick",
+             "python3 bench.py --no-cpu --steps 20 --warmup 0 --only adjoint,d3q19,batch --adjoint-tile-pick",
     "valu": "rocprofv3 --pmc SQ_INSTS_VALU SQ_INSTS_SALU SQ_INSTS_LDS SQ_WAVES -d gpurun_out/pmc_valu -o valu "
-            "--output-format csv -- python3 bench.py --no-cpu --steps 20 --warmup 0 --only adjoint,d3q19 "
-            "--two-step-shape 1 --two-step-3d 14x16,6x8 --adjoint-tile-pick",
+            "--output-format csv -- python3 bench.py --no-cpu --steps 20 --warmup 0 --only adjoint,d3q19,batch --adjoint-tile-pick",
     "stall": "rocprofv3 --pmc SQ_WAVES SQ_WAVE_CYCLES SQ_BUSY_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY "
              "SQ_WAIT_INST_LDS -d gpurun_out/pmc_stall -o stall --output-format csv -- "
-             "python3 bench.py --no-cpu --steps 20 --warmup 0 --only adjoint,d3q19 --two-step-shape 1 "
-             "--two-step-3d 14x16,6x8 --adjoint-tile-pick",
+             "python3 bench.py --no-cpu --steps 20 --warmup 0 --only adjoint,d3q19,batch --adjoint-tile-pick",
     "l2": "rocprofv3 --pmc TCC_HIT_sum TCC_MISS_sum -d gpurun_out/pmc_l2 -o l2 --output-format csv -- "
-          "python3 bench.py --no-cpu --steps 20 --warmup 0 --only adjoint,d3q19 --two-step-shape 1 "
-          "--two-step-3d 14x16,6x8 --adjoint-tile-pick",
+          "python3 bench.py --no-cpu --steps 20 --warmup 0 --only adjoint,d3q19,batch --adjoint-tile-pick",
 }
 # vector-ALU issue peak without packed FP32: each SIMD issues one 64-lane
 # instruction every 4 clocks (16 lanes per clock), 4 SIMDs per CU, so one
@@ -429,10 +423,13 @@ BATCH_NODES = 44439067
 
 # workload label -> (kernel name prefix in the trace, algorithmic bytes per launch)
 PROFILED = {
-    "nonlinear2d-1024 f32 two-step": ("k_sweep2<float, float, true, true, 3, ",
-                                      bytes_per_node(9, "f32", True) * 1024 * 1024),
-    "nonlinear2d-1024 f64 two-step": ("k_sweep2<double, double, true, true, 3, ",
-                                      bytes_per_node(9, "f64", True) * 1024 * 1024),
+    "nonlinear2d-1024 f32 6-step": ("k_sweep_multi<float, float, true, true, 6, 32, 16, ",
+                                    bytes_per_node(9, "f32", True) * 1024 * 1024),
+    "nonlinear2d-1024 f64 4-step": ("k_sweep_multi<double, double, true, true, 4, 16, 8, ",
+                                    bytes_per_node(9, "f64", True) * 1024 * 1024),
+    "d3q19-256 f32 two-step lines": ("k_sweep2_3dw<float, float, ", bytes_per_node(19, "f32", False) * 256 ** 3),
+    "d3q19-256 f64 two-step lines": ("k_sweep2_3dw<double, double, ", bytes_per_node(19, "f64", False) * 256 ** 3),
+    "batch-512 f32 6-step": ("k_batch_multi<float, float, true, 6, ", bytes_per_node(9, "f32", False) * BATCH_NODES),
     "nonlinear2d-1024 f32": ("k_sweep<9, float, float, true, true, true, false, 3, false, ",
                              bytes_per_node(9, "f32", True) * 1024 * 1024),
     "nonlinear2d-1024 f64": ("k_sweep<9, double, double, true, true, true, false, 3, false, ",
@@ -441,9 +438,6 @@ PROFILED = {
                       bytes_per_node(19, "f32", False) * 256 ** 3),
     "d3q19-256 f64": ("k_sweep<19, double, double, true, false, false, true, ",
                       bytes_per_node(19, "f64", False) * 256 ** 3),
-    "d3q19-256 f32 two-step": ("k_sweep2_3d<float, float, ", bytes_per_node(19, "f32", False) * 256 ** 3),
-    "d3q19-256 f64 two-step": ("k_sweep2_3d<double, double, ", bytes_per_node(19, "f64", False) * 256 ** 3),
-    "batch-512 f32 two-step": ("k_batch_sweep2<float, float, ", bytes_per_node(9, "f32", False) * BATCH_NODES),
     "adjoint2d-512 f64": ("k_adjoint<9, double, double, true, true, true, false, 3, ",
                           adjoint_bytes_per_node(9, "f64", True) * 512 * 512),
     "adjoint2d-512 f32": ("k_adjoint<9, float, float, true, true, true, false, 3, ",
@@ -453,6 +447,12 @@ PROFILED = {
     "adjoint2d-512 f32 pairs": ("k_adjoint2<float, float, true, true, 3, ",
                                 adjoint_pair_bytes_per_node(9, "f32", True) * 512 * 512),
 }
+
+
+def updates_per_node(label):
+    """Node updates per node and launch of a profiled workload."""
+    m = re.search(r" (\d+)-step", label)
+    return int(m.group(1)) if m else (2 if "two-step" in label or "pairs" in label else 1)
 
 
 def summarize_profiles(gdir, copy_bytes=1 << 30):
@@ -630,7 +630,7 @@ def summarize_profiles(gdir, copy_bytes=1 << 30):
             tr = w.get("trace_median_us")
             nodes = {"nonlinear2d-1024": 1024 * 1024, "adjoint2d-512": 512 * 512,
                      "d3q19-256": 256 ** 3, "batch-512": BATCH_NODES}[label.split(" ")[0]]
-            upd = nodes * (2 if ("two-step" in label or "pairs" in label) else 1)
+            upd = nodes * updates_per_node(label)
             frac = m["SQ_INSTS_VALU"] / (tr * 1e-6 * VALU_ISSUE_PEAK) if tr else None
             w.update({"sq_insts_valu": m["SQ_INSTS_VALU"], "valu_issue_fraction": frac})
             vl.append(f"| {label} | `{k.replace('lbm::', '')}` | {m.get('SQ_WAVES', 0):.0f} | "
