@@ -215,8 +215,8 @@ int lbm_set_current(lbm_ctx *ctx, int which, long long t);
 int lbm_set_chunk(lbm_ctx *ctx, int chunk);
 
 /* Workgroup order: on = one contiguous run of the domain per XCD (the
- * default unless the state exceeds the Infinity Cache or
- * LBM_FLAG_NO_XCD_REMAP is set), off = the hardware's round-robin order.
+ * default unless LBM_FLAG_NO_XCD_REMAP is set or, for single sweeps and D2Q9
+ * two-step passes, the state exceeds the Infinity Cache), off = the hardware's round-robin order.
  * lbm_tune sets it too. */
 int lbm_set_remap(lbm_ctx *ctx, int on);
 
@@ -230,7 +230,8 @@ int lbm_set_nontemporal(lbm_ctx *ctx, int on);
  * 1, 2, 4, 8, 16 workgroup blocks, with and without non-temporal accesses,
  * and with the XCD-aware block order (one contiguous slab per XCD) or the
  * hardware's round-robin order (unless LBM_FLAG_NO_XCD_REMAP pins the
- * latter), and, where allowed, two time steps per pass (lbm_set_two_step);
+ * latter), and, where allowed, two time steps per pass (lbm_set_two_step) and
+ * passes of several (lbm_set_multi_step);
  * keeps the fastest; then, unless LBM_FLAG_NO_GRAPH is set or a divergence
  * check is enabled, times lbm_step's graph replays against direct launches of
  * the same kernels and keeps direct launches unless graphs are at least 1%
