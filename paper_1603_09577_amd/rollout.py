@@ -39,7 +39,7 @@ def _k0_matrix(k0):
 
 class LbmRollout(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, phi0, k0, sim, nsteps, seg, pairs, keep_all):
+    def forward(ctx, phi0, k0, sim, nsteps, seg, pairs, keep_all=False):
         sim.set_k0(_k0_matrix(k0))
         sim.init(phi0.detach())
         checkpoints = []

@@ -249,3 +249,21 @@ def test_rollout_with_all_states_equals_checkpoints(lat, prec, T):
         out.append((ph.detach(), p0.grad, k0.grad))
     for o in out[1:]:
         assert all(torch.equal(a, b) for a, b in zip(out[0], o))
+
+
+def test_rollout_function_called_directly():
+    """LbmRollout.apply without the last argument keeps checkpoints."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    from paper_1603_09577_amd.rollout import LbmRollout, rollout
+    phi0 = W.noise_field((33, 70), 4, mean=0.4, amp=0.2)
+    k = torch.tensor([0.1, 0.01, 0.12], dtype=torch.float64)
+    grads = []
+    for direct in (True, False):
+        s = lbm.Lbm(_spec(70, 33, "f64"))
+        p0 = torch.tensor(phi0, dtype=torch.float64, device="cuda", requires_grad=True)
+        ph = LbmRollout.apply(p0, k, s, 9, 3, False) if direct else rollout(s, p0, k, 9, pairs=False)
+        (ph ** 2).sum().backward()
+        grads.append(p0.grad)
+    assert torch.equal(*grads)
