@@ -57,9 +57,8 @@ constexpr int kNumShapes = 4;
 // here; six steps cost the uneven instances more in ragged tiles (54 x 22
 // nodes) than four in 16 rows (58 x 10), which the tuner weighs.  us per step,
 // 128 instances of 32^2 to 512^2 (10.3 M nodes), two / four / six steps per
-// launch: FP32 80.2 / 54.5 / 46.9, FP64 152 / 113 / 113, FP16 58.3 / 50.1 /
-// 49.3; 8 instances (0.82 M nodes): FP32 6.2 / 5.2 / 4.3, FP64 11.1 / 10.0 /
-// 9.4.  Two steps move the state once per two updates at 0.86 of the copy
+// launch: FP32 83 / 54 / 48, FP64 152 / 106 / 106, FP16 66 / 50 / 49; 8 instances
+// (0.82 M nodes): FP32 6.4 / 5.1 / 4.3, FP64 10.9 / 9.4 / 8.8.  Two steps move the state once per two updates at 0.86 of the copy
 // rate; six are bound by vector issue and the halo.
 struct PassShape {
     int steps, rows, waves;

@@ -31,8 +31,9 @@
 // issue (about 110 operations per node and step, 1.45 times that with the
 // halo) and the barriers.  us per step before -> after, FP32 with K(phi) and a
 // source unless noted: 64^2 FP64 unequal rates 2.41 -> 1.14, 32-wide 0.89;
-// 256^2 3.5 -> 1.24; 1024^2 8.0 -> 5.9, FP64 14.3 -> 12.0; 1000 x 723 channel with unequal rates
-// 7.9 -> 5.1; 2048^2 44 -> 20.4, FP64 80 -> 51; 4000 x 2500 FP16 54 -> 44.5.
+// 256^2 3.5 -> 1.23; 1024^2 8.0 -> 5.8, FP64 14.3 -> 12.0; 1000 x 723 channel with
+// unequal rates 7.9 -> 5.1; 2048^2 44 -> 18.9, FP64 80 -> 48; 4000 x 2500 FP16 54 ->
+// 41.7.
 //
 // A Scheme-A run reads phi(t - 1) of the region from pin, hands each node's
 // source terms to the next step in the registers of the wave that owns its
