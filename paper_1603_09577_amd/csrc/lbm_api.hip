@@ -428,6 +428,13 @@ bool general_path(const lbm_ctx *c) {
 // takes the general kernel and never runs two-step passes).
 bool keeps_history(const lbm_ctx *c) { return c->dm.src && !c->dm.sb; }
 
+// The sweep reads the history of the state it starts from: where it keeps one,
+// and in the general kernel, which also runs with R = 0 (per-node K0) and forms
+// Remark III's dB/dt from it whatever the scheme.
+bool reads_history(const lbm_ctx *c) {
+    return general_path(c) ? !eff_dims(c).sb || remark3(c) : keeps_history(c);
+}
+
 // Calls the adjoint does not cover: Scheme B sources, fields, Remark III.
 bool adjoint_refused(const lbm_ctx *c) { return eff_dims(c).sb || c->kfield || c->rfield || remark3(c); }
 
@@ -1239,7 +1246,7 @@ int lbm_step_record(lbm_ctx *c, void *f_rows, size_t f_step, void *p_rows, size_
         return fail(LBM_E_INVALID, "steps must be multiples of 256 bytes that hold a state and a history");
     hipError_t e = hipMemcpyAsync(f_rows, c->f[c->cur], (size_t)c->dm.q * c->g.plane * storage_size(c->dm.prec),
                                   hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess && keeps_history(c))
+    if (e == hipSuccess && reads_history(c))
         e = hipMemcpyAsync(p_rows, c->p, (size_t)c->g.N * hist_size(c->dm.prec), hipMemcpyDeviceToDevice, st);
     if (e != hipSuccess) return hip_fail(e, "recorded steps, first state");
     if (nsteps > 1) {

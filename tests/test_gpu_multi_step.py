@@ -206,6 +206,62 @@ def test_recorded_states_bit_identical(nx, ny, prec, source, wall, rates, n):
         f = out
 
 
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("kind", ["remark3", "remark3 B", "remark3 walls", "K field", "K field A", "K, R fields", "A"])
+@pytest.mark.parametrize("n", [1, 5])
+def test_recorded_steps_take_the_history(kind, prec, n):
+    """step_record against step where the general kernel runs: it reads the
+    history also without a Scheme-A source (Remark III's dB/dt, R = 0 with a
+    per-node K0), so the first recorded sweep must find it; rows that start as
+    NaN show any that does not."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    from paper_1603_09577_amd.rollout import rollout
+    nx, ny = 50, 21
+    scheme = {"remark3": "none", "remark3 walls": "none", "K field": "none"}.get(kind, "B" if "B" in kind or "R" in kind else "A")
+    spec = _spec(nx, ny, prec, source=scheme, wall="walls" in kind)
+    if kind.startswith("remark3"):
+        spec = dict(spec, variant="remark3", b=[[0.0, 0.02, 0.06], [0.0, -0.03, 0.05]])
+    phi0 = W.noise_field((ny, nx), 5)
+    kf = torch.full((ny, nx, 3), 0.05, dtype=torch.float64, device="cuda")
+    kf[..., 2] = 0.01
+    rf = torch.full((ny, nx), 1e-4, dtype=torch.float64, device="cuda")
+
+    def new():
+        s = lbm.Lbm(spec)
+        if "field" in kind:
+            s.set_fields(kf, rf if "R" in kind else None)
+        return s.init(phi0)
+
+    a, b = new(), new()
+    a.step(3)
+    b.step(3)
+    fs = torch.full((n, b.f_bytes), 255, dtype=torch.uint8, device="cuda")   # all ones: NaN in every type
+    ps = torch.full((n, b.p_bytes), 255, dtype=torch.uint8, device="cuda")
+    assert b.step_record(fs, ps, n)
+    nb = nx * ny * (8 if prec == "f64" else 4)
+    for i in range(n):
+        w, _ = a.current()
+        assert torch.equal(a.storage_view(a.f[w]), b.storage_view(fs[i])), i
+        assert kind == "K, R fields" or torch.equal(a.p[:nb], ps[i][:nb]), i     # Scheme B alone has no history
+        a.step(1)
+    w, _ = a.current()
+    assert a.current() == b.current()
+    assert torch.equal(a.storage_view(a.f[w]), b.storage_view(b.f[w]))
+    assert torch.equal(a.p[:nb], b.p[:nb]) and torch.equal(a.phi(), b.phi())
+    assert torch.isfinite(b.phi()).all()
+    # a rollout of an input that requires a gradient records its states
+    k0 = torch.tensor([spec["k0"][0][0], spec["k0"][0][1], spec["k0"][1][1]], dtype=torch.float64)
+    s = new()
+    junk = torch.full((64, b.f_bytes + b.p_bytes), 255, dtype=torch.uint8, device="cuda")
+    del junk                                             # what the allocator hands out next holds NaN
+    got = rollout(s, torch.tensor(phi0, device="cuda", requires_grad=True), k0, n + 3)
+    ref = new()
+    ref.step(n + 3)
+    assert torch.equal(got.detach(), ref.phi())
+
+
 def test_recorded_sweeps_refusals():
     import torch
 
