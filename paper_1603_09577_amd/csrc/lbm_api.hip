@@ -470,6 +470,12 @@ void query_cus(lbm_ctx *c) {
         c->ncu = n;
 }
 
+// The device's CUs, 256 where they are not known.
+uint64_t cu_count(lbm_ctx *c) {
+    query_cus(c);
+    return c->ncu > 0 ? (uint64_t)c->ncu : 256;
+}
+
 // Resident workgroups per CU of the D3Q19 pass in the current tile shape and
 // the CU count, asked of the runtime once per shape (outside graph capture:
 // lbm_init, lbm_set_two_step and lbm_tune call this before any pass).
@@ -518,61 +524,6 @@ void pick_adj_shape(lbm_ctx *c) {
     const uint64_t per_cu6 = (tiles(6) + ncu - 1) / ncu, per_cu10 = (tiles(10) + ncu - 1) / ncu;
     if (c->dm.prec == 1 && tiles(10) * 12 <= 6 * 4 * ncu && 2 * per_cu10 <= per_cu6) c->adj_shape = 2;
     c->adj_shape_auto = c->adj_shape;
-}
-
-// Workgroups of a D2Q9 pass of several steps in shape `shape`.
-uint64_t multi_tiles(const lbm_ctx *c, int shape) {
-    int t = 2, tr = 4, nw = 0, tx = 64;
-    multi_shape_of(c->dm.prec, shape, &t, &tr, &nw, &tx);
-    const uint32_t tw = (uint32_t)(tx - 2 * (t - 1)), th = (uint32_t)(tr - 2 * (t - 1));
-    return (uint64_t)((c->g.nx + tw - 1) / tw) * ((c->g.ny + th - 1) / th);
-}
-
-// Shape of the D2Q9 passes of several steps.  A pass costs one launch (1.6 us
-// between dependent launches, plus the first loads and the last stores), one
-// collision per step on the chain of its waves, and the halo: T - 1 nodes on
-// each side of a region of 64 x TR or 32 x TR nodes.
-//  - While the grid gives every CU at most one workgroup, nothing else runs on
-//    that CU and the halo is free; a step costs about 0.9 us with the four rows
-//    per SIMD of a 64 x 16 region and 0.5 us with half of them (FP64).  So the
-//    32-wide region with the most steps that still fits one round wins: us per
-//    step, FP64 without / FP32 with a source, 64^2 32-wide T = 8 0.89 / 0.82, 6
-//    1.03 / 0.93, 64-wide T = 8 1.14 / 1.01; 128^2 32-wide T = 8, two rounds,
-//    1.24 / 1.03, 6 1.07 / 0.95, 64-wide 8 1.21 / 1.04; FP64 200^2 32-wide 4
-//    1.40, 64-wide 6 1.44.
-//  - FP32 and FP16 gain less from the shorter steps, and their second and third
-//    32-wide workgroup on a CU costs less: six steps up to two of them (200^2
-//    1.19, one 64 x 16 region with six steps 1.21), and up to three rather than
-//    four steps in 64 x 16 (300^2 1.53 against 1.62).
-//  - Then 64 x 16 with six, then with four steps in one round (256^2 1.26 / 1.76
-//    against 1.46 / 2.09 32-wide with four).
-//  - Then the tall region with six steps (512^2 FP32 2.18 against 2.43 for four
-//    steps in 16 rows, FP64 3.35 against 3.92), or with four where that fits
-//    one round of resident workgroups and six steps do not (1000 x 723 FP32
-//    with walls 5.14 against 5.65).
-//  - FP16 takes four steps in 32 rows up to eight workgroups per CU (512^2 3.07
-//    against 3.24 for six in 48 rows, 1024^2 6.02 / 6.79, 1600^2 12.2 / 12.6; 2048^2
-//    19.2 / 18.2).
-//  - Beyond one round the halo work counts: FP32 and FP16 keep six steps in the
-//    tall region (2048^2 FP32 18.9 against 22.3 for four), FP64, whose tall region
-//    leaves one workgroup per CU, takes four steps in 16 rows (1024^2 12.0 against
-//    12.6).
-int pick_multi(lbm_ctx *c) {
-    query_cus(c);
-    const uint64_t ncu = c->ncu > 0 ? (uint64_t)c->ncu : 256;
-    auto fits = [&](int shape, uint64_t per_cu) { return multi_tiles(c, shape) <= per_cu * ncu; };
-    const bool f64 = c->dm.prec == 0;
-    if (fits(5, 1)) return 5;
-    if (fits(6, f64 ? 1 : 2)) return 6;
-    if (fits(0, 1)) return 0;
-    if (f64 && fits(7, 1)) return 7;
-    if (fits(1, 1)) return 1;
-    if (!f64 && fits(6, 3)) return 6;
-    if (fits(2, 1)) return 2;
-    if (c->dm.prec == 2) return fits(4, 8) ? 4 : 3;
-    if (fits(3, f64 ? 1 : 2)) return 3;
-    if (fits(4, 2)) return 4;
-    return f64 ? 4 : 3;
 }
 
 // D3Q19: single sweeps, two-step passes in 62-node columns or in 64-node lines.
@@ -929,7 +880,12 @@ int lbm_create(const lbm_desc *desc, lbm_ctx **out) {
     c->two = c->two_ok;   // on by default where it applies (bit-identical; lbm_tune re-decides)
     c->multi_ok = c->multi = dm.deg3 && c->dm.o32 && (dm.q == 9 || dm.eqr);
     c->multi_remap = c->two_remap = (desc->flags & LBM_FLAG_NO_XCD_REMAP) ? 0 : 1;
-    if (c->multi_ok && dm.q == 9) c->multi_shape = c->multi_auto = pick_multi(c);
+    if (c->multi_ok && dm.q == 9) {
+        const uint64_t ncu = cu_count(c);
+        c->multi_shape = c->multi_auto = pick_multi(dm.prec, g.nx, g.ny, ncu);
+        c->multi = !two_steps_fit_better(dm.prec, c->multi_shape, g.nx, g.ny, ncu, c->dm.nt, dm.sb && dm.src,
+                                         dm.unit && !dm.wall);
+    }
     if (dm.q == 19) pick_lines(c);
     {
         // the two-sweep adjoint: periodic D2Q9 only; its partial slots cover
@@ -1601,7 +1557,7 @@ int lbm_tune(lbm_ctx *c, int reps, void *stream, char *report, size_t report_len
             const int shape = i == 0 ? c->multi_auto : (i <= c->multi_auto ? i - 1 : i);
             multi_shape(c, shape, &mt, &mtr, &mnw);
             if (c->dm.q == 9 && shape != 3 && shape != 4 &&
-                multi_tiles(c, shape) > (shape < 3 ? 4ull : 8ull) * (uint64_t)(c->ncu > 0 ? c->ncu : 256))
+                multi_tiles(c->dm.prec, shape, c->g.nx, c->g.ny) > (shape < 3 ? 4 : 8) * cu_count(c))
                 continue;
             const int width = c->dm.q == 9 && shape >= 5 ? 34 - 2 * mt : (c->dm.q == 9 ? 66 - 2 * mt : 64);
             c->multi_shape = shape;

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lbm_pick.h"
+
 namespace lbm {
 
 constexpr int kBlock = 256;     // threads per workgroup (4 wave64)
@@ -151,10 +153,7 @@ hipError_t launch_reduce_final(const double *part, int nparts, double *out, hipS
 hipError_t launch_sweep2_q9(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
                             const void *pin, void *pout, int *flag, int shape, hipStream_t st);
 // Several time steps per pass, D2Q9 with 3-term polynomials
-// (sweep_multi_q9_*.hip), in shape `shape`: steps per pass, rows of the region
-// (tile and halo) and waves per workgroup; false past the last shape.  Shapes
-// 0 to 2 run 8, 6 and 4 steps with one row per wave (16 x 16), 3 and 4 six and
-// four steps on more rows.
+// (sweep_multi_q9_*.hip), in shape `shape` (multi_shape_of).
 hipError_t launch_sweep_multi_q9(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
                                  const void *pin, void *pout, int *flag, int shape, hipStream_t st);
 // The same with every step's state recorded: step s (from 0) goes to fout +
@@ -169,24 +168,6 @@ hipError_t launch_sweep_multi_q9_f32(const Dims &dm, const Geom &g, const void *
                                      const void *pin, void *pout, int *flag, int shape, hipStream_t st);
 hipError_t launch_sweep_multi_q9_f16(const Dims &dm, const Geom &g, const void *coefs, const void *fin, void *fout,
                                      const void *pin, void *pout, int *flag, int shape, hipStream_t st);
-inline bool multi_shape_of(int prec, int shape, int *steps, int *rows, int *waves, int *width = nullptr) {
-    constexpr int t[3][5][3] = {{{8, 16, 16}, {6, 16, 16}, {4, 16, 16}, {6, 32, 16}, {4, 16, 8}},     // FP64
-                                {{8, 16, 16}, {6, 16, 16}, {4, 16, 16}, {6, 32, 16}, {4, 32, 16}},    // FP32
-                                {{8, 16, 16}, {6, 16, 16}, {4, 16, 16}, {6, 48, 16}, {4, 32, 16}}};   // FP16
-    constexpr int half[3] = {8, 6, 4};   // steps of the 32-wide shapes, 16 rows on 8 waves
-    if (prec < 0 || prec > 2 || shape < 0 || shape >= 8) return false;
-    if (width) *width = shape < 5 ? 64 : 32;
-    if (shape >= 5) {
-        *steps = half[shape - 5];
-        *rows = 16;
-        *waves = 8;
-        return true;
-    }
-    *steps = t[prec][shape][0];
-    *rows = t[prec][shape][1];
-    *waves = t[prec][shape][2];
-    return true;
-}
 // tile shape `shape` of two-step passes (rows, waves per workgroup); false past the last
 bool two_step_shape_of(int prec, int shape, int *rows, int *waves);
 // Two time steps per pass, D3Q19 (sweep_d3q19.hip): columns of 62 x rows nodes,
