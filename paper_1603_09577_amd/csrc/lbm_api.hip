@@ -526,33 +526,12 @@ void pick_adj_shape(lbm_ctx *c) {
     c->adj_shape_auto = c->adj_shape;
 }
 
-// D3Q19: single sweeps, two-step passes in 62-node columns or in 64-node lines.
-// A pass has one workgroup per column and chunk of planes, a wave computes 64
-// nodes whether the grid has them or not, and the planes of the halo are extra.
-//  - It wins over single sweeps once enough nodes share that, more of them the
-//    emptier the lines are: with f the filled part of the lines, N f^2 separates
-//    the two.  us per step single / lines, FP64 with a source and walls, 56^3
-//    (134k) 12.7 / 14.2, 72^3 (118k) 23.2 / 26.4, 60^3 (190k) 15.2 / 14.8, 80^3
-//    (200k) 29.5 / 28.8; FP32 100 x 60^2 (220k) 11.3 / 11.9, 64^3 (262k) 9.1 / 9.4, 50 x
-//    100 x 80 (244k) 12.7 / 11.9, 64^2 x 80 (327k) 11.0 / 10.0; FP16 with walls 100^3 (610k) 19.2 / 18.9,
-//    80 x 120 x 140 (525k) 26.4 / 28.1; without, where single sweeps move half the
-//    bytes at full occupancy, 130^3 (1.0M) 31 / 43, 128^3 (2.1M) 30.5 / 30.0.
-//  - Lines where they save a column (256^3 FP32 291 against 325, FP64 82 against 108
-//    on 128^3).  Where they do not, a 62-node column is the better one in FP64 (its
-//    lines have an odd wave: 200 x 180 x 160 224 / 215, with a source 247 / 228), in
-//    FP32 with a source and no walls or beyond a million nodes (216 x 157 x 128 105 /
-//    82, 100 x 80 x 60 with a source 15.3 / 13.4; 96^3 without 18.4 / 19.6) and in FP16 with a
-//    source beyond four million (216 x 157 x 128 87 / 72; 130^3 43 / 46).
+// The D3Q19 pass a run starts with.
 void pick_lines(lbm_ctx *c) {
     if (!c->multi_ok) return;
-    const uint32_t nx = c->g.nx, n = c->g.N, lines = (nx + 63) / 64;
-    const double f = (double)nx / (64.0 * lines);
-    const bool src = c->dm.src && !c->dm.sb;
-    const double small = c->dm.prec == 0 ? 190e3 : (c->dm.prec == 1 ? 240e3 : (c->dm.wall ? 600e3 : 2e6));
-    if (n * f * f < small) { c->two = c->multi = false; return; }
-    if (lines < (nx + 61) / 62) return;
-    c->multi = !(c->dm.prec == 0 ||
-                 (c->dm.prec == 1 ? (src && !c->dm.wall) || n > 1000000u : src && n > 4000000u));
+    const Pass3 p = pick_pass3(c->dm.prec, c->g.nx, c->g.N, c->dm.src && !c->dm.sb, c->dm.wall);
+    if (p == Pass3::single) c->two = false;
+    c->multi = p == Pass3::lines;
 }
 
 // z planes per column of the D3Q19 pass.  Each workgroup lives for its chunk

@@ -1,4 +1,4 @@
-// Which pass a D2Q9 run starts with: pure functions of the grid, the storage
+// Which pass a run starts with: pure functions of the grid, the storage
 // type and the number of CUs (no HIP types, so that they run on the host alone).
 #pragma once
 
@@ -120,6 +120,41 @@ inline bool two_steps_fit_better(int prec, int shape, uint32_t nx, uint32_t ny, 
         case 1: return twice && tiles > 4 * ncu && (sb || (!plain && !beyond_cache));
         default: return (twice && tiles > 2 * ncu) || (half_more && tiles > 4 * ncu);
     }
+}
+
+// D3Q19: single sweeps, two-step passes in 62-node columns or in 64-node lines,
+// for n nodes on lines of nx (src: a Scheme-A source).
+// A pass has one workgroup per column and chunk of planes, a wave computes 64
+// nodes whether the grid has them or not, and the planes of the halo are extra.
+//  - It wins over single sweeps once enough nodes share that, more of them the
+//    emptier the lines are: with f the filled part of the lines (FP64: of the
+//    62-node columns where it takes those), N f^2 separates the two.  us per step single / lines, FP64 with a source and walls, 56^3
+//    (143k) 11.4 / 13.7, 72^3 (126k) 20.9 / 25.6, 58^3 (171k) 12.0 / 13.8, 60^3 (202k)
+//    14.3 / 14.0 (without 13.3 / 12.0), 80^3 (213k) 27.8 / 28.5 (25.6 / 24.4); periodic
+//    58^3 with a source 13.6 / 12.9,
+//    without 12.2 / 11.2, 60^2 x 30 (101k) 8.3 / 8.9; FP32 100 x 60^2 (220k) 11.3 / 11.9, 64^3 (262k) 9.1 / 9.4, 50 x
+//    100 x 80 (244k) 12.7 / 11.9, 64^2 x 80 (327k) 11.0 / 10.0; FP16 with walls 100^3 (610k) 19.2 / 18.9,
+//    80 x 120 x 140 (525k) 26.4 / 28.1; without, where single sweeps move half the
+//    bytes at full occupancy, 130^3 (1.0M) 31 / 43, 128^3 (2.1M) 30.5 / 30.0.
+//  - Lines where they save a column (256^3 FP32 291 against 325, FP64 82 against 108
+//    on 128^3).  Where they do not, a 62-node column is the better one in FP64 (its
+//    lines have an odd wave: 200 x 180 x 160 224 / 215, with a source 247 / 228), in
+//    FP32 without walls or beyond a million nodes (lines / columns 216 x 157 x 128
+//    105 / 82; periodic 60 x 80^2 10.3 / 9.7, 180 x 60 x 90 18.5 / 17.4, with a source
+//    100 x 80 x 60 15.3 / 13.4; with walls 96^3 17.5 / 18.7) and in FP16 with a
+//    source beyond four million (216 x 157 x 128 87 / 72; 130^3 43 / 46).
+enum class Pass3 { single, columns, lines };
+
+inline Pass3 pick_pass3(int prec, uint32_t nx, uint32_t n, bool src, bool wall) {
+    const uint32_t lines = (nx + 63) / 64, columns = (nx + 61) / 62;
+    const bool saves = lines < columns;
+    const double f = prec == 0 && !saves ? (double)nx / (62.0 * columns) : (double)nx / (64.0 * lines);
+    const double small64 = wall ? 190e3 : (src ? 165e3 : 130e3);
+    const double small = prec == 0 ? small64 : (prec == 1 ? 240e3 : (wall ? 600e3 : 2e6));
+    if (n * f * f < small) return Pass3::single;
+    if (saves) return Pass3::lines;
+    const bool narrow = prec == 0 || (prec == 1 ? !wall || n > 1000000u : src && n > 4000000u);
+    return narrow ? Pass3::columns : Pass3::lines;
 }
 
 }  // namespace lbm

@@ -11,7 +11,13 @@ F64, F32, F16 = 0, 1, 2
 MAIN = r"""
 #include <cstdio>
 #include "lbm_pick.h"
-int main() {
+int main(int argc, char **) {
+    if (argc > 1) {
+        int prec; unsigned nx, n, src, wall;
+        while (std::scanf("%d %u %u %u %u", &prec, &nx, &n, &src, &wall) == 5)
+            std::printf("%d\n", (int)lbm::pick_pass3(prec, nx, n, src, wall));
+        return 0;
+    }
     int prec; unsigned nx, ny, ncu, large, sb, plain;
     while (std::scanf("%d %u %u %u %u %u %u", &prec, &nx, &ny, &ncu, &large, &sb, &plain) == 7) {
         const int s = lbm::pick_multi(prec, nx, ny, ncu);
@@ -28,8 +34,8 @@ def pick(tmp_path_factory):
     src.write_text(MAIN)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
 
-    def run(rows):
-        out = subprocess.run([str(exe)], input="\n".join(" ".join(str(int(v)) for v in r) for r in rows), text=True,
+    def run(rows, *mode):
+        out = subprocess.run([str(exe), *mode], input="\n".join(" ".join(str(int(v)) for v in r) for r in rows), text=True,
                              capture_output=True, check=True).stdout.split("\n")
         return [tuple(int(v) for v in line.split()) for line in out if line]
     return run
@@ -69,3 +75,19 @@ def test_wide_and_small_grids_keep_their_passes(pick):
     rows += [(p, nx, ny, 256, 0, 1, 0) for p in (F64, F32, F16) for nx in (55, 60, 62, 110, 124) for ny in (1, 20, 64, 300, 700)]
     got = pick(rows)
     assert all(0 <= s < 8 and not t for s, t in got)
+
+
+def test_d3q19_passes(pick):
+    """(type, grid, source, walls) -> 0 single sweeps, 1 two steps in 62-node
+    columns, 2 in 64-node lines.  FP64 counts the fill of the columns it takes:
+    60 nodes fill 62-node ones better than lines."""
+    cases = {(F64, (60, 60, 60), 0, 1): 1, (F64, (60, 60, 60), 1, 1): 1, (F64, (60, 60, 60), 0, 0): 1,
+             (F64, (58, 58, 58), 0, 1): 0, (F64, (58, 58, 58), 0, 0): 1,
+             (F64, (58, 58, 58), 1, 0): 1, (F64, (56, 56, 56), 1, 0): 0, (F64, (60, 60, 30), 0, 0): 0, (F64, (56, 56, 56), 1, 1): 0, (F64, (72, 72, 72), 1, 1): 0,
+             (F64, (64, 64, 64), 1, 1): 2, (F64, (62, 62, 62), 1, 1): 1, (F64, (128, 128, 128), 1, 1): 2,
+             (F64, (200, 180, 160), 0, 1): 1, (F64, (40, 40, 40), 0, 1): 0,
+             (F32, (60, 60, 60), 0, 1): 0, (F32, (64, 64, 64), 0, 1): 2, (F32, (100, 80, 60), 1, 0): 1, (F32, (60, 80, 80), 0, 0): 1, (F32, (96, 96, 96), 0, 1): 2,
+             (F32, (256, 256, 256), 0, 1): 2, (F32, (216, 157, 128), 0, 1): 1,
+             (F16, (100, 100, 100), 0, 1): 2, (F16, (216, 157, 128), 1, 1): 1, (F16, (100, 100, 100), 0, 0): 0}
+    got = pick([(p, n[0], n[0] * n[1] * n[2], s, w) for p, n, s, w in cases], "3")
+    assert [g[0] for g in got] == list(cases.values())
