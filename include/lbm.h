@@ -542,7 +542,8 @@ int lbm_batch_tune(lbm_batch *b, int reps, int use_cache, void *stream, char *re
  * Batches without a source whose polynomials all have degree <= 2 also offer
  * several time steps per launch (the passes of lbm_set_two_step and
  * lbm_set_multi_step, one workgroup per tile of an instance, bit-identical to
- * single sweeps), and start in one of them.  Steps per launch, tile rows x
+ * single sweeps), and start in one of them unless the instances are so narrow
+ * or small that most of the tiles would be empty.  Steps per launch, tile rows x
  * waves: for 4- and 2-byte storage shape 4 = 2 steps, 14 x 8, shape 5 = 2,
  * 6 x 4, shape 6 = 6, 22 x 16, shape 7 = 4, 10 x 8; for FP64 shape 4 = 2,
  * 6 x 8, shape 5 = 4, 10 x 8, shape 6 = 6, 22 x 16.  The grid argument is

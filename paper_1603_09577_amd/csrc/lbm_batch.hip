@@ -66,8 +66,8 @@ struct PassShape {
 constexpr PassShape kPass4[] = {{2, 14, 8}, {2, 6, 4}, {6, 22, 16}, {4, 10, 8}};
 constexpr PassShape kPass8[] = {{2, 6, 8}, {4, 10, 8}, {6, 22, 16}};
 constexpr int kMaxPass = 4, kNumPass4 = 4, kNumPass8 = 3;
-// the shape a batch with passes starts with (the fastest of them on 128
-// instances of 32^2 to 512^2, FP32 and FP64)
+// the pass shape a batch starts with where passes win (the fastest of them on
+// 128 instances of 32^2 to 512^2, FP32 and FP64)
 constexpr int kDefault4 = 2, kDefault8 = 1;
 
 template <typename TS, typename TC, bool SRC, bool KVAR, int WG, int NPT, int NP>
@@ -541,7 +541,15 @@ int lbm_batch_create(const lbm_desc *descs, int count, lbm_batch **out) {
         e = hipMalloc((void **)&b->d_tiles2[s], sizeof(uint2) * tl.size());
         if (e == hipSuccess) e = hipMemcpy(b->d_tiles2[s], tl.data(), sizeof(uint2) * tl.size(), hipMemcpyHostToDevice);
     }
-    if (b->npass) b->shape = kNumShapes + (b->prec == 0 ? kDefault8 : kDefault4);
+    if (b->npass) {
+        int dev = 0, ncu = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
+            ncu = 256;
+        const int i = b->prec == 0 ? kDefault8 : kDefault4;
+        if (batch_passes_win(b->prec, b->total_nodes, b->ntiles[0], b->ntiles2[i], (uint64_t)ncu))
+            b->shape = kNumShapes + i;
+    }
     if (e != hipSuccess) {
         lbm_batch_destroy(b);
         std::string m = std::string("batch setup: ") + hipGetErrorString(e);

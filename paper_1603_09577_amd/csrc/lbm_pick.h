@@ -157,4 +157,18 @@ inline Pass3 pick_pass3(int prec, uint32_t nx, uint32_t n, bool src, bool wall) 
     return narrow ? Pass3::columns : Pass3::lines;
 }
 
+// Whether a batch starts with the passes of its default shape rather than with
+// single sweeps.  A tile of a pass costs the same however little of it is grid:
+// 3.7 ns per step in FP32, 4.2 in FP16 (54 x 22 nodes), 4.1 in FP64 (58 x 10); a
+// single sweep costs 13, 9 and 23 ps per node and about 0.7 ns per 256-node block.
+// So a tile pays from 285, 465 or 180 nodes' worth of single sweeps on, and
+// narrow or tiny instances do not fill that.  Up to two tiles per CU a launch
+// costs more than the tiles.  us per step single sweeps / passes: 400 of 2 x 500
+// FP32 6.1 / 35, FP64 11.0 / 85; 5000 of 8^2 7.1 / 17.2; 300 of 10 x 300 12.0 / 16.2; 4000 of
+// 16^2 FP16 10.6 / 15.9, FP32 15.1 / 15.0; 1500 of 32^2 FP16 13.3 / 12.7; 64 of 4^2 3.8 / 1.7.
+inline bool batch_passes_win(int prec, uint64_t nodes, uint64_t blocks, uint64_t tiles, uint64_t ncu) {
+    const uint64_t tile_worth = prec == 0 ? 180 : (prec == 1 ? 285 : 465);
+    return tiles <= 2 * ncu || tiles * tile_worth <= nodes + 50 * blocks;
+}
+
 }  // namespace lbm

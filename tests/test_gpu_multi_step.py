@@ -138,6 +138,24 @@ def test_batch_passes_identical(prec, shape, rates):
         b.set_shape(shape + (2 if prec != "f64" else 1) if shape == 6 else 9, 0, 1)
 
 
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+def test_batch_of_narrow_instances_starts_with_single_sweeps(prec):
+    """Instances that leave most of every tile empty start with single sweeps,
+    bit for bit the passes of the same batch."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    specs = [_spec(2, 500, prec, source="none")] * 60
+    phi0 = [W.noise_field((500, 2), i) for i in range(60)]
+    a, b = lbm.Batch(specs).init(phi0), lbm.Batch(specs).init(phi0)
+    assert a.get_shape()["npt"] > 0
+    b.set_shape(6)
+    a.step(13)
+    b.step(13)
+    assert torch.equal(a.phi(), b.phi())
+    assert lbm.Batch(specs[:2]).get_shape()["npt"] < 0        # few tiles: a launch costs more
+
+
 @pytest.mark.parametrize("n,prec,wall,source", [
     ((64, 13, 9), "f32", True, "none"), ((128, 20, 22), "f64", True, "A"), ((65, 27, 11), "f32", False, "A"),
     ((63, 7, 5), "f16", True, "A"), ((3, 2, 2), "f32", True, "none"), ((1, 1, 3), "f64", False, "B"),

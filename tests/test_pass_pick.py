@@ -11,7 +11,13 @@ F64, F32, F16 = 0, 1, 2
 MAIN = r"""
 #include <cstdio>
 #include "lbm_pick.h"
-int main(int argc, char **) {
+int main(int argc, char **argv) {
+    if (argc > 1 && argv[1][0] == 'b') {
+        int prec; unsigned long long nodes, blocks, tiles;
+        while (std::scanf("%d %llu %llu %llu", &prec, &nodes, &blocks, &tiles) == 4)
+            std::printf("%d\n", (int)lbm::batch_passes_win(prec, nodes, blocks, tiles, 256));
+        return 0;
+    }
     if (argc > 1) {
         int prec; unsigned nx, n, src, wall;
         while (std::scanf("%d %u %u %u %u", &prec, &nx, &n, &src, &wall) == 5)
@@ -91,3 +97,17 @@ def test_d3q19_passes(pick):
              (F16, (100, 100, 100), 0, 1): 2, (F16, (216, 157, 128), 1, 1): 1, (F16, (100, 100, 100), 0, 0): 0}
     got = pick([(p, n[0], n[0] * n[1] * n[2], s, w) for p, n, s, w in cases], "3")
     assert [g[0] for g in got] == list(cases.values())
+
+
+def test_batches_of_narrow_or_tiny_instances(pick):
+    """(type, nx, ny, instances) -> whether the batch starts with passes."""
+    cases = {(F32, 2, 500, 400): 0, (F64, 2, 500, 400): 0, (F16, 500, 2, 400): 0, (F64, 500, 2, 400): 0,
+             (F32, 8, 8, 5000): 0, (F32, 4, 4, 20000): 0, (F32, 10, 300, 300): 0, (F64, 16, 16, 4000): 0,
+             (F16, 16, 16, 4000): 0, (F16, 24, 24, 2000): 0, (F32, 4, 4, 64): 1, (F64, 8, 8, 400): 1,
+             (F32, 32, 32, 1500): 1, (F16, 32, 32, 1500): 1, (F64, 32, 32, 1500): 1, (F64, 64, 64, 400): 1,
+             (F16, 64, 64, 400): 1, (F32, 60, 400, 40): 1, (F64, 60, 400, 40): 1, (F32, 300, 300, 128): 1}
+    rows = []
+    for p, nx, ny, k in cases:
+        tw, th = (58, 10) if p == F64 else (54, 22)
+        rows.append((p, nx * ny * k, -(-nx * ny // 256) * k, -(-nx // tw) * -(-ny // th) * k))
+    assert [g[0] for g in pick(rows, "b")] == list(cases.values())
