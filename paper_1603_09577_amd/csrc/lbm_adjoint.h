@@ -477,7 +477,7 @@ __device__ __forceinline__ constexpr int shared_rows_first(int j) {
 // 33.5; FP32 10 x 12 512^2 5.5 -> 5.2, 6 x 4 400^2 4.8 -> 4.1.
 template <typename TS, typename TC, bool SRC, bool KVAR, int NP, int TH, int NW>
 __global__ void __launch_bounds__(NW * 64)
-__attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 && NP <= 4 && TH == 6 ? 3 : 1, 8)))
+__attribute__((amdgpu_waves_per_eu(sizeof(TC) != 8 ? 1 : (NP > 4 ? 2 : (TH == 6 ? 3 : 1)), 8)))
 k_adjoint2(const Geom g, const Coefs<TC> *__restrict__ cfa, const TS *__restrict__ f1,
            const typename HistType<TS>::T *__restrict__ p1, const TS *__restrict__ f0,
            const typename HistType<TS>::T *__restrict__ p0, const TC *__restrict__ psi_next,
