@@ -468,7 +468,9 @@ __device__ __forceinline__ constexpr int shared_rows_first(int j) {
 // FP64 6-row tiles with short polynomials are held to 3 waves per SIMD (168
 // registers), what their workgroup memory allows anyway (3 workgroups of 4
 // waves per CU); with 9-term polynomials that limit would spill.  10-row
-// tiles fit 2 workgroups per CU, and take no register limit.
+// tiles fit 2 workgroups per CU, and take no register limit.  9-term FP64 kernels
+// are held to 2 waves per SIMD: left alone, those with K(phi) and a source took
+// 258 registers, one wave (1024^2 10 x 4 56.4 -> 45.2, 6 x 4 65.0 -> 49.8).
 // Bound by memory on large grids (1024^2 FP64: 330 MB of states, psi and pi per
 // pair, 5 TB/s) and by a wave's chain of loads and arithmetic on small ones,
 // so each row's loads go ahead of the arithmetic of the one before.  us per
