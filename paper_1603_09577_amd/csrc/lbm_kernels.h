@@ -980,6 +980,12 @@ __device__ __forceinline__ void sweep2_tile(const Geom &g, const Coefs<TC> *__re
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int nx = (int)g.nx, ny = (int)g.ny;
     bool bad = false;
+    // The coefficients of a row.  9-term kernels fetch them for each row: kept
+    // over the rows of a wave they outnumber the scalar registers and travel
+    // through lanes of vector registers (130 to 210 of them in FP64; us per step
+    // 1024^2 FP64 with a source 23.0 -> 20.4, 2048^2 FP16 without 24.2 -> 22.0; 4-term
+    // kernels lose by it, 128^2 FP64 2.60 -> 2.78).
+    auto row_cf = [&] { return cf + (NP == kMaxP ? opaque_zero() : 0u); };
     // phase 1: the tile and its halo, coordinates x0 - 1 + lane and y0 - 1 + r.
     // A population with velocity c comes from column x - c_x of row y - c_y
     // (periodic).  The three source columns are byte offsets fixed per lane;
@@ -1030,7 +1036,7 @@ __device__ __forceinline__ void sweep2_tile(const Geom &g, const Coefs<TC> *__re
                 h[k] = wl ? -(TC)hs[i][k] + cf->ew[cy == 1 ? 0 : 1][k] : (TC)hs[i][k];
             }
             TC out[9];
-            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB>(cf, h, ps[i], 0u, nullptr, nullptr, false, out,
+            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB>(row_cf(), h, ps[i], 0u, nullptr, nullptr, false, out,
                                                                         HAND ? &lev[HAND ? i : 0] : nullptr);
 #pragma unroll
             for (int k = 0; k < 9; ++k) lf[k][r][lane] = to_store<TS>(out[k]);
@@ -1061,7 +1067,7 @@ __device__ __forceinline__ void sweep2_tile(const Geom &g, const Coefs<TC> *__re
             }
             const TC pp_off = SRC ? (TC)*at<true>(pin, n) : TC(0);
             TC out[9];
-            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB>(cf, h, pp_off, n, nullptr, nullptr, false, out,
+            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB>(row_cf(), h, pp_off, n, nullptr, nullptr, false, out,
                                                                         HAND ? &lev[HAND ? i : 0] : nullptr);
 #pragma unroll
             for (int k = 0; k < 9; ++k) lf[k][r][lane] = to_store<TS>(out[k]);
@@ -1085,7 +1091,7 @@ __device__ __forceinline__ void sweep2_tile(const Geom &g, const Coefs<TC> *__re
             }
             const TC pp_off = (SRC && !HAND) ? (TC)lp[HAND ? 0 : r][lane] : TC(0);
             TC out[9];
-            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB>(cf, h, pp_off, 0u, nullptr, nullptr, false, out,
+            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB>(row_cf(), h, pp_off, 0u, nullptr, nullptr, false, out,
                                                                         nullptr, prev);
             bad |= !__builtin_isfinite(phio);
             if (x < nx && y < ny) {
