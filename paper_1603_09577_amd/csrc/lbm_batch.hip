@@ -235,7 +235,8 @@ PassShape pass_shape(const lbm_batch *b, int i) { return b->prec == 0 ? kPass8[i
 bool is_pass(const lbm_batch *b) { return b->shape >= kNumShapes; }
 
 // one sweep; single-sweep shape `shape` (a two-step batch uses shape 0 for
-// an odd remaining step)
+// an odd remaining step); with 3-term polynomials the kernels have the bits of
+// the passes and of the instance alone
 hipError_t batch_sweep_launch(lbm_batch *b, const void *fin, void *fout, hipStream_t st, int shape) {
     const TileShape sh = kShapes[shape];
     const uint32_t nt = b->ntiles[shape];
@@ -244,7 +245,9 @@ hipError_t batch_sweep_launch(lbm_batch *b, const void *fin, void *fout, hipStre
     const uint32_t nblk = (nt + chunk - 1) / chunk;
     const uint2 *tl = b->d_tiles[shape];
 #define LBM_BL(TS, TC, S, K, WG, NPT)                                                                   \
-    if (b->lowdeg) LBM_BL_NP(TS, TC, S, K, WG, NPT, 4) else LBM_BL_NP(TS, TC, S, K, WG, NPT, 9)
+    if (b->deg3) LBM_BL_NP(TS, TC, S, K, WG, NPT, 3)                                                     \
+    else if (b->lowdeg) LBM_BL_NP(TS, TC, S, K, WG, NPT, 4)                                             \
+    else LBM_BL_NP(TS, TC, S, K, WG, NPT, 9)
 #define LBM_BL_NP(TS, TC, S, K, WG, NPT, NP)                                                            \
     hipLaunchKernelGGL((k_batch_sweep<TS, TC, S, K, WG, NPT, NP>), dim3(nblk), dim3(WG), 0, st,         \
                        b->d_inst, (const Coefs<TC> *)b->d_coefs, tl, nt, chunk, b->remap,               \

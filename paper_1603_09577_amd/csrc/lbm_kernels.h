@@ -640,7 +640,7 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
         const TC wb2 = TC(w2 / w1) * wb1;
         constexpr int NC = PolyLen<NP>::NC, NPL = D * (D - 1) / 2;
         TC ea[D], es[NPL], eo[NPL];
-        if constexpr (NC <= 6) {
+        if constexpr (NP <= 3) {
 #pragma unroll
             for (int a = 0; a < D; ++a) ea[a] = poly<NC, D == 2>(cf->ce[a], phi);
 #pragma unroll
@@ -649,8 +649,9 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
                 eo[i] = poly<NC, D == 2>(cf->ce[6 + i], phi);
             }
         } else {
-            // long polynomials: one Horner chain per tensor entry costs less
-            // than one per even part
+            // longer polynomials: one Horner chain per tensor entry costs less
+            // than one per even part (4-term, us per step 128^2 FP64 2.60 -> 2.47,
+            // 500 x 400 FP32 3.83 -> 3.76)
             TC E[6];
 #pragma unroll
             for (int i = 0; i < 6; ++i) {
