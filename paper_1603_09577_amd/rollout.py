@@ -3,10 +3,12 @@
 ``rollout(sim, phi0, k0, nsteps)`` runs the fused sweep nsteps times and
 returns phi(T); its backward runs the hand-written reversed sweep
 (lbm_adjoint_step).  Without ``seg``, the forward pass keeps all T states where
-they take at most an eighth of the memory that is free at that moment, and
-the backward pass only walks them: 512^2 FP64 with a source, 64 steps (1.3 GB),
-1290 us instead of 1500.  Otherwise two-level checkpointing: a copy of the
-state every ``seg`` steps (ceil(sqrt(T)) by default) in the forward pass, and
+they take at most a quarter of what is free beyond half of the device's memory
+(an eighth of an empty device; rollouts that wait for their backward together
+leave that half to the program), and the backward pass only walks them: 512^2
+FP64 with a source, 64 steps (1.3 GB), 1290 us instead of 1500.  They are saved
+tensors of the graph and go with it.  Otherwise two-level checkpointing: a copy
+of the state every ``seg`` steps (ceil(sqrt(T)) by default) in the forward pass, and
 in the backward pass each segment is recomputed into a ring of seg states and
 then walked backwards.  Memory: about 2 sqrt(T) states.  Where two reversed
 sweeps per launch apply (lbm_adjoint_pair_ok) and a timed trial finds them
@@ -44,8 +46,8 @@ class LbmRollout(torch.autograd.Function):
         sim.init(phi0.detach())
         checkpoints = []
         t = 0
-        ctx.states = _record(sim, nsteps) if keep_all else None
-        if ctx.states:
+        states = _record(sim, nsteps) if keep_all else ()
+        if states:
             t = nsteps
         while t < nsteps:
             which, _ = sim.current()
@@ -58,12 +60,12 @@ class LbmRollout(torch.autograd.Function):
         ctx.pairs = pairs
         ctx.k0_len = k0.numel()
         ctx.k0_device = k0.device
-        ctx.save_for_backward(phi0.detach())
+        ctx.save_for_backward(phi0.detach(), *states)
         return phiT
 
     @staticmethod
     def backward(ctx, gphi):
-        (phi0,) = ctx.saved_tensors
+        phi0, *states = ctx.saved_tensors
         sim, seg = ctx.sim, ctx.seg
         gphi = gphi.to(torch.float64).contiguous()
         if ctx.pairs == "auto":
@@ -73,7 +75,7 @@ class LbmRollout(torch.autograd.Function):
         cur_psi, pi = sim.adjoint_buffers()
         psi_other, pi_other = sim.adjoint_buffers()
         sim.adjoint_seed(gphi, cur_psi, pi)
-        for ring in _segments(ctx, sim, seg):
+        for ring in _segments(ctx, states, sim, seg):
             i = len(ring) - 1
             while i >= 0:
                 if use_pairs and i >= 1:
@@ -93,21 +95,22 @@ class LbmRollout(torch.autograd.Function):
 
 
 def _record(sim, nsteps):
-    """The states before each of the next nsteps steps, which are taken, or None
+    """The states before each of the next nsteps steps, which are taken, or ()
     where they do not fit or the run does not record."""
     dev = sim.device
     need = nsteps * (sim.f_bytes + sim.p_bytes)
-    if nsteps < 1 or 8 * need > torch.cuda.mem_get_info(dev)[0]:
-        return None
+    free, total = torch.cuda.mem_get_info(dev)
+    if nsteps < 1 or 4 * need > free - total // 2:
+        return ()
     fs = torch.empty((nsteps, sim.f_bytes), dtype=torch.uint8, device=dev)
     ps = torch.empty((nsteps, sim.p_bytes), dtype=torch.uint8, device=dev)
-    return (fs, ps) if sim.step_record(fs, ps, nsteps) else None
+    return (fs, ps) if sim.step_record(fs, ps, nsteps) else ()
 
 
-def _segments(ctx, sim, seg):
+def _segments(ctx, states, sim, seg):
     """Lists of consecutive (state, history), the last steps first."""
-    if ctx.states:
-        yield list(zip(*ctx.states))
+    if states:
+        yield list(zip(*states))
         return
     # the states of a segment: its checkpoint, then the recomputed ones
     rows = max(1, min(seg, ctx.nsteps) - 1)

@@ -341,3 +341,63 @@ def test_rollout_function_called_directly():
         (ph ** 2).sum().backward()
         grads.append(p0.grad)
     assert torch.equal(*grads)
+
+
+def _rollout_inputs(nx=256, ny=256, prec="f64"):
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    spec = _spec(nx, ny, prec)
+    p0 = torch.tensor(W.noise_field((ny, nx), 4), device="cuda", requires_grad=True)
+    k = spec["k0"]
+    k0 = torch.tensor([k[0][0], k[0][1], k[1][1]], dtype=torch.float64, requires_grad=True)
+    return lbm.Lbm(spec), p0, k0
+
+
+def test_recorded_states_go_with_the_graph():
+    """The kept states are saved tensors: released after the backward while
+    phi(T) is still referenced, refused to a second backward, and seen by
+    saved-tensor hooks."""
+    import torch
+
+    from paper_1603_09577_amd.rollout import rollout
+    s, p0, k0 = _rollout_inputs()
+    T = 24
+    (rollout(s, p0, k0, T, pairs=False) ** 2).sum().backward()       # allocates what the gradients take
+    grad = p0.grad.clone()
+    p0.grad = k0.grad = None
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_allocated()
+    ph = rollout(s, p0, k0, T, pairs=False)
+    kept = T * (s.f_bytes + s.p_bytes)
+    assert torch.cuda.memory_allocated() - before >= kept
+    loss = (ph ** 2).sum()
+    loss.backward()
+    assert torch.cuda.memory_allocated() - before < kept / 4
+    assert torch.equal(p0.grad, grad)
+    with pytest.raises(RuntimeError):
+        loss.backward()
+    sizes = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: (sizes.append(t.numel()), t.cpu())[1], lambda t: t.cuda()):
+        ph = rollout(s, p0, k0, T, pairs=False)
+        loss = (ph ** 2).sum()
+    assert T * s.f_bytes in sizes and T * s.p_bytes in sizes
+    p0.grad = None
+    loss.backward()
+    assert torch.equal(p0.grad, grad)
+
+
+def test_rollouts_together_leave_half_of_the_memory(monkeypatch):
+    """What one rollout keeps counts for the next: at most a quarter of what is
+    free beyond half of the device."""
+    import torch
+
+    from paper_1603_09577_amd import rollout as R
+    s, p0, k0 = _rollout_inputs(64, 48)
+    s.init(p0.detach())
+    T = 8
+    need = T * (s.f_bytes + s.p_bytes)
+    for free, total, keeps in ((8 * need, 8 * need, True), (8 * need - 1, 8 * need, False),
+                               (100 * need, 192 * need, True), (99 * need, 192 * need, False)):
+        monkeypatch.setattr(torch.cuda, "mem_get_info", lambda dev=None, v=(free, total): v)
+        assert bool(R._record(s, T)) == keeps, (free, total)
