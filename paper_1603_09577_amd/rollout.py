@@ -102,8 +102,11 @@ def _record(sim, nsteps):
     free, total = torch.cuda.mem_get_info(dev)
     if nsteps < 1 or 4 * need > free - total // 2:
         return ()
-    fs = torch.empty((nsteps, sim.f_bytes), dtype=torch.uint8, device=dev)
-    ps = torch.empty((nsteps, sim.p_bytes), dtype=torch.uint8, device=dev)
+    try:
+        fs = torch.empty((nsteps, sim.f_bytes), dtype=torch.uint8, device=dev)
+        ps = torch.empty((nsteps, sim.p_bytes), dtype=torch.uint8, device=dev)
+    except torch.OutOfMemoryError:     # the process may have less than the device has free
+        return ()
     return (fs, ps) if sim.step_record(fs, ps, nsteps) else ()
 
 

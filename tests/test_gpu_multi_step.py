@@ -401,3 +401,29 @@ def test_rollouts_together_leave_half_of_the_memory(monkeypatch):
                                (100 * need, 192 * need, True), (99 * need, 192 * need, False)):
         monkeypatch.setattr(torch.cuda, "mem_get_info", lambda dev=None, v=(free, total): v)
         assert bool(R._record(s, T)) == keeps, (free, total)
+
+
+def test_rollout_within_a_memory_limit_of_the_process():
+    """Where the process may not allocate what the device has free, the rollout
+    keeps checkpoints instead of all states, with the same gradients."""
+    import torch
+
+    from paper_1603_09577_amd.rollout import rollout
+    s, p0, k0 = _rollout_inputs(256, 256)
+    T = 64                                          # 320 MB of states, 60 MB with checkpoints
+
+    def grads():
+        p0.grad = k0.grad = None
+        (rollout(s, p0, k0, T, pairs=False) ** 2).sum().backward()
+        torch.cuda.synchronize()
+        return p0.grad.clone(), k0.grad.clone()
+
+    want = grads()
+    torch.cuda.empty_cache()
+    total = torch.cuda.mem_get_info()[1]
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + 200e6) / total)
+    try:
+        got = grads()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
