@@ -530,8 +530,8 @@ int lbm_batch_get_phi(lbm_batch *b, double *phi_arena, void *stream);
  * and nodes per thread, persistent grid size, XCD-aware order) over `reps`
  * sweeps of the bound batch, keeps the fastest, then re-initialises the
  * state from the phi0 arena given to lbm_batch_init (step counter back to 0).
- * With use_cache, a previous decision for the same batch signature is read
- * from (and new ones appended to) the text file named by $LBM_TUNE_CACHE,
+ * With use_cache, a previous decision for the same batch signature (sizes,
+ * precision, kernels and the shapes on offer) is read from (and new ones appended to) the text file named by $LBM_TUNE_CACHE,
  * default ~/.cache/lbm_batch_tune.txt.  A report of the timings is written
  * into `report` (may be NULL). */
 int lbm_batch_tune(lbm_batch *b, int reps, int use_cache, void *stream, char *report, size_t report_len);

@@ -66,6 +66,7 @@ struct PassShape {
 constexpr PassShape kPass4[] = {{2, 14, 8}, {2, 6, 4}, {6, 22, 16}, {4, 10, 8}};
 constexpr PassShape kPass8[] = {{2, 6, 8}, {4, 10, 8}, {6, 22, 16}};
 constexpr int kMaxPass = 4, kNumPass4 = 4, kNumPass8 = 3;
+constexpr int kShapeTable = 2;   // version of the shape tables in the tuner's cache: raise it when they change
 // the pass shape a batch starts with where passes win (the fastest of them on
 // 128 instances of 32^2 to 512^2, FP32 and FP64)
 constexpr int kDefault4 = 2, kDefault8 = 1;
@@ -499,16 +500,6 @@ int lbm_batch_create(const lbm_desc *descs, int count, lbm_batch **out) {
         delete b;
         return api_fail(LBM_E_INVALID, "batch too large");
     }
-    {
-        // short key: precision, flags, FNV-1a of the size list
-        std::string s = key.str();
-        uint64_t h = 1469598103934665603ull;
-        for (char c : s) { h ^= (unsigned char)c; h *= 1099511628211ull; }
-        char buf[64];
-        std::snprintf(buf, sizeof(buf), "p%d_s%d_k%d_n%d_%016llx", b->prec, (int)b->src, (int)b->kvar, count,
-                      (unsigned long long)h);
-        b->key = buf;
-    }
     hipError_t e = hipMalloc((void **)&b->d_inst, sizeof(BatchInst) * count);
     if (e == hipSuccess) e = hipMalloc(&b->d_coefs, coefs.size());
     if (e == hipSuccess) e = hipMalloc((void **)&b->d_flag, 256);
@@ -543,6 +534,19 @@ int lbm_batch_create(const lbm_desc *descs, int count, lbm_batch **out) {
         b->ntiles2[s] = (uint32_t)tl.size();
         e = hipMalloc((void **)&b->d_tiles2[s], sizeof(uint2) * tl.size());
         if (e == hipSuccess) e = hipMemcpy(b->d_tiles2[s], tl.data(), sizeof(uint2) * tl.size(), hipMemcpyHostToDevice);
+    }
+    {
+        // short key: the table of shapes, precision, what chooses the kernels, the
+        // passes offered, FNV-1a of the size list.  An entry of another table or
+        // another set of kernels misses and is tuned anew.
+        const std::string sizes = key.str();
+        uint64_t h = 1469598103934665603ull;
+        for (char c : sizes) { h ^= (unsigned char)c; h *= 1099511628211ull; }
+        char buf[96];
+        std::snprintf(buf, sizeof(buf), "t%d_p%d_s%d_k%d_d%d_u%d_o%d_n%d_%016llx", kShapeTable, b->prec, (int)b->src,
+                      (int)b->kvar, b->deg3 ? 2 : (b->lowdeg ? 3 : 8), (int)b->unit, b->npass, count,
+                      (unsigned long long)h);
+        b->key = buf;
     }
     if (b->npass) {
         int dev = 0, ncu = 0;

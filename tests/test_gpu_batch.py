@@ -159,3 +159,30 @@ def test_tuner_cache_roundtrip(tmp_path, monkeypatch):
     second = b2.tune(reps=1, use_cache=True)
     assert second.startswith("cached")
     assert b2.get_shape() == shape
+
+
+def test_tuner_cache_misses_other_shape_tables_and_kernels(tmp_path, monkeypatch):
+    """A cached shape is taken only by a batch that was offered the same shapes
+    of the same table for the same kernels: not from the entries of an older
+    table, nor from a batch of the same sizes with longer polynomials."""
+    from paper_1603_09577_amd import lbm
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("LBM_TUNE_CACHE", str(path))
+    sizes = [(40, 30), (64, 64), (100, 21)]
+    specs = [W.spec_nonlinear_2d(nx, ny, source=False, precision="f32") for nx, ny in sizes]
+    phis = [W.noise_field((ny, nx), 7) for nx, ny in sizes]
+    # the entry of the first table: single sweeps in shape 1
+    h = 1469598103934665603
+    for c in "".join(f"{nx}x{ny}," for nx, ny in sizes).encode():
+        h = ((h ^ c) * 1099511628211) % (1 << 64)
+    path.write_text(f"p1_s0_k1_n3_{h:016x} 1 0 1\n")
+    long = [dict(s, kpoly=[1.0, 0.0, 1.0, 0.01]) for s in specs]
+    rates = [dict(s, s=[0.0] + [1.3] * 8) for s in specs]
+    for batch in (long, specs, rates):
+        b = lbm.Batch(batch).init(phis)
+        assert not b.tune(reps=2, use_cache=True).startswith("cached")
+        shape = b.get_shape()
+        again = lbm.Batch(batch).init(phis)
+        assert again.tune(reps=2, use_cache=True).startswith("cached")
+        assert again.get_shape() == shape
+    assert len(path.read_text().splitlines()) == 4
