@@ -208,6 +208,7 @@ struct lbm_batch {
     uint2 *d_tiles2[kMaxPass] = {nullptr, nullptr, nullptr, nullptr};
     uint32_t ntiles2[kMaxPass] = {0, 0, 0, 0};
     int npass = 0;          // pass shapes available (0: no source-free 3-term batch)
+    bool passes_win = false;   // and the batch starts with one (batch_passes_win)
     int *d_flag = nullptr;
     int shape = 0;          // index into kShapes, or kNumShapes + a pass shape
     uint32_t grid = 0;      // workgroups per sweep (0 = one per tile)
@@ -554,8 +555,8 @@ int lbm_batch_create(const lbm_desc *descs, int count, lbm_batch **out) {
             hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
             ncu = 256;
         const int i = b->prec == 0 ? kDefault8 : kDefault4;
-        if (batch_passes_win(b->prec, b->total_nodes, b->ntiles[0], b->ntiles2[i], (uint64_t)ncu))
-            b->shape = kNumShapes + i;
+        b->passes_win = batch_passes_win(b->prec, b->total_nodes, b->ntiles[0], b->ntiles2[i], (uint64_t)ncu);
+        if (b->passes_win) b->shape = kNumShapes + i;
     }
     if (e != hipSuccess) {
         lbm_batch_destroy(b);
@@ -712,11 +713,10 @@ int lbm_batch_tune(lbm_batch *b, int reps, int use_cache, void *stream, char *re
         for (int s = 0; s < kNumShapes; ++s)
             for (uint32_t gr : grids)
                 for (int rm = 0; rm < 2; ++rm) {
-                    // with passes to choose from (46.9 us per step against 148
-                    // for the best single sweep on 128 instances of FP32), the
-                    // persistent grids of single sweeps are not worth their
-                    // trials
-                    if (b->npass && gr) continue;
+                    // where passes win (46.9 us per step against 148 for the best
+                    // single sweep on 128 instances of FP32), the persistent
+                    // grids of single sweeps are not worth their trials
+                    if (b->passes_win && gr) continue;
                     b->shape = s; b->grid = gr; b->remap = rm;
                     // sweeps read the current state and write the other buffer only
                     hipError_t e = batch_sweep_launch(b, b->f[b->cur], b->f[b->cur ^ 1], st, s);

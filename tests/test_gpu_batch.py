@@ -186,3 +186,15 @@ def test_tuner_cache_misses_other_shape_tables_and_kernels(tmp_path, monkeypatch
         assert again.tune(reps=2, use_cache=True).startswith("cached")
         assert again.get_shape() == shape
     assert len(path.read_text().splitlines()) == 4
+
+
+def test_tuner_tries_persistent_grids_where_single_sweeps_win():
+    """Narrow instances, which passes serve badly, get every launch form of
+    single sweeps tried; the others only one workgroup per tile."""
+    from paper_1603_09577_amd import lbm
+    for (nx, ny, count), persistent in (((2, 500, 60), True), ((64, 64, 8), False)):
+        spec = W.spec_nonlinear_2d(nx, ny, source=False, precision="f32")
+        b = lbm.Batch([spec] * count).init([W.noise_field((ny, nx), i) for i in range(count)])
+        rep = b.tune(reps=1)
+        assert (" grid 1024 " in rep) == persistent, rep
+        assert "steps per launch" in rep
