@@ -291,10 +291,12 @@ int lbm_two_step_shape(const lbm_ctx *ctx, int shape, int *rows, int *waves);
  * in pairs (their lengths may differ), so state and history end where single
  * sweeps leave them; the last one to three steps of a call use single sweeps.
  * On by default where it applies, in a shape picked for the grid, and
- * launched directly (no graphs); small D3Q19 grids start with single sweeps,
- * and where lines save no column mostly with lbm_set_two_step's.  lbm_tune times
- * the shapes; lbm_set_two_step turns it off.  Not used with per-node fields or
- * Remark III.
+ * launched directly (no graphs); D2Q9 grids whose width fits 62-node columns
+ * much better start with lbm_set_two_step's passes, small D3Q19 grids with single
+ * sweeps, and D3Q19 where lines save no column mostly with lbm_set_two_step's.  lbm_tune times
+ * the shapes; lbm_set_two_step turns it off.  Not used with per-node fields,
+ * Remark III or a Scheme-B source with unequal rates (these calls succeed, and
+ * the run keeps its single sweeps).
  * mode: -1 on in the library's pick, 0 off, k >= 1 on in shape k - 1.
  * lbm_multi_step_shape: steps per pass, tile rows and waves per workgroup of a
  * shape (the D2Q9 tile is 66 - 2 steps nodes wide, 34 - 2 steps in shapes 5

@@ -26,14 +26,16 @@ hipError_t multi_shape(const Dims &dm, const Geom &g, const void *coefs, const v
                            (const Coefs<TC> *)coefs, (const TS *)fin, (TS *)fout, (const TP *)pin, (TP *)pout, \
                            tiles_x, flag);                                                                \
         break;
-#define LBM_MULTI6(S, K)                                                         \
-    LBM_MULTI(S, K, 0, 0) LBM_MULTI(S, K, 0, 1) LBM_MULTI(S, K, 0, 2)             \
-    LBM_MULTI(S, K, 1, 0) LBM_MULTI(S, K, 1, 1) LBM_MULTI(S, K, 1, 2)
+#define LBM_MULTI4(S, K) LBM_MULTI(S, K, 0, 1) LBM_MULTI(S, K, 0, 2) LBM_MULTI(S, K, 1, 1) LBM_MULTI(S, K, 1, 2)
+#define LBM_MULTI6(S, K) LBM_MULTI(S, K, 0, 0) LBM_MULTI(S, K, 1, 0) LBM_MULTI4(S, K)
     switch (code) {
-        LBM_MULTI6(0, 0) LBM_MULTI6(0, 1) LBM_MULTI6(1, 0) LBM_MULTI6(1, 1) LBM_MULTI6(2, 0) LBM_MULTI6(2, 1)
+        LBM_MULTI6(0, 0) LBM_MULTI6(0, 1) LBM_MULTI6(1, 0) LBM_MULTI6(1, 1)
+        // Scheme B with unequal rates runs the general sweep (general_path)
+        LBM_MULTI4(2, 0) LBM_MULTI4(2, 1)
         default: return hipErrorInvalidValue;
     }
 #undef LBM_MULTI6
+#undef LBM_MULTI4
 #undef LBM_MULTI
     return hipGetLastError();
 }

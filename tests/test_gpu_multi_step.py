@@ -343,6 +343,29 @@ def test_rollout_function_called_directly():
     assert torch.equal(*grads)
 
 
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_scheme_b_with_unequal_rates_keeps_single_sweeps(prec):
+    """Its passes are accepted and change nothing: the general sweep runs, also
+    for recorded steps and after the tuner."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    spec = _spec(60, 41, prec, source="B", rates="unequal")
+    phi0 = W.noise_field((41, 60), 11)
+    out = []
+    for prepare in (lambda s: None, lambda s: s.set_multi_step(True), lambda s: s.set_multi_step(True, 3),
+                    lambda s: s.set_two_step(True), lambda s: s.set_two_step(False)):
+        s = lbm.Lbm(spec).init(phi0)
+        prepare(s)
+        s.step(19)
+        out.append(s.phi())
+    s = lbm.Lbm(spec).init(phi0)
+    assert "steps per pass" not in s.tune(reps=1)
+    s.step(19)
+    out.append(s.phi())
+    assert all(torch.equal(out[0], o) for o in out[1:])
+
+
 def _rollout_inputs(nx=256, ny=256, prec="f64"):
     import torch
 
