@@ -61,6 +61,78 @@ def test_every_shape_bit_identical(prec, shape, nx, ny, source, wall, rates):
     _compare(_spec(nx, ny, prec, source, wall, rates), lambda s: s.set_multi_step(True, shape))
 
 
+@pytest.mark.parametrize("shape", range(8))
+@pytest.mark.parametrize("nx,ny,wall,rates", [(100, 37, False, "equal"), (59, 31, True, "unequal"), (64, 64, False, "1.3")])
+def test_history_of_the_whole_grid_f64(shape, nx, ny, wall, rates):
+    """The FP64 history (8 bytes a node) after each call, up to the last row."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    spec = _spec(nx, ny, "f64", "A", wall, rates)
+    phi0 = W.noise_field((ny, nx), 13)
+    a, b = lbm.Lbm(spec).init(phi0), lbm.Lbm(spec).init(phi0)
+    a.set_two_step(False)
+    b.set_multi_step(True, shape)
+    for n in STEPS:
+        a.step(n)
+        b.step(n)
+        assert torch.equal(a.p[:8 * nx * ny], b.p[:8 * nx * ny]), n
+
+
+def _graph_specs():
+    yield _spec(96, 70, "f32"), W.noise_field((70, 96), 19)
+    yield _spec(40, 33, "f64", wall=True, rates="unequal"), W.noise_field((33, 40), 20)
+    spec, phi0, _ = W.d3q19_walls_source((20, 18, 22), precision="f32")
+    yield spec, phi0
+
+
+@pytest.mark.parametrize("two", [False, True])
+@pytest.mark.parametrize("i", range(3))
+def test_graphs_without_longer_passes_identical(i, two):
+    """Graph replays of single sweeps and of two-step passes, with the passes of
+    several steps (launched directly) off: against direct launches, the other
+    workgroup order and the default run, after several replays from either
+    buffer with other work between them."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    spec, phi0 = list(_graph_specs())[i]
+    runs = []
+    for flags in (0, lbm.FLAG_NO_GRAPH, lbm.FLAG_NO_XCD_REMAP):
+        s = lbm.Lbm(spec, flags=flags).init(phi0)
+        s.set_two_step(two)
+        runs.append(s)
+    runs.append(lbm.Lbm(spec).init(phi0))
+    for n in (100, 33, 64, 97):
+        phis = []
+        for s in runs:
+            s.step(n)
+            phis.append(s.phi())
+            s.reduce(phis[-1])
+        assert all(torch.equal(phis[0], p) for p in phis[1:]), n
+        assert len({s.current() for s in runs}) == 1
+
+
+@pytest.mark.parametrize("i", range(3))
+def test_launch_variants_of_single_sweeps_identical(i):
+    """Non-temporal accesses, chunks and block orders of the single sweeps
+    themselves (longer passes ignore the first two), against the default run."""
+    import torch
+
+    from paper_1603_09577_amd import lbm
+    spec, phi0 = list(_graph_specs())[i]
+    ref = lbm.Lbm(spec).init(phi0)
+    ref.step(70)
+    want = ref.phi()
+    for nt, chunk, fl in ((1, 1, 0), (0, 3, 0), (1, 5, 0), (0, 3, lbm.FLAG_NO_XCD_REMAP), (1, 2, lbm.FLAG_NO_XCD_REMAP)):
+        s = lbm.Lbm(spec, flags=fl).init(phi0)
+        s.set_two_step(False)
+        s.set_nontemporal(nt)
+        s.set_chunk(chunk)
+        s.step(70)
+        assert torch.equal(s.phi(), want), (nt, chunk, fl)
+
+
 @pytest.mark.parametrize("nx,ny,prec", [(64, 64, "f64"), (130, 120, "f64"), (200, 200, "f64"), (120, 90, "f32"),
                                          (190, 200, "f16"), (300, 300, "f32"), (250, 250, "f32"), (300, 310, "f64"), (500, 500, "f32"),
                                          (1000, 723, "f32"), (1100, 1200, "f16"), (1100, 1200, "f64")])
