@@ -295,6 +295,7 @@ void pack(const HostModel &m, Coefs<TC> &c) {
     c.srate = (TC)m.srate;
     c.shalf = (TC)(0.5 * m.srate);
     c.oms = (TC)(1.0 - m.srate);
+    c.omh = (TC)(0.5 * (1.0 - m.srate));
     c.k0scale = (TC)m.k0scale;
     c.nb = m.nb; c.ncb = m.ncb; c.nk = m.nk; c.nr = m.nr;
     for (int p = 0; p < kMaxP; ++p) { c.bq[p] = (TC)m.bq[p]; c.bqp[p] = (TC)m.bqp[p]; }

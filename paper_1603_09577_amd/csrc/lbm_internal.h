@@ -70,7 +70,7 @@ struct Coefs {
     TC sn[9];             // D2Q9: rates over the row norms
     TC phi_ref;
     TC srate;             // common non-flux rate s (equal-rate path)
-    TC shalf, oms;        // s / 2 and 1 - s
+    TC shalf, oms, omh;   // s / 2, 1 - s and (1 - s) / 2
     TC k0scale;           // 3 / d = dG / d(K0 k)
     int nb, ncb, nk, nr;  // used coefficient counts
     // rational flux B_a = (sum b[a] phi^p) / Q(phi) (Remark III only): Q and Q',
