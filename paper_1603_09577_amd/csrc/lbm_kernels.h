@@ -36,8 +36,13 @@ struct HistType { using T = float; };
 template <>
 struct HistType<double> { using T = double; };
 
-template <typename TS>
-constexpr bool is_f32 = std::is_same<TS, float>::value;
+// Whether the equal-rate collision keeps the mass with the exact balance of
+// collide_node: FP32 storage, and FP64 on D2Q9.  FP16 storage rounds far more than
+// it saves, and the D3Q19 kernels of FP16 and FP64 are short of the registers it
+// takes (129^3 periodic FP16 with a source 30.3 -> 37.1 us per step; FP64 lines with
+// a source spill).
+template <int Q, typename TS>
+constexpr bool exact_mass = std::is_same<TS, float>::value || (Q == 9 && std::is_same<TS, double>::value);
 
 // Plain or non-temporal (streaming) accesses of the distribution planes.  The
 // streaming form skips cache allocation: a gain when the state is far larger
@@ -521,14 +526,14 @@ __device__ __forceinline__ T tree_sum(const T *v) {
 // without its arithmetic.
 // EQR: 0 unequal rates (moment space), 1 all non-flux rates equal, 2 all equal to
 // 1 (the populations enter only through their moments; the same bits as 1).
-// F32: the populations are stored in FP32 (the exact mass balance below).
-template <int Q, typename TC, int EQR, bool SRC, bool KVAR, int NP, bool SB = false, bool F32 = false, bool KF = false>
+// EM: the exact mass balance (exact_mass).
+template <int Q, typename TC, int EQR, bool SRC, bool KVAR, int NP, bool SB = false, bool EM = false, bool KF = false>
 __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, const TC *h, TC pp_off, uint32_t n,
                                            const double *kfield, const double *rfield, bool rem3, TC *out,
                                            SrcLevel<TC> *cur = nullptr, const SrcLevel<TC> *prev = nullptr) {
     using L = Lattice<Q>;
     constexpr int D = L::dim, P = (Q - 1) / 2;
-    constexpr bool EXACT = EQR != 0 && F32;   // the exact mass balance
+    constexpr bool EXACT = EQR != 0 && EM;
     TC g0n[6];
     const bool kfon = KF && kfield != nullptr;   // uniform across the launch
     if (kfon) g0_of_field<D>(cf, kfield, n, g0n);
@@ -676,8 +681,8 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
                 eo[i] = TC(2) * f2 * E[3 + i];
             }
         }
-        // The two populations of a pair, (1 - s) h + even +- 3 w1 odd.  In FP32
-        // they are formed as m + g and 2 m - (m + g): their sum is then 2 m with no
+        // The two populations of a pair, (1 - s) h + even +- 3 w1 odd.  With
+        // EXACT they are formed as m + g and 2 m - (m + g): their sum is then 2 m with no
         // rounding, so that what the pair takes from the node's mass is known
         // exactly (see the mass balance below).
         TC mass = SB ? Rx : Se;
@@ -865,16 +870,15 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
     // Mass balance.  Collision conserves sum_k g_k and the Scheme-A source adds
     // exactly Se to it (Eq. 9 sums to R over k; Scheme B adds R), so the rest
     // population takes the remainder.  The map is unchanged in exact arithmetic;
-    // in FP32 it stops the drift that rounded weights (sum_k w_k = 1 + O(1e-8))
+    // it stops the drift that rounded weights (in FP32 sum_k w_k = 1 + O(1e-8))
     // would otherwise add to the mass at every step.
-    // Stored in FP32, with equal rates, it is h_0 plus the changes of the pairs, each
-    // exact (FP16 storage rounds far more than this saves, and its kernels are short
-    // of registers: D3Q19 periodic with a source 129^3 30.3 -> 37.1 us per step).
-    // As (phi + Se) less the sum of the others it rounds four times at the size of
+    // The exact form is h_0 plus the changes of the pairs, none of them rounded.  As
+    // (phi + Se) less the sum of the others it rounds four times at the size of
     // phi, by the same amounts wherever the field is smooth or steady, and the
-    // mass drifts: relative L2 error of phi after 8000 steps, 64 x 200 between
+    // mass drifts: relative L2 error of phi after 8000 steps, FP32 64 x 200 between
     // walls without a source 1.1e-5 -> 2e-7, periodic 100 x 90 with a source 2e-7 to
-    // 2e-6 -> 2e-8 to 4e-8.
+    // 2e-6 -> 2e-8 to 4e-8; FP64 after 4000 steps against 80-bit arithmetic, 90 rows
+    // between walls 2.9e-15 -> 8e-17, with a source 3.2e-15 -> 2e-16.
     if constexpr (!EXACT) out[0] = (phio + Se) - tree_sum<Q - 1>(out + 1);
 
     return phio;
@@ -900,7 +904,7 @@ __device__ __forceinline__ void sweep_node(const Geom &g, const Coefs<TC> *__res
     // history read issued together with the gathers, so its latency overlaps theirs
     const TC pp_off = (SRC || rem3) ? (TC)*at<O32>(pin, n) : TC(0);
     TC out[Q];
-    const TC phio = collide_node<Q, TC, EQR, SRC, KVAR, NP, SB, is_f32<TS>, KF>(cf, h, pp_off, n, kfield, rfield, rem3, out);
+    const TC phio = collide_node<Q, TC, EQR, SRC, KVAR, NP, SB, exact_mass<Q, TS>, KF>(cf, h, pp_off, n, kfield, rfield, rem3, out);
     if (SRC || rem3) *at<O32>(pout, n) = (typename HistType<TS>::T)phio;
 
     if constexpr (O32) {
@@ -1056,7 +1060,7 @@ __device__ __forceinline__ void sweep2_tile(const Geom &g, const Coefs<TC> *__re
                 h[k] = wl ? -(TC)hs[i][k] + cf->ew[cy == 1 ? 0 : 1][k] : (TC)hs[i][k];
             }
             TC out[9];
-            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB, is_f32<TS>>(row_cf(), h, ps[i], 0u, nullptr, nullptr, false, out,
+            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB, exact_mass<9, TS>>(row_cf(), h, ps[i], 0u, nullptr, nullptr, false, out,
                                                                         HAND ? &lev[HAND ? i : 0] : nullptr);
 #pragma unroll
             for (int k = 0; k < 9; ++k) lf[k][r][lane] = to_store<TS>(out[k]);
@@ -1087,7 +1091,7 @@ __device__ __forceinline__ void sweep2_tile(const Geom &g, const Coefs<TC> *__re
             }
             const TC pp_off = SRC ? (TC)*at<true>(pin, n) : TC(0);
             TC out[9];
-            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB, is_f32<TS>>(row_cf(), h, pp_off, n, nullptr, nullptr, false, out,
+            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB, exact_mass<9, TS>>(row_cf(), h, pp_off, n, nullptr, nullptr, false, out,
                                                                         HAND ? &lev[HAND ? i : 0] : nullptr);
 #pragma unroll
             for (int k = 0; k < 9; ++k) lf[k][r][lane] = to_store<TS>(out[k]);
@@ -1111,7 +1115,7 @@ __device__ __forceinline__ void sweep2_tile(const Geom &g, const Coefs<TC> *__re
             }
             const TC pp_off = (SRC && !HAND) ? (TC)lp[HAND ? 0 : r][lane] : TC(0);
             TC out[9];
-            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB, is_f32<TS>>(row_cf(), h, pp_off, 0u, nullptr, nullptr, false, out,
+            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, NP, SB, exact_mass<9, TS>>(row_cf(), h, pp_off, 0u, nullptr, nullptr, false, out,
                                                                         nullptr, prev);
             bad |= !__builtin_isfinite(phio);
             if (x < nx && y < ny) {
@@ -1297,7 +1301,7 @@ k_sweep2_3d(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict
                         h[k] = wl ? -(TC)hc[j][k] + cf->ew[cz == 1 ? 0 : 1][k] : (TC)hc[j][k];
                     }
                     TC out[19];
-                    const TC phio = collide_node<19, TC, EQ, SRC, KVAR, NP, SB, is_f32<TS>>(
+                    const TC phio = collide_node<19, TC, EQ, SRC, KVAR, NP, SB, exact_mass<19, TS>>(
                         cf, h, SRC ? (TC)pc[j] : TC(0), 0u, nullptr, nullptr, false, out,
                         HAND ? &lev0[HAND ? j : 0] : nullptr);
                     bad |= !__builtin_isfinite(phio);
@@ -1338,7 +1342,7 @@ k_sweep2_3d(const Geom g, const Coefs<TC> *__restrict__ cf, const TS *__restrict
                     }
                 }
                 TC out[19];
-                const TC phio = collide_node<19, TC, EQ, SRC, KVAR, NP, SB, is_f32<TS>>(cf, h, pp_off, 0u, nullptr, nullptr,
+                const TC phio = collide_node<19, TC, EQ, SRC, KVAR, NP, SB, exact_mass<19, TS>>(cf, h, pp_off, 0u, nullptr, nullptr,
                                                                              false, out, nullptr, prev);
                 bad |= !__builtin_isfinite(phio);
                 if (x < nx && y < ny) {

@@ -106,7 +106,7 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
             h[k] = wl ? -v + cf->ew[cy == 1 ? 0 : 1][k] : v;
         }
         const TC pp = SRC ? (TC)*at<true>(pin, (uint32_t)yg * g.nx + (uint32_t)xg) : TC(0);
-        const TC phi0 = collide_node<9, TC, EQ, SRC, KVAR, 3, SB, is_f32<TS>>(cf, h, pp, 0u, nullptr, nullptr, false, out,
+        const TC phi0 = collide_node<9, TC, EQ, SRC, KVAR, 3, SB, exact_mass<9, TS>>(cf, h, pp, 0u, nullptr, nullptr, false, out,
                                                                   SRC ? &lev[SRC ? i : 0] : nullptr);
         if (REC && own && r >= H && r < TR - H && yl < ny) store(0, yl, out, phi0);
 #pragma unroll
@@ -136,7 +136,7 @@ __device__ __forceinline__ void sweep_multi_tile(const Geom &g, const Coefs<TC> 
                 h[k] = wl ? -v + cf->ew[cy == 1 ? 0 : 1][k] : v;
             }
             SrcLevel<TC> *lv = SRC ? &lev[SRC ? i : 0] : nullptr;
-            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, 3, SB, is_f32<TS>>(cf, h, TC(0), 0u, nullptr, nullptr, false, out,
+            const TC phio = collide_node<9, TC, EQ, SRC, KVAR, 3, SB, exact_mass<9, TS>>(cf, h, TC(0), 0u, nullptr, nullptr, false, out,
                                                                       LAST ? nullptr : lv, lv);
             if constexpr (!LAST) {
 #pragma unroll

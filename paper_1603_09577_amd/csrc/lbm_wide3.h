@@ -142,7 +142,7 @@ k_sweep2_3dw(const Geom g, const Coefs<TC> *__restrict__ cfa, const TS *__restri
             for (int k = 0; k < 19; ++k) h[k] = (TC)hc[k];
             if (WALL && zg == 0) wall_fix<1>(cf, h, h);
             if (WALL && zg == nz - 1) wall_fix<-1>(cf, h, h);
-            const TC phio = collide_node<19, TC, EQ, SRC, KVAR, NP, SB, is_f32<TS>>(cf, h, SRC ? (TC)pc : TC(0), 0u, nullptr, nullptr,
+            const TC phio = collide_node<19, TC, EQ, SRC, KVAR, NP, SB, exact_mass<19, TS>>(cf, h, SRC ? (TC)pc : TC(0), 0u, nullptr, nullptr,
                                                                          false, out, SRC ? &lev0 : nullptr);
             bad |= !__builtin_isfinite(phio);
             if (SRC) ph0 = (TP)phio;
@@ -179,7 +179,7 @@ k_sweep2_3dw(const Geom g, const Coefs<TC> *__restrict__ cfa, const TS *__restri
                 if (zc2 == 0) wall_fix<1>(cf, own, h);
                 if (zc2 == nz - 1) wall_fix<-1>(cf, own, h);
             }
-            const TC phio = collide_node<19, TC, EQ, SRC, KVAR, NP, SB, is_f32<TS>>(cf, h, SRC ? (TC)ph1 : TC(0), 0u, nullptr, nullptr,
+            const TC phio = collide_node<19, TC, EQ, SRC, KVAR, NP, SB, exact_mass<19, TS>>(cf, h, SRC ? (TC)ph1 : TC(0), 0u, nullptr, nullptr,
                                                                          false, out, nullptr, SRC ? &lev1 : nullptr);
             bad |= !__builtin_isfinite(phio);
             if (x0 + lane < nx && y0 + wv - 1 < ny) {
