@@ -168,11 +168,14 @@ int lbm_init(lbm_ctx *ctx, const double *phi0_dev, void *f_a, void *f_b, void *p
              void *stream);
 
 /* Advance nsteps time steps (Eq. 2 with the Scheme-A source, anti-bounce-back
- * walls), one fused stream-collide sweep per step.  Runs of 32 sweeps are
- * replayed from a HIP graph captured on first use (an internal stream; the
- * graph is launched on the caller's stream) unless LBM_FLAG_NO_GRAPH is set,
- * a divergence check is enabled or lbm_tune found direct launches faster.  Asynchronous unless a divergence check is
- * due (lbm_set_check), in which case it synchronises the stream and returns
+ * walls): passes of several steps where they are on (lbm_set_multi_step,
+ * lbm_set_two_step), one fused stream-collide sweep per step otherwise and for
+ * the last few steps of a call.  Passes of lbm_set_multi_step are launched
+ * directly; otherwise runs of 32 steps are replayed from a HIP graph captured on
+ * first use (an internal stream; the graph is launched on the caller's stream)
+ * unless LBM_FLAG_NO_GRAPH is set, a divergence check is enabled or lbm_tune
+ * found direct launches faster.  Asynchronous unless a divergence check is due
+ * (lbm_set_check), in which case it synchronises the stream and returns
  * LBM_E_DIVERGED when a non-finite phi appeared. */
 int lbm_step(lbm_ctx *ctx, int nsteps, void *stream);
 
@@ -183,8 +186,8 @@ int lbm_sweep(lbm_ctx *ctx, const void *f_in, void *f_out, void *p, void *stream
 
 /* nsteps sweeps from (f_in, p_in) with every state kept: the state after sweep
  * i (from 0) goes to f_out + i f_step bytes, its history to p_out + i p_step
- * (runs without a Scheme-A source or Remark III neither read nor write a
- * history).  The steps are multiples of 256 that hold a distribution buffer and
+ * (runs with none of a Scheme-A source, Remark III and per-node fields in Scheme
+ * A neither read nor write a history).  The steps are multiples of 256 that hold a distribution buffer and
  * a history; inputs and outputs must not overlap.  Bit for bit nsteps calls of
  * lbm_sweep; runs that qualify take passes of several steps
  * (lbm_set_multi_step).  Does not touch the bound buffers or the step counter. */
@@ -290,11 +293,11 @@ int lbm_two_step_shape(const lbm_ctx *ctx, int shape, int *rows, int *waves);
  * where nx is a multiple of 64.  Passes run
  * in pairs (their lengths may differ), so state and history end where single
  * sweeps leave them; the last one to three steps of a call use single sweeps.
- * On by default where it applies, in a shape picked for the grid, and
- * launched directly (no graphs); D2Q9 grids whose width fits 62-node columns
- * much better start with lbm_set_two_step's passes, small D3Q19 grids with single
- * sweeps, and D3Q19 where lines save no column mostly with lbm_set_two_step's.  lbm_tune times
- * the shapes; lbm_set_two_step turns it off.  Not used with per-node fields,
+ * On by default where it applies, in a shape picked for the grid, and launched
+ * directly (no graphs).  D2Q9 grids whose width fits 62-node columns much better
+ * start with lbm_set_two_step's passes, small D3Q19 grids with single sweeps, and
+ * D3Q19 grids where lines save no column mostly with lbm_set_two_step's.  lbm_tune
+ * times the shapes; lbm_set_two_step turns it off.  Not used with per-node fields,
  * Remark III or a Scheme-B source with unequal rates (these calls succeed, and
  * the run keeps its single sweeps).
  * mode: -1 on in the library's pick, 0 off, k >= 1 on in shape k - 1.

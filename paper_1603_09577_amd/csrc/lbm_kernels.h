@@ -105,7 +105,7 @@ __device__ __forceinline__ void store_planes(TS *__restrict__ base, uint64_t pla
 // wave.  S, FP64: the instruction is spelled out.  The compiler picks the form
 // that overwrites its addend and copies each scalar coefficient to two vector
 // registers first: 34 copies per node of a D2Q9 pass with K(phi) and a source
-// among 116 FP64 operations, 16 left (us per step 512^2 3.63 -> 3.50, 1024^2
+// among about 110 FP64 operations, 16 left (us per step 512^2 3.63 -> 3.50, 1024^2
 // 12.30 -> 12.00).  Neither a nor x is the direct result of a transcendental
 // instruction, nor is the result a DPP operand, so no wait state is due.
 template <bool S>
@@ -614,9 +614,10 @@ __device__ __forceinline__ TC collide_node(const Coefs<TC> *__restrict__ cf, con
         // d = T - v / (3 w1), q = d - (1 - w2 / w1) T: the factor 3 w1 goes
         // into the last multiply-add of each population.
         // With s = 1 the first term is gone.
-        // Bound by vector issue on large grids: 105 instead of 131 operations
-        // of a D2Q9 node with K(phi) and the Scheme-A source before the factors
-        // moved to the host.
+        // Bound by vector issue on large grids: a D2Q9 node with K(phi) and the
+        // Scheme-A source takes 106 FP32 operations in a pass, 97 with s = 1 (26
+        // more before the factors moved to the host), and 129 where it rebuilds
+        // the previous level's source terms.
         constexpr double w1 = L::w(1), w2 = L::w(Q - 1), kj = 1.0 / (L::jnorm * 1.5 * w1);
         constexpr bool ONE = EQR == 2;
         const TC s = ONE ? TC(1) : cf->srate, sh = ONE ? TC(0.5) : cf->shalf;

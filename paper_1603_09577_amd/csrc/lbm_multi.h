@@ -11,7 +11,8 @@
 // storage type in LDS as a store would round them, so the result equals T
 // single sweeps bit for bit.
 //
-// One LDS copy serves all steps.  Slot k of a cell holds, before an odd step,
+// One LDS copy serves all steps: the A-A pattern of in-place streaming (Bailey et
+// al., 2009), on a tile instead of the grid.  Slot k of a cell holds, before an odd step,
 // the population the cell gathers from direction k; an odd step reads its own
 // cell's nine slots and leaves population k in its own slot opp(k); an even
 // step s > 0 gathers population k from slot opp(k) of the cell at -c_k and
@@ -28,8 +29,8 @@
 // its 84 MB through the Infinity Cache takes with the ramp of a launch, and on
 // a small grid most of a pass is launch, first loads and last stores.  With
 // six steps the bytes per step fall to a third and what is left is vector
-// issue (about 110 operations per node and step, 1.45 times that with the
-// halo) and the barriers.  us per step before -> after, FP32 with K(phi) and a
+// issue (97 operations per node and step with rates 1, 106 with equal and 133 with
+// unequal rates, 1.45 times that with the halo) and the barriers.  us per step before -> after, FP32 with K(phi) and a
 // source unless noted: 64^2 FP64 unequal rates 2.41 -> 1.14, 32-wide 0.89;
 // 256^2 3.5 -> 1.23; 1024^2 8.0 -> 5.8, FP64 14.3 -> 12.0; 1000 x 723 channel with
 // unequal rates 7.9 -> 5.1; 2048^2 44 -> 18.9, FP64 80 -> 48; 4000 x 2500 FP16 54 ->

@@ -14,7 +14,7 @@ hipError_t multi_shape(const Dims &dm, const Geom &g, const void *coefs, const v
     const uint32_t tiles_x = (g.nx + TW - 1) / TW, tiles_y = (g.ny + TH - 1) / TH;
     const dim3 grid(tiles_x * tiles_y), block(64 * NW);
     // source: none, Scheme A (history pin -> pout) or Scheme B (no history)
-    // collision: moment space, equal rates, rates 1.  The last saves 10 of 145
+    // collision: moment space, equal rates, rates 1.  The last saves 9 of 106
     // operations of a node where issue is the bound (us per step with a source:
     // FP32 1024^2 6.20 -> 5.84, 4000 x 2500 50.1 -> 46.2; FP64 1024^2 12.28 ->
     // 11.95; FP16 4000 x 2500 44.7 -> 41.6)
